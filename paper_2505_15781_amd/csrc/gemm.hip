@@ -3,7 +3,8 @@
 // The active rows of a denoising step (Algorithm 1 line 3: the transformer runs on x[M_{t-1}] only)
 // are the M dimension; their count lives on the device, so kernels bound M by *m_dev.
 //
-// bf16, K a multiple of 64 (every model shape): `gemm_dma`. MFMA 32x32x16 tiles; the A and W tiles of
+// bf16, K a multiple of 64 (every model shape): `gemm_dma`. Tiles of 192 rows or columns and more by 256 take the
+// 8-wavefront loop of gemm_pingpong.h; what follows is about the 4-wavefront loop of the others. MFMA 32x32x16 tiles; the A and W tiles of
 // a K step travel from global memory straight into LDS (global_load_lds_dwordx4: 16 bytes per lane, lane i
 // lands at base + 16 i) through a ring of STAGES buffers, so up to STAGES-1 tiles are in flight without
 // holding registers. The LDS layout XOR-swizzles the 16-byte chunks of a 128-byte row with (row >> 1)
@@ -15,8 +16,9 @@
 // Two launch options, both measured: `stagger` starts each workgroup's K loop at a different tile (unsplit
 // launches otherwise sweep the same columns of A and W in step and crowd a few memory channels: up to 25 %
 // on the widest projection at <= 128 rows); `xcd_group` renumbers workgroups so that the 32 that run
-// together on one XCD (hardware sends workgroup i to XCD i mod 8) cover a compact 4 x 8 block of tiles and
-// share their A and W tiles through that XCD's L2 (hit rate 54 % -> 78 % and 5 % less time at 6144 rows).
+// together on one XCD (hardware sends workgroup i to XCD i mod 8) cover a compact block of tiles, 6 rows high, and
+// share their A and W tiles through that XCD's L2 (heights 3 to 12 are within 4 % of each other at 6144 rows, 1 and 24
+// cost 5-15 %).
 // bf16, other K (multiple of 8): `gemm_reg`, register-staged tiles. fp32 mode / anything else: `gemm_simt`.
 #include <atomic>
 
@@ -155,11 +157,11 @@ constexpr KindInfo kKinds[] = {
     {64, 128},    // GEMM_DMA_64x128   <2,1,1,4> 4 stages
     {128, 128},   // GEMM_DMA_128x128  <2,2,2,2> 3 stages
     {128, 256},   // GEMM_DMA_128x256  <2,4,2,2> 3 stages
-    {256, 256},   // GEMM_DMA_256x256  <4,4,2,2> 2 stages
+    {256, 256},   // GEMM_DMA_256x256  <4,2,2,4> 2 stages, 8 wavefronts
     {128, 96},    // GEMM_DMA_128x96   <1,3,4,1> 4 stages
     {128, 192},   // GEMM_DMA_128x192  <2,3,2,2> 3 stages
-    {256, 192},   // GEMM_DMA_256x192  <4,3,2,2> 2 stages
-    {192, 256},   // GEMM_DMA_192x256  <3,4,2,2> 2 stages
+    {256, 192},   // GEMM_DMA_256x192  <2,3,4,2> 2 stages, 8 wavefronts
+    {192, 256},   // GEMM_DMA_192x256  <3,2,2,4> 2 stages, 8 wavefronts
 };
 static_assert(sizeof(kKinds) / sizeof(kKinds[0]) == GEMM_DMA_LAST + 1, "one entry per gemm_dma kind");
 static_assert(GEMM_DMA_192x256 == DKV_GEMM_DMA_192x256 && GEMM_REG_64x128 == DKV_GEMM_REG_64x128 &&

@@ -35,6 +35,30 @@ template <int BM, int WN> struct EpiSmem {
     int redi[BM][WN];        //           arg maxima
 };
 
+// The column statistics that the WN wavefronts of a row left in LDS, merged into the tile's record of the row.
+template <int BM, int WN, int NTHREADS>
+__device__ __forceinline__ void merge_head_columns(const EpiSmem<BM, WN> &sm, const GemmEpilogue &ep, int m0, int M, int tile_n) {
+    for (int r = threadIdx.x; r < BM; r += NTHREADS) {
+        const int m = m0 + r;
+        if (m < M) {
+            float mx = sm.red[r][0], sum = sm.red2[r][0];
+            int best = sm.redi[r][0];
+#pragma unroll
+            for (int w = 1; w < WN; ++w) {      // ascending columns: ties keep the lower id
+                const float om = sm.red[r][w], os = sm.red2[r][w];
+                if (om > mx) {
+                    sum = sum * __expf(mx - om) + os;      // mx == -inf only with sum == 0
+                    mx = om;
+                    best = sm.redi[r][w];
+                } else if (om > -INFINITY) {
+                    sum += os * __expf(om - mx);
+                }
+            }
+            ep.head_part[(size_t)m * ep.head_tiles + tile_n] = HeadPartial{mx, sum, best, 0};
+        }
+    }
+}
+
 template <int EPI, int MT, int NT, int WM, int WN>
 __device__ __forceinline__ void run_epilogue(f32x16 (&acc)[MT][NT], const GemmEpilogue &ep, void *smem_raw,
                                              int m0, int n0, int M, int N, int tile_n, int tiles_n) {
@@ -105,24 +129,6 @@ __device__ __forceinline__ void run_epilogue(f32x16 (&acc)[MT][NT], const GemmEp
             }
         if (__any(nan) && lane == 0) atomicOr(ep.status, 1 /* STATUS_NAN */);
         __syncthreads();
-        for (int r = tid; r < BM; r += NTHREADS) {
-            const int m = m0 + r;
-            if (m < M) {
-                float mx = sm.red[r][0], sum = sm.red2[r][0];
-                int best = sm.redi[r][0];
-#pragma unroll
-                for (int w = 1; w < WN; ++w) {      // ascending columns: ties keep the lower id
-                    const float om = sm.red[r][w], os = sm.red2[r][w];
-                    if (om > mx) {
-                        sum = sum * __expf(mx - om) + os;      // mx == -inf only with sum == 0
-                        mx = om;
-                        best = sm.redi[r][w];
-                    } else if (om > -INFINITY) {
-                        sum += os * __expf(om - mx);
-                    }
-                }
-                ep.head_part[(size_t)m * ep.head_tiles + tile_n] = HeadPartial{mx, sum, best, 0};
-            }
-        }
+        merge_head_columns<BM, WN, NTHREADS>(sm, ep, m0, M, tile_n);
     }
 }

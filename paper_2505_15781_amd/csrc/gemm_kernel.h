@@ -30,6 +30,57 @@ __device__ __forceinline__ constexpr int waitcnt_imm(int n, bool lgkm0) {
 
 #include "gemm_epilogue.h"
 
+constexpr int XCD_ROWS = 6;   // tile rows of a group in the XCD-grouped order
+
+// One unit of work of a workgroup: a tile of the product and the part of its K range.
+struct TileWork {
+    int m0, n0, kt0, nk, slot;
+};
+
+// Work of this workgroup: one (tile, K slice) given by the 3-D grid, or, in fractional mode, the K-tile
+// units [w u, (w+1) u) of the sequence "tile 0's K tiles, tile 1's K tiles, ..." (tiles column-fastest),
+// which may end one output tile and begin the next. The part of tile t done by workgroup w goes to
+// partial slot w - floor(t * kt_total / u); the host only uses shares for which every tile gets the same
+// number of parts.
+template <int BM, int BN>
+__device__ __forceinline__ TileWork next_tile_work(int &unit, int unit_end, int frac_units, int kt_total, int kt_per_split,
+                                                   int tiles_n, int flags) {
+    TileWork w;
+    if (frac_units) {
+        const int tile = unit / kt_total;
+        w.kt0 = unit - tile * kt_total;
+        w.nk = min(kt_total - w.kt0, unit_end - unit);
+        w.m0 = (tile / tiles_n) * BM;
+        w.n0 = (tile % tiles_n) * BN;
+        w.slot = blockIdx.x - (tile * kt_total) / frac_units;
+        unit += w.nk;
+    } else {
+        int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+        if (flags & GEMM_FLAG_XCD_GROUP) {
+            // position of this workgroup in the order "XCD 0's share, XCD 1's share, ..." of the sequence
+            // (K slice, group of XCD_ROWS tile rows, tile column, tile row within the group)
+            const int gx = gridDim.x, gy = gridDim.y, total = gx * gy * gridDim.z;
+            const int id = bx + gx * (by + gy * bz);
+            // XCD x runs the ids x, x + 8, ...: total / 8 of them, one more for x < total % 8
+            const int pos = (id & 7) * (total >> 3) + min(id & 7, total & 7) + (id >> 3);
+            bz = pos / (gx * gy);
+            const int p2 = pos - bz * gx * gy;
+            const int grp = p2 / (XCD_ROWS * gx), within = p2 - grp * XCD_ROWS * gx;
+            const int rows_in_grp = min(XCD_ROWS, gy - grp * XCD_ROWS);
+            by = grp * XCD_ROWS + within % rows_in_grp;
+            bx = within / rows_in_grp;
+        }
+        w.m0 = by * BM;
+        w.n0 = bx * BN;
+        w.kt0 = bz * kt_per_split;
+        w.nk = min(kt_total, w.kt0 + kt_per_split) - w.kt0;
+        w.slot = bz;
+    }
+    return w;
+}
+
+#include "gemm_pingpong.h"
+
 template <int EPI, int MT, int NT, int WM, int WN, int STAGES>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_dma(const bf16_t *__restrict__ A,
                                                          const bf16_t *__restrict__ W, float *__restrict__ P,
@@ -44,6 +95,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dma(const bf16_t *__restric
     static_assert((STAGES - 2) * (CA + CW) < 64, "vmcnt is a 6-bit counter");
     extern __shared__ __attribute__((aligned(16))) uint4 lds[];
     static_assert(sizeof(EpiSmem<BM, WN>) <= STAGES * STAGE_CHUNKS * 16, "epilogue scratch fits the tile stages");
+    if constexpr (NW == 8) {
+        pingpong_tiles<EPI, MT, NT, WM, WN>(A, W, P, m_upper, m_cap, m_dev, N, K, kt_per_split, frac_units, flags, ep,
+                                            reinterpret_cast<unsigned char *>(lds));
+    } else {
 
     const int M = m_dev ? min(*m_dev, m_upper) : m_upper;
     const int kt_total = K / BK;
@@ -52,46 +107,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dma(const bf16_t *__restric
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t lds_base = (uint32_t)(size_t)(lds_ptr_t)lds;
 
-    // Work of this workgroup: one (tile, K slice) given by the 3-D grid, or, in fractional mode, the K-tile
-    // units [w u, (w+1) u) of the sequence "tile 0's K tiles, tile 1's K tiles, ..." (tiles column-fastest),
-    // which may end one output tile and begin the next. The part of tile t done by workgroup w goes to
-    // partial slot w - floor(t * kt_total / u); the host only uses shares for which every tile gets the same
-    // number of parts.
     const int tiles_n = (N + BN - 1) / BN;
     int unit = frac_units ? blockIdx.x * frac_units : 0;
     const int unit_end = frac_units ? min(unit + frac_units, tiles_n * ((m_upper + BM - 1) / BM) * kt_total) : 0;
   for (;;) {
-    int m0, n0, kt0, nk, slot;
-    if (frac_units) {
-        const int tile = unit / kt_total;
-        kt0 = unit - tile * kt_total;
-        nk = min(kt_total - kt0, unit_end - unit);
-        m0 = (tile / tiles_n) * BM;
-        n0 = (tile % tiles_n) * BN;
-        slot = blockIdx.x - (tile * kt_total) / frac_units;
-        unit += nk;
-    } else {
-        int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-        if (flags & GEMM_FLAG_XCD_GROUP) {
-            // position of this workgroup in the order "XCD 0's share, XCD 1's share, ..." of the sequence
-            // (K slice, group of 4 tile rows, tile column, tile row within the group)
-            const int gx = gridDim.x, gy = gridDim.y, total = gx * gy * gridDim.z;
-            const int id = bx + gx * (by + gy * bz);
-            // XCD x runs the ids x, x + 8, ...: total / 8 of them, one more for x < total % 8
-            const int pos = (id & 7) * (total >> 3) + min(id & 7, total & 7) + (id >> 3);
-            bz = pos / (gx * gy);
-            const int p2 = pos - bz * gx * gy;
-            const int grp = p2 / (4 * gx), within = p2 - grp * 4 * gx;
-            const int rows_in_grp = min(4, gy - grp * 4);
-            by = grp * 4 + within % rows_in_grp;
-            bx = within / rows_in_grp;
-        }
-        m0 = by * BM;
-        n0 = bx * BN;
-        kt0 = bz * kt_per_split;
-        nk = min(kt_total, kt0 + kt_per_split) - kt0;
-        slot = bz;
-    }
+    const TileWork tw = next_tile_work<BM, BN>(unit, unit_end, frac_units, kt_total, kt_per_split, tiles_n, flags);
+    const int m0 = tw.m0, n0 = tw.n0, kt0 = tw.kt0, nk = tw.nk, slot = tw.slot;
     if (m0 < M) {
     // first K tile of this workgroup's loop (the loop wraps around the slice)
     const int kt_rot = (flags & GEMM_FLAG_STAGGER) ? (int)((unsigned)(n0 / BN * 5 + m0 / BM * 3) % (unsigned)nk) : 0;
@@ -203,6 +224,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_dma(const bf16_t *__restric
     if (!frac_units || unit >= unit_end) break;
     __syncthreads();      // every wave is done with the LDS stages before the next part refills them
   }
+    }   // 4 wavefronts
 }
 
 template <int EPI, int MT, int NT, int WM, int WN, int STAGES>
@@ -253,15 +275,15 @@ int dispatch_dma(const void *A, const void *W, float *partial, int m_upper, int 
         case GEMM_DMA_128x256:
             return launch_dma<EPI, 2, 4, 2, 2, 3>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
         case GEMM_DMA_256x256:
-            return launch_dma<EPI, 4, 4, 2, 2, 2>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
+            return launch_dma<EPI, 4, 2, 2, 4, 2>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
         case GEMM_DMA_128x96:
             return launch_dma<EPI, 1, 3, 4, 1, 4>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
         case GEMM_DMA_128x192:
             return launch_dma<EPI, 2, 3, 2, 2, 3>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
         case GEMM_DMA_256x192:
-            return launch_dma<EPI, 4, 3, 2, 2, 2>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
+            return launch_dma<EPI, 2, 3, 4, 2, 2>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
         case GEMM_DMA_192x256:
-            return launch_dma<EPI, 3, 4, 2, 2, 2>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
+            return launch_dma<EPI, 3, 2, 2, 4, 2>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
     }
     dkv_set_error("kernel %d is not a tile kernel", p.kind);
     return DKV_E_UNSUPPORTED;

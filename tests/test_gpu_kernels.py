@@ -98,6 +98,21 @@ def test_projection_with_fused_swiglu_epilogue(kind, m, n, k):
     assert e.value.code == -3
 
 
+@pytest.mark.parametrize("kind", ["dma_256x256", "dma_256x192", "dma_192x256"])
+@pytest.mark.parametrize("k_tiles", [1, 2, 3, 4, 5, 9])
+@pytest.mark.parametrize("m,n", [(1, 4), (255, 193), (257, 258), (193, 512)])
+def test_eight_wavefront_tiles_at_short_k_and_tile_edges(kind, k_tiles, m, n):
+    """The two wavefront groups run one barrier apart and fetch two K tiles ahead: one to five K tiles take every exit
+    of that schedule; rows and columns just below and above a tile, widths that are no multiple of 4. fp32 sums of
+    64 k_tiles products: 1e-5 is far above their rounding."""
+    import paper_2505_15781_amd as P
+    k = 64 * k_tiles
+    x = D.normal_f32(13, 1, (m, k), bf16=True)
+    w = D.normal_f32(13, 2, (n, k), std=0.02, bf16=True)
+    y = P.gemm(_dev(x, BF16), _dev(w, BF16), BF16, kind=kind, split_k=1).cpu().numpy()
+    check_close(y, x.astype(np.float64) @ w.astype(np.float64).T, 1e-5, f"{kind} {m}x{n}x{k}")
+
+
 def test_projection_rejects_unknown_option_bits():
     import paper_2505_15781_amd as P
     x = _dev(D.normal_f32(6, 1, (4, 64), bf16=True), BF16)
