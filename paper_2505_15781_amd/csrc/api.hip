@@ -422,6 +422,12 @@ extern "C" int dkv_denoise_step(dkv_ctx *c, int32_t step, const int32_t *forced_
             // single K slice: SwiGLU in the projection's epilogue, the fp32 gate/up product is never written
             p.flags |= GEMM_FLAG_SWIGLU;
             if ((rc = timed_gemm(c, c->a, c->wgu[l], reinterpret_cast<float *>(c->f), rows, n_rows, 2 * m.d_ffn, d, p))) return rc;
+        } else if (dkv_gemm_f32_few_rows(dt, rows, 2 * m.d_ffn, d)) {
+            rc = timed(c, p.kind, ((double)rows * d + 2.0 * m.d_ffn * d + (double)rows * m.d_ffn) * 4.0, 4.0 * rows * m.d_ffn * d, [&] {
+                return dkv_launch_gemm_f32_few_rows(static_cast<const float *>(c->a), static_cast<const float *>(c->wgu[l]),
+                                                    static_cast<float *>(c->f), rows, n_rows, 2 * m.d_ffn, d, true, s);
+            });
+            if (rc) return rc;
         } else {
             if ((rc = timed_gemm(c, c->a, c->wgu[l], c->part, rows, n_rows, 2 * m.d_ffn, d, p))) return rc;
             if ((rc = dkv_launch_swiglu(dt, s, rows, c->part, p.split_k, (size_t)rows * 2 * m.d_ffn, c->counts, c->f, m.d_ffn))) return rc;

@@ -133,6 +133,11 @@ bool dkv_gemm_can_fuse_swiglu(int dtype, int n, int k, const GemmPlan &p);
 int dkv_launch_gemm(int dtype, const void *A, const void *W, float *partial, int m_upper, int m_cap,
                     const int *m_dev, int n, int k, GemmPlan plan, hipStream_t stream);
 
+// fp32 product of few rows (see gemm_f32.hip), optionally with silu(gate) * up as its result [m][n/2]
+bool dkv_gemm_f32_few_rows(int dtype, int m, int n, int k);
+int dkv_launch_gemm_f32_few_rows(const float *A, const float *W, float *out, int m_upper, const int *m_dev, int n, int k,
+                                 bool swiglu, hipStream_t stream);
+
 struct AttnPlan {
     int use_mfma;     // 1: bf16 MFMA kernel, 0: generic kernel
     int q_tiles;      // 16-row query tiles per (sequence, kv head), upper bound

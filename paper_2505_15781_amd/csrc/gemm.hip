@@ -323,6 +323,9 @@ int dkv_launch_gemm(int dtype, const void *A, const void *W, float *partial, int
             break;
         }
         default: {
+            if (dkv_gemm_f32_few_rows(dtype, m_upper, n, k))
+                return dkv_launch_gemm_f32_few_rows((const float *)A, (const float *)W, partial, m_upper, m_dev, n, k, false,
+                                                    stream);
             dim3 grid(ceil_div(n, 64), ceil_div(m_upper, 64), 1);
             if (dtype == DKV_BF16)
                 hipLaunchKernelGGL((gemm_simt<bf16_t>), grid, dim3(256), 0, stream, (const bf16_t *)A,

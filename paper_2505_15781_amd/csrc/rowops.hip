@@ -155,9 +155,10 @@ __global__ __launch_bounds__(NT) void residual_norm_kernel(const float *__restri
                                                             const float *__restrict__ gain,
                                                             float *__restrict__ h, T *__restrict__ a, int d,
                                                             float eps) {
+    // The row is fetched before its number is held against the count: every row of the grid exists in h and part, so
+    // the latencies of the two loads overlap instead of adding up (the kernel is one chain of latencies at few rows).
     __shared__ float red[16];
     const int r = blockIdx.x;
-    if (r >= counts[0]) return;
     float4 v[V4], g[V4];
     float ss = 0.f;
 #pragma unroll
@@ -175,6 +176,7 @@ __global__ __launch_bounds__(NT) void residual_norm_kernel(const float *__restri
         v[i] = x;
         ss += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
     }
+    if (r >= counts[0]) return;
     ss = block_sum(ss, red);
     const float rs = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
@@ -552,7 +554,8 @@ template <typename T> int vpt_dispatch_resnorm(hipStream_t s, int rows, int d, c
                        counts, gain, h, a, d, eps)
     if (d % 4) { dkv_set_error("d_model %d must be a multiple of 4", d); return DKV_E_UNSUPPORTED; }
     // one float4 per lane per slice where the row is long enough: more wavefronts per row hide the load latency
-    if (d <= 1024) GO(1, 256);
+    if (d <= 256) GO(1, 64);
+    else if (d <= 1024) GO(1, 256);
     else if (d <= 2048) GO(1, 512);
     else if (d <= 4096) GO(1, 1024);
     else if (d <= 8192) GO(2, 1024);
