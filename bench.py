@@ -49,8 +49,7 @@ def parse():
 
 
 def ensure_built():
-    lib = os.path.join(ROOT, "paper_2505_15781_amd", "libdkv.so")
-    if not os.path.exists(lib):
+    if not all(os.path.exists(os.path.join(ROOT, "paper_2505_15781_amd", f)) for f in ("libdkv.so", "_marshal.so")):
         from paper_2505_15781_amd.build import build
         build()
 

@@ -17,6 +17,7 @@ if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2505_15781_amd.build` "
                       "(there is no CPU fallback)")
 lib = C.CDLL(LIB_PATH)
+from . import _marshal  # noqa: E402  (built beside the library)
 
 c_i32, c_f32, c_vp, c_sz = C.c_int32, C.c_float, C.c_void_p, C.c_size_t
 
@@ -78,6 +79,7 @@ lib.dkv_attn_update_workspace_bytes.argtypes = [c_i32] * 7
 lib.dkv_attn_update.argtypes = [c_vp] * 8 + [c_i32] * 8 + [c_vp, c_sz, c_vp]
 lib.dkv_attn_update_static.argtypes = [c_vp] * 8 + [c_i32] * 8 + [c_vp]
 STATIC_SCRATCH_BYTES = 4 << 20
+_marshal.bind(C.cast(lib.dkv_attn_update, c_vp).value, C.cast(lib.dkv_attn_update_static, c_vp).value)
 lib.dkv_concat_reorder.argtypes = [c_vp] * 7 + [c_i32] * 6 + [c_vp]
 lib.dkv_peak_copy.argtypes = [c_vp, c_vp, c_sz, c_vp]
 lib.dkv_peak_read.argtypes = [c_vp, c_vp, c_sz, c_vp]
@@ -104,11 +106,14 @@ def _check(rc):
 
 
 def _ptr(t):
-    return None if t is None else c_vp(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = torch._C._cuda_getCurrentRawStream      # the handle alone, without a Stream object around it
 
 
 def _stream():
-    return c_vp(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _tdtype(dtype):
@@ -301,22 +306,15 @@ def attn_update_workspace_bytes(batch, n_q_heads, n_kv_heads, seq_len, head_dim,
 
 def attn_update(k_cache, v_cache, q, k_new, v_new, active_idx, active_off, out, rows, max_rows_per_seq, dtype,
                 workspace):
-    B, Hkv, L, dh = k_cache.shape
-    Hq = q.shape[1] if q is not None and q.dim() == 3 else out.shape[1]
-    _check(lib.dkv_attn_update(_ptr(k_cache), _ptr(v_cache), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(active_idx),
-                               _ptr(active_off), _ptr(out), rows, max_rows_per_seq, B, Hq, Hkv, L, dh, dtype,
-                               _ptr(workspace), 0 if workspace is None else workspace.numel() * workspace.element_size(),
-                               _stream()))
+    _check(_marshal.attn_update(k_cache, v_cache, q, k_new, v_new, active_idx, active_off, out, rows, max_rows_per_seq,
+                                dtype, workspace, _stream()))
 
 
 def attn_update_static(k_cache, v_cache, q, k_new, v_new, active_idx, active_off, out, rows, max_rows_per_seq,
                        dtype):
     """dkv_attn_update without a workspace argument: the library's static scratch array is used."""
-    B, Hkv, L, dh = k_cache.shape
-    Hq = q.shape[1] if q is not None and q.dim() == 3 else out.shape[1]
-    _check(lib.dkv_attn_update_static(_ptr(k_cache), _ptr(v_cache), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                      _ptr(active_idx), _ptr(active_off), _ptr(out), rows, max_rows_per_seq, B, Hq,
-                                      Hkv, L, dh, dtype, _stream()))
+    _check(_marshal.attn_update_static(k_cache, v_cache, q, k_new, v_new, active_idx, active_off, out, rows,
+                                       max_rows_per_seq, dtype, _stream()))
 
 
 def concat_reorder(k_cached, v_cached, k_new, v_new, take, dtype):

@@ -4,11 +4,13 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdkv.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")      # CPython module of the binding (csrc/marshal.c)
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -47,6 +49,8 @@ def build(verbose=False, incremental=False):
     with ThreadPoolExecutor(max(1, min(8, len(jobs)))) as ex:
         list(ex.map(lambda c: _run(c, verbose), jobs))
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB], verbose)
+    _run([os.environ.get("CC", "gcc"), "-O2", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "marshal.c"), "-o", MARSHAL], verbose)
     return LIB
 
 
