@@ -1,14 +1,14 @@
 // Bidirectional attention of the active queries over the full-length, position-indexed K/V cache
 // (Eq. 4: softmax(Q^{A_t} K^{I T} / sqrt(d)) V^I, no mask; query heads of one group share a K/V head).
 //
-// bf16 kernels (attn_ksplit.h, attn_shared.h): a "query row" is an (active row, query head of the group)
-// pair, handled in tiles of 16. Keys stream in tiles through LDS (K rows and a transposed copy of the V
-// rows), the next tile's global loads are in flight while the current tile is multiplied. Scores are formed
-// transposed (keys x queries) so the probabilities come out of the MFMA already laid out as the
+// bf16 kernels (attn_ksplit.h, attn_shared.h, attn_wide.h): a "query row" is an (active row, query head of the
+// group) pair, handled in tiles of 16 or 32. Keys stream in tiles through LDS (K rows and V rows as they are stored,
+// the V operand through transposing reads), the next tiles are on their way while the current one is multiplied. Scores
+// are formed transposed (keys x queries) so the probabilities come out of the MFMA already laid out as the
 // operand of the second product and never leave registers; the output accumulates transposed
 // (head_dim x queries) with a running max / sum per query (online softmax). The key-split kernel deals
-// the key tiles to the wavefronts of a workgroup and merges their states in LDS; the shared kernel
-// gives every wavefront its own query tiles over one shared K/V tile. When the keys are also sliced
+// the key tiles to the wavefronts of a workgroup and merges their states in LDS; the other two
+// give every wavefront its own query tile over one shared K/V tile. When the key-split kernel also slices the keys
 // across workgroups every workgroup writes (max, sum, unnormalised output) and attn_merge combines them.
 //
 // generic kernel (fp32 mode and odd head sizes): one wavefront per (row, query head), lanes stride
@@ -139,12 +139,6 @@ __device__ __forceinline__ uint4 load16_nt(const void *p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// 16 bytes, plain
-__device__ __forceinline__ uint4 load16(const void *p) {
-    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 // Work-item order of the bf16 kernels. The `inner` workgroups of a (sequence, kv head) pair (query groups or blocks
 // x key slices) read the same K/V rows, and the hardware sends workgroup i to XCD i mod 8, each with an L2 of its
 // own: consecutive ids would have every XCD fetch the pair's K/V once more (measured: 4.2x the K/V bytes from
@@ -161,6 +155,7 @@ static inline unsigned attn_grid(long pairs, int inner) { return (unsigned)((pai
 
 #include "attn_shared.h"
 #include "attn_ksplit.h"
+#include "attn_wide.h"
 
 // Merge the key slices of one (row, head): one wavefront per pair.
 template <int DH>
@@ -294,8 +289,8 @@ AttnPlan dkv_attn_plan(int dtype, int batch, int n_q_heads, int n_kv_heads, int 
                        int max_rows_per_seq) {
     AttnPlan p;
     p.use_mfma = (dtype == DKV_BF16 && (head_dim == 64 || head_dim == 128)) ? 1 : 0;
-    p.shared_nq = 0;
-    p.shared_waves = 0;
+    p.shared = 0;
+    p.wide = 0;
     p.q_blocks = 0;
     p.ksplit_nq = 0;
     p.ksplit_waves = 0;
@@ -308,34 +303,33 @@ AttnPlan dkv_attn_plan(int dtype, int batch, int n_q_heads, int n_kv_heads, int 
         p.tiles_per_split = ceil_div(seq_len, KT);
         return p;
     }
-    // Measured on MI355X over the shapes of the four workloads: the shared-tile kernel (about 450 TFLOP/s when
-    // compute bound, against 200 for the key-split kernel, and K/V read from L2 once per 128 query rows) wins
-    // as soon as its blocks of 8 query tiles make enough workgroups to occupy the chip without slicing the
-    // keys, even when the last block of a head is mostly empty; below that the key-split kernel does.
-    const int blocks8 = ceil_div(p.q_tiles, 8);
-    const bool shared = head_dim == 128 && p.q_tiles >= 5 && (long)batch * n_kv_heads * blocks8 >= 192;
-    int s = 1, n_tiles, min_tiles;
-    if (shared) {
-        // Blocks of 8 query tiles either way. With fewer than two workgroups per compute unit, 8 wavefronts
-        // with one query tile each: a second wavefront per SIMD fills the waits of the first (softmax between
-        // the two products, the tile barrier), which two co-resident workgroups do otherwise.
-        const bool wide = (long)batch * n_kv_heads * blocks8 < 512;
-        p.shared_nq = wide ? 1 : 2;
-        p.shared_waves = wide ? 8 : 4;
-        p.q_blocks = blocks8;
-        n_tiles = ceil_div(seq_len, 64);
-        min_tiles = 2;
-    } else {
-        p.ksplit_nq = p.q_tiles >= 2 ? 2 : 1;
-        p.q_groups = ceil_div(p.q_tiles, p.ksplit_nq);
-        n_tiles = ceil_div(seq_len, KT);
-        const long items = (long)batch * n_kv_heads * p.q_groups;
-        // 8 wavefronts per workgroup (one workgroup per compute unit) while that still gives every compute
-        // unit at most one; beyond, 4 wavefronts so that two workgroups share a unit
-        p.ksplit_waves = items <= 256 ? 8 : 4;
-        if (items < 192) s = (int)((384 + items - 1) / items);
-        min_tiles = 2 * p.ksplit_waves;                     // two tiles per wavefront
+    // Blocks of 128 query rows that share K/V tiles (head_dim 128, more than four query tiles) from 80 workgroups on; below,
+    // or with fewer rows, the key-split kernel. Measured in us (key-split kernel / attn_wide.h, with the scatter): 64
+    // workgroups (1 x 32 heads, 512 keys, 255 rows) 14.1 / 16.0, 84 (3 x 4 kv heads of 7, 290 keys, 124 rows) 14.3 /
+    // 12.5, 128 (1 x 32 heads, 512 rows) 19.8 / 17.7, 128 (4 x 32 heads, 1024 keys, 128 rows) 27.9 / 25.3.
+    // Where a pair has one block and its K/V is long, the stream of K/V bounds the launch and attn_shared.h, with two
+    // tiles on their way, is ahead as long as its larger workgroups make one round: 8 x 32 heads, 128 rows: 1024 keys
+    // 40.4 against 43.0 us, but 512 keys 24.0 against 22.7, and several blocks per pair (4 x 32 heads, 1024 keys, 256
+    // rows) 39.0 against 34.7.
+    const int blocks = ceil_div(p.q_tiles, 8);
+    const long wgs = (long)batch * n_kv_heads * blocks;
+    if (head_dim == 128 && p.q_tiles >= 5 && wgs >= 80) {
+        p.shared = blocks == 1 && seq_len >= 768 && wgs >= 192 && wgs < 512;
+        p.wide = !p.shared;
+        p.q_blocks = blocks;
+        p.splits = 1;
+        p.tiles_per_split = ceil_div(seq_len, 64);
+        return p;
     }
+    p.ksplit_nq = p.q_tiles >= 2 ? 2 : 1;
+    p.q_groups = ceil_div(p.q_tiles, p.ksplit_nq);
+    const int n_tiles = ceil_div(seq_len, KT);
+    const long items = (long)batch * n_kv_heads * p.q_groups;
+    // 8 wavefronts per workgroup (one workgroup per compute unit) while that still gives every compute
+    // unit at most one; beyond, 4 wavefronts so that two workgroups share a unit
+    p.ksplit_waves = items <= 256 ? 8 : 4;
+    int s = items < 192 ? (int)((384 + items - 1) / items) : 1;
+    const int min_tiles = 2 * p.ksplit_waves;               // two tiles per wavefront
     const int max_s = n_tiles / min_tiles > 0 ? n_tiles / min_tiles : 1;
     if (s > max_s) s = max_s;
     p.tiles_per_split = ceil_div(n_tiles, s);
@@ -425,42 +419,30 @@ int dkv_launch_attention(int dtype, const void *q, void *k_cache, void *v_cache,
                                    rows_upper);
             DKV_LAUNCH_CHECK();
         }
-    } else if (plan.shared_nq) {
-        const size_t smem = 2 * 64 * ((128 * 2 + 16) + (128 * 2 + 32));   // two stages of 64 K rows and 64 V rows
-        const unsigned wgs = attn_grid((long)batch * n_kv_heads, plan.q_blocks * plan.splits);
+    } else if (plan.wide) {
         static std::atomic<bool> lds_ok{false};
         if (!lds_ok.load(std::memory_order_acquire)) {
-            DKV_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_shared<2, 4, false>),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-            DKV_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_shared<2, 4, true>),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-            DKV_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_shared<1, 8, false>),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-            DKV_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_shared<1, 8, true>),
+            DKV_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_wide),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, WIDE_LDS_BYTES));
+            lds_ok.store(true, std::memory_order_release);
+        }
+        hipLaunchKernelGGL(attn_bf16_wide, dim3(attn_grid((long)batch * n_kv_heads, plan.q_blocks)), dim3(256),
+                           WIDE_LDS_BYTES, stream, (const bf16_t *)q, (const bf16_t *)k_cache, (const bf16_t *)v_cache,
+                           row_off, (bf16_t *)out, batch, n_q_heads, n_kv_heads, seq_len, plan.q_blocks, rows_upper,
+                           scale_log2e);
+        DKV_LAUNCH_CHECK();
+    } else if (plan.shared) {
+        constexpr size_t smem = 2 * 64 * ((128 * 2 + 16) + (128 * 2 + 32));   // two stages of 64 K rows and 64 V rows
+        static std::atomic<bool> lds_ok{false};
+        if (!lds_ok.load(std::memory_order_acquire)) {
+            DKV_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_shared),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
             lds_ok.store(true, std::memory_order_release);
         }
-#define SHARED(NQ_, NW_, ONCE_)                                                                                   \
-    hipLaunchKernelGGL((attn_bf16_shared<NQ_, NW_, ONCE_>), dim3(wgs), dim3(64 * NW_), smem, stream, (const bf16_t *)q,  \
-                       (const bf16_t *)k_cache, (const bf16_t *)v_cache, row_off, (bf16_t *)out, (float *)partial, \
-                       batch, n_q_heads, n_kv_heads, seq_len, plan.q_blocks, plan.splits, plan.tiles_per_split,    \
-                       rows_upper, scale_log2e)
-        const bool once = plan.q_blocks == 1;       // nobody else reads the K/V rows of a workgroup
-        if (plan.shared_waves == 8) {
-            if (once) SHARED(1, 8, true);
-            else SHARED(1, 8, false);
-        } else {
-            if (once) SHARED(2, 4, true);
-            else SHARED(2, 4, false);
-        }
-#undef SHARED
+        hipLaunchKernelGGL(attn_bf16_shared, dim3(attn_grid((long)batch * n_kv_heads, 1)), dim3(512), smem, stream,
+                           (const bf16_t *)q, (const bf16_t *)k_cache, (const bf16_t *)v_cache, row_off, (bf16_t *)out,
+                           batch, n_q_heads, n_kv_heads, seq_len, rows_upper, scale_log2e);
         DKV_LAUNCH_CHECK();
-        if (plan.splits > 1) {
-            hipLaunchKernelGGL((attn_merge<128>), dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, stream,
-                               (const float *)partial, (bf16_t *)out, row_off, batch, n_q_heads, plan.splits,
-                               rows_upper);
-            DKV_LAUNCH_CHECK();
-        }
     }
     return DKV_OK;
 }

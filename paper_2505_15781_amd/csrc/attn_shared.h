@@ -1,21 +1,19 @@
-// Attention kernel for larger active sets: the NW (4 or 8) wavefronts of a workgroup share each K/V tile.
-// Included by attention.hip (uses its helpers); head_dim 128 only.
+// Attention kernel for one block of up to 128 query rows per (sequence, kv head): the eight wavefronts of a workgroup share
+// each K/V tile, 16 query rows each. Included by attention.hip (uses its helpers); head_dim 128 only.
 //
-// Work item = (sequence, kv head, block of NW*NQ query tiles of 16 rows, key slice). The workgroup
-// streams its key slice in tiles of 64 keys: every thread fetches part of the K rows and of the V rows
-// as they are stored (transposing LDS reads form the V operand of the second product), two LDS stages alternate, and the global
-// loads of the next tile (with 8 wavefronts: of the next two) are in flight while the current one is multiplied. Each wavefront multiplies its own NQ query
-// tiles against the shared tile, so a K or V fragment read from LDS feeds NQ MFMAs and the tile is read
-// from L2 once per 64*NQ query rows instead of once per 16.
+// Work item = (sequence, kv head). The workgroup streams the keys in tiles of 64: every thread fetches part of the K rows
+// and of the V rows as they are stored (transposing LDS reads form the V operand of the second product), two LDS stages
+// alternate, and the global loads of the next two tiles are in flight while the current one is multiplied. Every K/V row
+// is read by one workgroup of the launch, so the kernel is bound by that stream (8 sequences x 32 heads x 1024 keys, 128
+// rows: 33-35 us for 134 MB); 16 rows per wavefront instead of attn_wide.h's 32 put two wavefronts on a SIMD where only one
+// workgroup runs on a unit, and two tiles on their way cover a miss.
 #pragma once
 
-template <int NQ, int NW, bool ONCE>
-__global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_shared(
+__global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_shared(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc,
-    const int *__restrict__ row_off, bf16_t *__restrict__ out, float *__restrict__ part, int batch,
-    int Hq, int Hkv, int L, int q_blocks, int splits, int tiles_per_split, int rows_cap,
+    const int *__restrict__ row_off, bf16_t *__restrict__ out, int batch, int Hq, int Hkv, int L, int rows_cap,
     float scale_log2e) {
-    constexpr int DH = 128, KT2 = 64;
+    constexpr int NQ = 1, NW = 8, DH = 128, KT2 = 64;
     constexpr int K_STRIDE = DH * 2 + 16;      // bytes per key row
     constexpr int V_STRIDE = DH * 2 + 32;      // bytes per V row
     constexpr int K_BYTES = KT2 * K_STRIDE, STAGE_BYTES = K_BYTES + KT2 * V_STRIDE;
@@ -24,14 +22,12 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int G = Hq / Hkv;
     int pair, within;
-    if (!attn_item(blockIdx.x, batch * Hkv, q_blocks * splits, pair, within)) return;
-    const int split = within % splits, qb = within / splits;
+    if (!attn_item(blockIdx.x, batch * Hkv, 1, pair, within)) return;
     const int kvh = pair % Hkv, b = pair / Hkv;
 
     const int r0 = row_off[b], nrows = row_off[b + 1] - r0;
     const int nq = nrows * G;
-    const int mb0 = qb * NW * NQ * 16;
-    if (mb0 >= nq) return;                       // uniform for the workgroup
+    if (nq <= 0) return;                         // uniform for the workgroup
 
     const int qi = lane & 15, g = lane >> 4;
     bool q_ok[NQ];
@@ -39,7 +35,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu
     bf16x8 qf[NQ][DH / 32];
 #pragma unroll
     for (int j = 0; j < NQ; ++j) {
-        const int mq = mb0 + (wave * NQ + j) * 16 + qi;
+        const int mq = (wave * NQ + j) * 16 + qi;
         q_ok[j] = mq < nq && r0 + mq / G < rows_cap;
         q_row[j] = q_ok[j] ? r0 + mq / G : 0;
         q_head[j] = kvh * G + (q_ok[j] ? mq % G : 0);
@@ -54,13 +50,12 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu
     const bf16_t *Kb = Kc + ((size_t)b * Hkv + kvh) * (size_t)L * DH;
     const bf16_t *Vb = Vc + ((size_t)b * Hkv + kvh) * (size_t)L * DH;
     const int n_tiles = (L + KT2 - 1) / KT2;
-    const int t0 = split * tiles_per_split, t1 = min(n_tiles, t0 + tiles_per_split);
+    const int t0 = 0, t1 = n_tiles;
 
     // per thread: CH chunks (16 B) of K and of V per tile, in register set A or B on their way to LDS
     constexpr int NT = 64 * NW, CH = KT2 * (DH / 8) / NT;
     uint4 kA[CH], vA[CH], kB[CH], vB[CH];
-    // ONCE: one block of query tiles per (sequence, kv head), so nobody else reads these K/V rows in this launch and
-    // they are fetched with the non-temporal hint; with several blocks they are meant to be found in L2 again.
+    // Nobody else reads these K/V rows in this launch: they are fetched with the non-temporal hint.
     // The loads are unconditional (keys past the end are clamped to the last row: their scores are masked and their
     // probabilities are zero) so that the code is one straight line and the waits below can count: with a branch
     // around every load the compiler can only wait for all of them, which puts the loads of the tile after next in
@@ -70,13 +65,8 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int c = tid + NT * i, key = c >> 4, ch = c & 15, gk = min(key0 + key, L - 1);
-            if (ONCE) {
-                kr[i] = load16_nt(Kb + (size_t)gk * DH + ch * 8);
-                vr[i] = load16_nt(Vb + (size_t)gk * DH + ch * 8);
-            } else {
-                kr[i] = load16(Kb + (size_t)gk * DH + ch * 8);
-                vr[i] = load16(Vb + (size_t)gk * DH + ch * 8);
-            }
+            kr[i] = load16_nt(Kb + (size_t)gk * DH + ch * 8);
+            vr[i] = load16_nt(Vb + (size_t)gk * DH + ch * 8);
         }
     };
     auto store_tile = [&](int stage, const uint4 (&kr)[CH], const uint4 (&vr)[CH]) {
@@ -151,45 +141,32 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu
         load_tile(t0, kA, vA);
         store_tile(0, kA, vA);
         int t = t0;
-        if (NW == 8) {
-            // one workgroup per compute unit: while a tile is multiplied, the next one waits in one register set
-            // and the one after it is being fetched into the other (16 registers per set)
-            if (t + 1 < t1) load_tile(t + 1, kA, vA);
+        // one workgroup per compute unit: while a tile is multiplied, the next one waits in one register set
+        // and the one after it is being fetched into the other (16 registers per set)
+        if (t + 1 < t1) load_tile(t + 1, kA, vA);
+        __syncthreads();
+        for (; t + 3 < t1; t += 2) {
+            load_tile(t + 2, kB, vB);
+            multiply(t, 0);
+            store_tile(1, kA, vA);
             __syncthreads();
-            for (; t + 3 < t1; t += 2) {
-                load_tile(t + 2, kB, vB);
-                multiply(t, 0);
-                store_tile(1, kA, vA);
-                __syncthreads();
-                load_tile(t + 3, kA, vA);
-                multiply(t + 1, 1);
+            load_tile(t + 3, kA, vA);
+            multiply(t + 1, 1);
+            store_tile(0, kB, vB);
+            __syncthreads();
+        }
+        // one to three tiles are left: t in stage 0, t + 1 on its way in set A
+        if (t + 2 < t1) load_tile(t + 2, kB, vB);
+        multiply(t, 0);
+        if (t + 1 < t1) {
+            store_tile(1, kA, vA);
+            __syncthreads();
+            multiply(t + 1, 1);
+            if (t + 2 < t1) {
                 store_tile(0, kB, vB);
                 __syncthreads();
+                multiply(t + 2, 0);
             }
-            // one to three tiles are left: t in stage 0, t + 1 on its way in set A
-            if (t + 2 < t1) load_tile(t + 2, kB, vB);
-            multiply(t, 0);
-            if (t + 1 < t1) {
-                store_tile(1, kA, vA);
-                __syncthreads();
-                multiply(t + 1, 1);
-                if (t + 2 < t1) {
-                    store_tile(0, kB, vB);
-                    __syncthreads();
-                    multiply(t + 2, 0);
-                }
-            }
-        } else {
-            // two workgroups per compute unit cover each other's waits: one tile ahead is enough
-            __syncthreads();
-            for (; t + 1 < t1; ++t) {
-                const int stage = (t - t0) & 1;
-                load_tile(t + 1, kA, vA);
-                multiply(t, stage);
-                store_tile(stage ^ 1, kA, vA);
-                __syncthreads();
-            }
-            multiply(t, (t - t0) & 1);
         }
     }
 
@@ -197,24 +174,14 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu
     for (int j = 0; j < NQ; ++j) {
         const float l = query_lanes_sum(l_acc[j][0]);
         if (!q_ok[j]) continue;
-        if (splits == 1) {
-            const float inv = 1.f / l;
-            bf16_t *op = out + ((size_t)q_row[j] * Hq + q_head[j]) * DH;
+        const float inv = 1.f / l;
+        bf16_t *op = out + ((size_t)q_row[j] * Hq + q_head[j]) * DH;
 #pragma unroll
-            for (int mt = 0; mt < DH / 16; ++mt) {
-                uint2 w;
-                w.x = (uint32_t)f2bf(acc[j][mt][0] * inv) | ((uint32_t)f2bf(acc[j][mt][1] * inv) << 16);
-                w.y = (uint32_t)f2bf(acc[j][mt][2] * inv) | ((uint32_t)f2bf(acc[j][mt][3] * inv) << 16);
-                *reinterpret_cast<uint2 *>(op + 16 * mt + 4 * g) = w;
-            }
-        } else {
-            float *rec = part + (((size_t)q_row[j] * Hq + q_head[j]) * splits + split) * (DH + 4);
-            if (g == 0) {
-                rec[0] = m_run[j];
-                rec[1] = l;
-            }
-#pragma unroll
-            for (int mt = 0; mt < DH / 16; ++mt) *reinterpret_cast<f32x4 *>(rec + 4 + 16 * mt + 4 * g) = acc[j][mt];
+        for (int mt = 0; mt < DH / 16; ++mt) {
+            uint2 w;
+            w.x = (uint32_t)f2bf(acc[j][mt][0] * inv) | ((uint32_t)f2bf(acc[j][mt][1] * inv) << 16);
+            w.y = (uint32_t)f2bf(acc[j][mt][2] * inv) | ((uint32_t)f2bf(acc[j][mt][3] * inv) << 16);
+            *reinterpret_cast<uint2 *>(op + 16 * mt + 4 * g) = w;
         }
     }
 }

@@ -1,0 +1,238 @@
+// Attention kernel for active sets of hundreds of query rows: 32 query rows per wavefront, 32x32x16 MFMA, head_dim 128.
+// Included by attention.hip (uses its helpers).
+//
+// Work item = (sequence, kv head, block of 128 query rows). Keys stream in tiles of 64 through two LDS stages that the
+// memory system fills directly (global_load_lds: no staging registers, no LDS stores); each of the four wavefronts
+// multiplies its 32 query rows against the shared tile, so a K or V fragment read from LDS feeds 32 queries.
+//
+// Why: with 16-row tiles the loop was a chain product -> softmax -> product in every wavefront, and the two wavefronts of a
+// SIMD did the same part at the same time: matrix pipes busy 35 %, vector issue 49 %, their sum and little overlap. Here
+// a wavefront works on half tiles of 32 keys in a skewed order: one stretch holds the scores of half tile j + 1, the output
+// products of half tile j - 1 and the exponentials of half tile j, which do not depend on each other, and the schedule
+// deals them out one MFMA, one or two LDS reads, four or five vector instructions at a time. The running sum stays on the
+// vector units: v_dot2 goes through the matrix pipe (11 cycles each next to MFMAs), and a product with a row of ones costs
+// an eighth more MFMAs. Two workgroups share a compute unit and cover each other's barrier (one per tile).
+// Kernel time before and after: 8 sequences x 32 heads x 1024 keys, 512 rows 103 -> 79 us (870 TFLOP/s), 4 x 32 heads x
+// 1536 keys, 1536 rows 213 -> 163 us (950 TFLOP/s), 16 x 4 kv heads of 7, 768 keys, up to 129 rows 35 -> 25 us. With
+// nothing but the MFMAs the second takes 100 us (the clock falls under their power), so what is left is mostly the
+// first tiles of a workgroup and the fills (without them 12 % less time).
+#pragma once
+
+typedef __attribute__((address_space(3))) void *lds_ptr_t;
+template <int V> struct StageC { static constexpr int value = V; };
+
+// LDS rows of 256 bytes (one key); the 16-byte chunk c of row r sits in place c ^ wide_swizzle(r): 16 consecutive rows put
+// a chunk into 16 different places (score operands: one chunk of 32 rows), and 4 consecutive rows put a 64-byte group into
+// 4 different groups (transposing reads: 32 bytes of 4 rows each).
+__device__ __forceinline__ int wide_swizzle(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+
+// 16 bytes per lane from base + voff into LDS at lds_addr + 16 * lane (base, lds_addr wave-uniform); awaited with vmcnt
+__device__ __forceinline__ void wide_dma16(uint32_t voff, const void *base, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
+}
+
+constexpr int WIDE_LDS_BYTES = 4 * 64 * 256;         // K0 K1 V0 V1
+
+__global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_wide(
+    const bf16_t *__restrict__ Q, const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc,
+    const int *__restrict__ row_off, bf16_t *__restrict__ out, int batch, int Hq, int Hkv, int L, int q_blocks,
+    int rows_cap, float scale_log2e) {
+    constexpr int NW = 4, DH = 128, ROW = DH * 2, KT2 = 64, TILE = KT2 * ROW;     // bytes of a row, of a K or V tile
+    constexpr int DI = KT2 / (4 * NW);                          // DMA instructions (4 rows each) per wavefront and tile
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int G = Hq / Hkv, n_tiles = (L + KT2 - 1) / KT2;
+    const int qi = lane & 31, g = lane >> 5, l16 = lane & 15, l4 = lane >> 4;
+    const uint32_t lds_base = (uint32_t)(size_t)(lds_ptr_t)smem_raw;
+    int pair, qb;
+    if (!attn_item(blockIdx.x, batch * Hkv, q_blocks, pair, qb)) return;
+    const int kvh = pair % Hkv, b = pair / Hkv;
+    const int r0 = row_off[b], nq = (row_off[b + 1] - r0) * G, mb0 = qb * NW * 32;
+    if (mb0 >= nq) return;                       // uniform for the workgroup
+
+    // DMA: instruction i of a wavefront fills rows 4 (i NW + wave) + [0, 4) of a tile; lane -> row lane / 16, place lane % 16.
+    // Keys past the end are clamped to the last one: their scores are masked, their probabilities zero.
+    const char *Kb = reinterpret_cast<const char *>(Kc + (size_t)pair * (size_t)L * DH);
+    const char *Vb = reinterpret_cast<const char *>(Vc + (size_t)pair * (size_t)L * DH);
+    uint32_t chunk[DI];
+#pragma unroll
+    for (int i = 0; i < DI; ++i) chunk[i] = (l16 ^ wide_swizzle(4 * (i * NW + wave) + l4)) << 4;
+    auto fill = [&](const char *base, int t, uint32_t dst) {
+#pragma unroll
+        for (int i = 0; i < DI; ++i) {
+            const int row = 4 * (i * NW + wave) + l4;
+            wide_dma16((uint32_t)min(row, L - 1 - t * KT2) * ROW + chunk[i], base + (size_t)t * TILE,
+                       lds_base + dst + 4 * (i * NW + wave) * ROW);
+        }
+    };
+    // this lane's query row; rows beyond the host's bound have no slot in Q and out
+    const int mq = mb0 + wave * 32 + qi;
+    const bool q_ok = mq < nq && r0 + mq / G < rows_cap;
+    const size_t q_at = q_ok ? ((size_t)(r0 + mq / G) * Hq + kvh * G + mq % G) * DH : (size_t)(kvh * G) * DH;
+    bf16x8 qf[DH / 16];
+#pragma unroll
+    for (int ks = 0; ks < DH / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(Q + q_at + 8 * g + 16 * ks);
+    fill(Kb, 0, 0);
+    fill(Vb, 0, 2 * TILE);
+    if (n_tiles > 1) fill(Kb, 1, TILE);
+
+    // score operands: row lane & 31, chunk 2 ks + g
+    const unsigned char *krow = smem_raw + qi * ROW;
+    const int kx = (g ^ wide_swizzle(qi)) << 4;
+    // output operand: see vt_operand; block lane / 16 = (g, dims + 16 half), key 4 g + j / 4 (+ 8), dims 4 (j % 4)
+    const unsigned char *vrow = smem_raw + 2 * TILE + (4 * g + (l16 >> 2)) * ROW + ((l16 & 1) << 3);
+    const int vx = ((2 * (l4 & 1) + ((l16 & 3) >> 1)) ^ (((l16 >> 2) << 2) | g)) << 4;       // keys + 8: swizzle ^ 2
+
+    // lowest finite start: scores of -inf then give probabilities of zero, also where a whole half tile is masked
+    float m_run = -3.0e38f, l_run = 0.f;
+    f32x16 acc[DH / 32], stA, stB;               // stA, stB: scores of the first and the second 32 keys of a tile
+    bf16x8 pA[2], pB[2];                         // their probabilities
+#pragma unroll
+    for (int i = 0; i < DH / 32; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) pB[0][e] = pB[1][e] = (__bf16)0.f;
+
+    auto k_operand = [&](int ks, int stage, int half) {
+        return *reinterpret_cast<const bf16x8 *>(krow + (kx ^ (ks << 5)) + stage * TILE + half * 32 * ROW);
+    };
+    // keys of k step ks in operand order: 16 ks + 4 g + {0..3}, 16 ks + 8 + 4 g + {0..3}: as the scores leave the MFMA
+    auto v_operand = [&](int mt, int ks, int stage, int half) {
+        const unsigned char *p = vrow + stage * TILE + (2 * half + ks) * 16 * ROW;
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + (vx ^ (mt << 6))));
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p + 8 * ROW + (vx ^ (mt << 6) ^ 32)));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    // One stretch: scores of a half tile (into sn), output products of the half tile before the last (pv), exponentials of
+    // the last one (so -> pn). The three are independent of each other.
+    auto stretch = [&](f32x16 &sn, int kstage, int khalf, const bf16x8 (&pv)[2], int vstage, int vhalf, const f32x16 &so,
+                       bf16x8 (&pn)[2]) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sn[v] = 0.f;
+        f32x8 p[2];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(i, kstage, khalf), qf[i], sn, 0, 0, 0);
+            acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(i & 3, i >> 2, vstage, vhalf), pv[i >> 2], acc[i & 3], 0, 0, 0);
+#pragma unroll
+            for (int e = 2 * i; e < 2 * i + 2; ++e)
+                p[e >> 3][e & 7] = __builtin_amdgcn_exp2f(fmaf(so[e], scale_log2e, -m_run));
+        }
+        // running sum of exactly the rounded probabilities of the second product
+        float l2 = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            pn[ks] = __builtin_convertvector(p[ks], bf16x8);
+            const u32x4_t y = __builtin_bit_cast(u32x4_t, pn[ks]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                l_run += __uint_as_float(y[e] << 16);
+                l2 += __uint_as_float(y[e] & 0xffff0000u);
+            }
+        }
+        l_run += l2;
+        asm volatile("" : "+v"(pn[0]), "+v"(pn[1]), "+v"(l_run));        // here, not behind the branches of maximum()
+        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);
+        }
+    };
+    // Maximum of the half tile whose first key is `key`. The reference m_run of the exponentials follows the maximum only
+    // when that has grown by more than 2^8: the probabilities are then at most 2^8, which costs bf16 and fp32 no
+    // precision, and the output is hardly ever rescaled after the first tile. References are whole numbers, so that the
+    // probabilities that still wait for their product (pw) can be rescaled exactly.
+    auto maximum = [&](f32x16 &st, int key, bf16x8 (&pw)[2]) {
+        if (key + 32 > L) {                      // wave-uniform: only the last tile of a sequence has keys past the end
+            const int left = L - key - 4 * g;
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (8 * (v >> 2) + (v & 3) >= left) st[v] = -INFINITY;
+        }
+        float mx = st[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, st[v]);
+        float u, w;
+        swap_rows32(mx, u, w);
+        mx = fmaxf(u, w) * scale_log2e;
+        if (__builtin_amdgcn_ballot_w64(mx > m_run + 8.f) != 0) {
+            const float m_new = fmaxf(m_run, ceilf(mx));
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= alpha;
+#pragma unroll
+            for (int mt = 0; mt < DH / 32; ++mt) acc[mt] *= alpha;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) pw[ks][e] = (__bf16)((float)pw[ks][e] * alpha);
+            m_run = m_new;
+        }
+    };
+    auto tile_barrier = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0070);      // vmcnt(0), lgkmcnt(0): this wavefront's fills have landed, its LDS reads returned
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    // the first stretch multiplies (zero) probabilities with the second half of V stage 1: no NaN may be there
+    for (int i = tid; i < TILE / 32; i += 64 * NW) reinterpret_cast<uint4 *>(smem_raw + 3 * TILE + TILE / 2)[i] = make_uint4(0, 0, 0, 0);
+    tile_barrier();
+#pragma unroll
+    for (int v = 0; v < 16; ++v) stA[v] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) stA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(i, 0, 0), qf[i], stA, 0, 0, 0);
+    maximum(stA, 0, pB);
+    // Tile t, in stage S; the scores of its first half are formed.
+    auto step = [&](int t, auto stage) {
+        constexpr int S = decltype(stage)::value;
+        stretch(stB, S, 1, pB, S ^ 1, 1, stA, pA);
+        maximum(stB, t * KT2 + 32, pA);
+        // behind the barrier K(t + 1) and V(t) have landed for everybody, and everybody is done with K(t) and V(t - 1)
+        tile_barrier();
+        if (t + 2 < n_tiles) fill(Kb, t + 2, S * TILE);
+        if (t + 1 < n_tiles) fill(Vb, t + 1, (2 + (S ^ 1)) * TILE);
+        stretch(stA, S ^ 1, 0, pA, S, 0, stB, pB);            // behind the last tile: scores of an old tile, never used
+        if (t + 1 < n_tiles) maximum(stA, (t + 1) * KT2, pB);
+    };
+    for (int t = 0; t < n_tiles; t += 2) {
+        step(t, StageC<0>{});
+        if (t + 1 < n_tiles) step(t + 1, StageC<1>{});
+    }
+    const int last = (n_tiles - 1) & 1;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(i & 3, i >> 2, last, 1), pB[i >> 2], acc[i & 3], 0, 0, 0);
+
+    float u, w;
+    swap_rows32(l_run, u, w);
+    const float inv = 1.f / (u + w);
+    if (!q_ok) return;
+    bf16_t *op = out + q_at + 8 * g;
+#pragma unroll
+    for (int mt = 0; mt < DH / 32; ++mt)
+#pragma unroll
+        for (int c = 0; c < 4; c += 2) {
+            // lane qi holds dims 8 c + {0..3} and 8 c + 8 + {0..3}, lane qi + 32 the other four of each: after the swaps the
+            // first has the lower 8 dims, the second the upper 8
+            uint32_t y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int v = 4 * c + (e >> 1) * 4 + (e & 1) * 2;
+                y[e] = (uint32_t)f2bf(acc[mt][v] * inv) | ((uint32_t)f2bf(acc[mt][v + 1] * inv) << 16);
+            }
+            const auto p0 = __builtin_amdgcn_permlane32_swap(y[0], y[2], false, false);
+            const auto p1 = __builtin_amdgcn_permlane32_swap(y[1], y[3], false, false);
+            *reinterpret_cast<uint4 *>(op + 32 * mt + 8 * c) = make_uint4(p0[0], p1[0], p0[1], p1[1]);
+        }
+}

@@ -142,10 +142,10 @@ struct AttnPlan {
     int use_mfma;     // 1: bf16 MFMA kernel, 0: generic kernel
     int q_tiles;      // 16-row query tiles per (sequence, kv head), upper bound
     int splits;       // slices of the key range
-    int tiles_per_split;   // in tiles of 32 keys (wave-private kernel) or 64 keys (shared kernel)
-    int shared_nq;    // 0: one wavefront per item; 1 or 2: workgroup-shared K/V tiles, query tiles per wavefront
-    int shared_waves; // shared kernel: wavefronts per workgroup (4 or 8)
-    int q_blocks;     // shared kernel: blocks of shared_waves * shared_nq query tiles
+    int tiles_per_split;   // in tiles of 32 keys (key-split kernel)
+    int shared;       // 1: one block of 128 query rows per pair, workgroup-shared K/V tiles (attn_shared.h)
+    int wide;         // 1: blocks of 128 query rows, 32 per wavefront (attn_wide.h)
+    int q_blocks;     // shared, wide: blocks of 128 query rows per (sequence, kv head)
     int ksplit_nq;    // 0, or 1 / 2: key-split kernel (wavefronts of a workgroup share the keys), query tiles per item
     int ksplit_waves; // key-split kernel: wavefronts per workgroup (4 or 8)
     int q_groups;     // key-split kernel: groups of ksplit_nq query tiles

@@ -230,6 +230,23 @@ def test_attention_shared_tiles_with_ragged_sequences():
     _attn_case(shape, None, 53, ragged=[79, 0, 300, 5])
 
 
+@pytest.mark.parametrize("seq_len,rows", [(16, 16), (17, 17), (32, 20), (33, 33), (63, 15), (65, 65), (97, 16), (129, 31), (160, 100)])
+def test_attention_wide_query_blocks_at_tile_edges(seq_len, rows):
+    """Blocks of 128 query rows, 32 per wavefront (6 x 16 kv heads of 8 query heads): one to three key tiles of 64, a
+    half tile of 32 keys that is full, ragged or masked as a whole, query rows that fill the last block or leave one
+    active row (8 query rows) in it."""
+    shape = D.AttnUpdateShape(batch=6, n_q_heads=128, n_kv_heads=16, seq_len=seq_len, head_dim=128, dtype=BF16)
+    _attn_case(shape, rows, 54)
+
+
+@pytest.mark.parametrize("seq_len", [768, 769, 900])
+def test_attention_one_query_block_over_long_sequences(seq_len):
+    """One block of query rows per (sequence, kv head) and at least 12 key tiles: the kernel with two tiles on their way,
+    both exits of its two-tile loop; sequences without active rows and with a full block."""
+    shape = D.AttnUpdateShape(batch=4, n_q_heads=64, n_kv_heads=64, seq_len=seq_len, head_dim=128, dtype=BF16)
+    _attn_case(shape, None, 55, ragged=[100, 0, 128, 5])
+
+
 @pytest.mark.parametrize("dh", [128, 64])
 def test_attention_many_small_items(dh):
     """More (sequence, head, query group) items than compute units: the key-split kernel in its
