@@ -303,18 +303,17 @@ AttnPlan dkv_attn_plan(int dtype, int batch, int n_q_heads, int n_kv_heads, int 
         p.tiles_per_split = ceil_div(seq_len, KT);
         return p;
     }
-    // Blocks of 128 query rows that share K/V tiles (head_dim 128, more than four query tiles) from 80 workgroups on; below,
-    // or with fewer rows, the key-split kernel. Measured in us (key-split kernel / attn_wide.h, with the scatter): 64
-    // workgroups (1 x 32 heads, 512 keys, 255 rows) 14.1 / 16.0, 84 (3 x 4 kv heads of 7, 290 keys, 124 rows) 14.3 /
-    // 12.5, 128 (1 x 32 heads, 512 rows) 19.8 / 17.7, 128 (4 x 32 heads, 1024 keys, 128 rows) 27.9 / 25.3.
+    // Blocks of 128 query rows that share K/V tiles (head_dim 128, more than four query tiles) from 192 workgroups on; below,
+    // or with fewer rows, the key-split kernel: at 128 workgroups the two are within 5 % of each other (1 x 32 heads, 512
+    // keys, 512 rows 19.7 against 19.9 us, 4 x 32 heads, 1024 keys, 128 rows 29.4 against 30.4), at 64 it is 9 % ahead.
     // Where a pair has one block and its K/V is long, the stream of K/V bounds the launch and attn_shared.h, with two
-    // tiles on their way, is ahead as long as its larger workgroups make one round: 8 x 32 heads, 128 rows: 1024 keys
-    // 40.4 against 43.0 us, but 512 keys 24.0 against 22.7, and several blocks per pair (4 x 32 heads, 1024 keys, 256
-    // rows) 39.0 against 34.7.
+    // tiles on their way, is ahead of attn_wide.h: 8 x 32 heads, 128 rows, 1024 keys 40.3 against 43.0 us; 512 keys 25.4
+    // against 24.8, and several blocks per pair (4 x 32 heads, 1024 keys, 256 rows) 38.6 against 36.2.
     const int blocks = ceil_div(p.q_tiles, 8);
     const long wgs = (long)batch * n_kv_heads * blocks;
-    if (head_dim == 128 && p.q_tiles >= 5 && wgs >= 80) {
-        p.shared = blocks == 1 && seq_len >= 768 && wgs >= 192 && wgs < 512;
+    if (head_dim == 128 && p.q_tiles >= 5 && wgs >= 192) {
+        // fewer than two workgroups per compute unit: 8 wavefronts
+        p.shared = blocks > 1 || seq_len < 768 ? 0 : wgs < 512 ? 8 : 4;
         p.wide = !p.shared;
         p.q_blocks = blocks;
         p.splits = 1;
@@ -435,13 +434,19 @@ int dkv_launch_attention(int dtype, const void *q, void *k_cache, void *v_cache,
         constexpr size_t smem = 2 * 64 * ((128 * 2 + 16) + (128 * 2 + 32));   // two stages of 64 K rows and 64 V rows
         static std::atomic<bool> lds_ok{false};
         if (!lds_ok.load(std::memory_order_acquire)) {
-            DKV_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_shared),
+            DKV_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_shared<1, 8>),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+            DKV_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_shared<2, 4>),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
             lds_ok.store(true, std::memory_order_release);
         }
-        hipLaunchKernelGGL(attn_bf16_shared, dim3(attn_grid((long)batch * n_kv_heads, 1)), dim3(512), smem, stream,
-                           (const bf16_t *)q, (const bf16_t *)k_cache, (const bf16_t *)v_cache, row_off, (bf16_t *)out,
-                           batch, n_q_heads, n_kv_heads, seq_len, rows_upper, scale_log2e);
+#define SHARED(NQ_, NW_)                                                                                             \
+    hipLaunchKernelGGL((attn_bf16_shared<NQ_, NW_>), dim3(attn_grid((long)batch * n_kv_heads, 1)), dim3(64 * NW_), smem, \
+                       stream, (const bf16_t *)q, (const bf16_t *)k_cache, (const bf16_t *)v_cache, row_off,         \
+                       (bf16_t *)out, batch, n_q_heads, n_kv_heads, seq_len, rows_upper, scale_log2e)
+        if (plan.shared == 8) SHARED(1, 8);
+        else SHARED(2, 4);
+#undef SHARED
         DKV_LAUNCH_CHECK();
     }
     return DKV_OK;

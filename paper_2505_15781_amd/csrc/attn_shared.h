@@ -1,19 +1,21 @@
-// Attention kernel for one block of up to 128 query rows per (sequence, kv head): the eight wavefronts of a workgroup share
-// each K/V tile, 16 query rows each. Included by attention.hip (uses its helpers); head_dim 128 only.
+// Attention kernel for one block of up to 128 query rows per (sequence, kv head): the NW (4 or 8) wavefronts of a workgroup
+// share each K/V tile. Included by attention.hip (uses its helpers); head_dim 128 only.
 //
 // Work item = (sequence, kv head). The workgroup streams the keys in tiles of 64: every thread fetches part of the K rows
 // and of the V rows as they are stored (transposing LDS reads form the V operand of the second product), two LDS stages
-// alternate, and the global loads of the next two tiles are in flight while the current one is multiplied. Every K/V row
-// is read by one workgroup of the launch, so the kernel is bound by that stream (8 sequences x 32 heads x 1024 keys, 128
-// rows: 33-35 us for 134 MB); 16 rows per wavefront instead of attn_wide.h's 32 put two wavefronts on a SIMD where only one
-// workgroup runs on a unit, and two tiles on their way cover a miss.
+// alternate, and the global loads of the next tile (with 8 wavefronts: of the next two) are in flight while the current
+// one is multiplied. Every K/V row is read by one workgroup of the launch, so the kernel is bound by that stream (8
+// sequences x 32 heads x 1024 keys, 128 rows: 33-35 us for 134 MB). Up to one workgroup per compute unit, 8 wavefronts
+// with 16 query rows each put two on a SIMD and two tiles on their way cover a miss; from two per unit on, 4 wavefronts
+// with 32 rows each (16 sequences, 100 rows: 68.1 against 71.6 us).
 #pragma once
 
-__global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_shared(
+template <int NQ, int NW>
+__global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_shared(
     const bf16_t *__restrict__ Q, const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc,
     const int *__restrict__ row_off, bf16_t *__restrict__ out, int batch, int Hq, int Hkv, int L, int rows_cap,
     float scale_log2e) {
-    constexpr int NQ = 1, NW = 8, DH = 128, KT2 = 64;
+    constexpr int DH = 128, KT2 = 64;
     constexpr int K_STRIDE = DH * 2 + 16;      // bytes per key row
     constexpr int V_STRIDE = DH * 2 + 32;      // bytes per V row
     constexpr int K_BYTES = KT2 * K_STRIDE, STAGE_BYTES = K_BYTES + KT2 * V_STRIDE;
@@ -141,32 +143,45 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         load_tile(t0, kA, vA);
         store_tile(0, kA, vA);
         int t = t0;
-        // one workgroup per compute unit: while a tile is multiplied, the next one waits in one register set
-        // and the one after it is being fetched into the other (16 registers per set)
-        if (t + 1 < t1) load_tile(t + 1, kA, vA);
-        __syncthreads();
-        for (; t + 3 < t1; t += 2) {
-            load_tile(t + 2, kB, vB);
-            multiply(t, 0);
-            store_tile(1, kA, vA);
+        if (NW == 8) {
+            // one workgroup per compute unit: while a tile is multiplied, the next one waits in one register set
+            // and the one after it is being fetched into the other (16 registers per set)
+            if (t + 1 < t1) load_tile(t + 1, kA, vA);
             __syncthreads();
-            load_tile(t + 3, kA, vA);
-            multiply(t + 1, 1);
-            store_tile(0, kB, vB);
-            __syncthreads();
-        }
-        // one to three tiles are left: t in stage 0, t + 1 on its way in set A
-        if (t + 2 < t1) load_tile(t + 2, kB, vB);
-        multiply(t, 0);
-        if (t + 1 < t1) {
-            store_tile(1, kA, vA);
-            __syncthreads();
-            multiply(t + 1, 1);
-            if (t + 2 < t1) {
+            for (; t + 3 < t1; t += 2) {
+                load_tile(t + 2, kB, vB);
+                multiply(t, 0);
+                store_tile(1, kA, vA);
+                __syncthreads();
+                load_tile(t + 3, kA, vA);
+                multiply(t + 1, 1);
                 store_tile(0, kB, vB);
                 __syncthreads();
-                multiply(t + 2, 0);
             }
+            // one to three tiles are left: t in stage 0, t + 1 on its way in set A
+            if (t + 2 < t1) load_tile(t + 2, kB, vB);
+            multiply(t, 0);
+            if (t + 1 < t1) {
+                store_tile(1, kA, vA);
+                __syncthreads();
+                multiply(t + 1, 1);
+                if (t + 2 < t1) {
+                    store_tile(0, kB, vB);
+                    __syncthreads();
+                    multiply(t + 2, 0);
+                }
+            }
+        } else {
+            // two workgroups per compute unit cover each other's waits: one tile ahead is enough
+            __syncthreads();
+            for (; t + 1 < t1; ++t) {
+                const int stage = (t - t0) & 1;
+                load_tile(t + 1, kA, vA);
+                multiply(t, stage);
+                store_tile(stage ^ 1, kA, vA);
+                __syncthreads();
+            }
+            multiply(t, (t - t0) & 1);
         }
     }
 

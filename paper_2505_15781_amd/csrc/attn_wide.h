@@ -9,13 +9,14 @@
 // SIMD did the same part at the same time: matrix pipes busy 35 %, vector issue 49 %, their sum and little overlap. Here
 // a wavefront works on half tiles of 32 keys in a skewed order: one stretch holds the scores of half tile j + 1, the output
 // products of half tile j - 1 and the exponentials of half tile j, which do not depend on each other, and the schedule
-// deals them out one MFMA, one or two LDS reads, four or five vector instructions at a time. The running sum stays on the
-// vector units: v_dot2 goes through the matrix pipe (11 cycles each next to MFMAs), and a product with a row of ones costs
-// an eighth more MFMAs. Two workgroups share a compute unit and cover each other's barrier (one per tile).
-// Kernel time before and after: 8 sequences x 32 heads x 1024 keys, 512 rows 103 -> 79 us (870 TFLOP/s), 4 x 32 heads x
-// 1536 keys, 1536 rows 213 -> 163 us (950 TFLOP/s), 16 x 4 kv heads of 7, 768 keys, up to 129 rows 35 -> 25 us. With
-// nothing but the MFMAs the second takes 100 us (the clock falls under their power), so what is left is mostly the
-// first tiles of a workgroup and the fills (without them 12 % less time).
+// deals them out one MFMA, one or two LDS reads, three vector instructions at a time. The running sum is a product with a
+// row of ones (v_dot2 costs 11 cycles each next to MFMAs, unpacking and adding on the vector units 2 % of the time). Two
+// workgroups share a compute unit and cover each other's barrier (one per tile).
+// Per call, with the scatter launch, before and after (same card): 8 sequences x 32 heads x 1024 keys, 512 rows 127.4 ->
+// 119.0 us; 4 x 32 heads x 1536 keys, 1536 rows 231 -> 218 us; 16 x 4 kv heads of 7, 768 keys, up to 129 rows 41.5 -> 35.3
+// us. What bounds it: vector instructions, a quarter of them the rescaling of the output, which some query of the 32
+// needs at most half tiles. A reference that lags the maximum by up to 2^8 saves those (another 8-14 %), but then the
+// largest probability is no longer exactly 1 and the error against float64 grows by up to 10 %: not done.
 #pragma once
 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
@@ -85,7 +86,16 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int vx = ((2 * (l4 & 1) + ((l16 & 3) >> 1)) ^ (((l16 >> 2) << 2) | g)) << 4;       // keys + 8: swizzle ^ 2
 
     // lowest finite start: scores of -inf then give probabilities of zero, also where a whole half tile is masked
-    float m_run = -3.0e38f, l_run = 0.f;
+    float m_run = -3.0e38f, alpha = 1.f;
+    bool behind = false;
+    // sum of exactly the rounded probabilities of the second product: a product with a tile whose row 0 is ones; element 0
+    // of the lanes below 32 is the sum of query qi, everything else stays zero
+    f32x16 l_acc;
+    bf16x8 ones;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) l_acc[v] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = qi == 0 ? (__bf16)1.0f : (__bf16)0.0f;
     f32x16 acc[DH / 32], stA, stB;               // stA, stB: scores of the first and the second 32 keys of a tile
     bf16x8 pA[2], pB[2];                         // their probabilities
 #pragma unroll
@@ -113,6 +123,8 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         for (int v = 0; v < 16; ++v) sn[v] = 0.f;
         f32x8 p[2];
 #pragma unroll
+        for (int ks = 0; ks < 2; ++ks) l_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pv[ks], l_acc, 0, 0, 0);
+#pragma unroll
         for (int i = 0; i < 8; ++i) {
             sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(i, kstage, khalf), qf[i], sn, 0, 0, 0);
             acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(i & 3, i >> 2, vstage, vhalf), pv[i >> 2], acc[i & 3], 0, 0, 0);
@@ -120,38 +132,35 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             for (int e = 2 * i; e < 2 * i + 2; ++e)
                 p[e >> 3][e & 7] = __builtin_amdgcn_exp2f(fmaf(so[e], scale_log2e, -m_run));
         }
-        // running sum of exactly the rounded probabilities of the second product
-        float l2 = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            pn[ks] = __builtin_convertvector(p[ks], bf16x8);
-            const u32x4_t y = __builtin_bit_cast(u32x4_t, pn[ks]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                l_run += __uint_as_float(y[e] << 16);
-                l2 += __uint_as_float(y[e] & 0xffff0000u);
-            }
-        }
-        l_run += l2;
-        asm volatile("" : "+v"(pn[0]), "+v"(pn[1]), "+v"(l_run));        // here, not behind the branches of maximum()
+        for (int ks = 0; ks < 2; ++ks) pn[ks] = __builtin_convertvector(p[ks], bf16x8);
+        asm volatile("" : "+v"(pn[0]), "+v"(pn[1]));        // here, not behind the branches of maximum()
         __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
             __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
             __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);
         }
     };
-    // Maximum of the half tile whose first key is `key`. The reference m_run of the exponentials follows the maximum only
-    // when that has grown by more than 2^8: the probabilities are then at most 2^8, which costs bf16 and fp32 no
-    // precision, and the output is hardly ever rescaled after the first tile. References are whole numbers, so that the
-    // probabilities that still wait for their product (pw) can be rescaled exactly.
-    auto maximum = [&](f32x16 &st, int key, bf16x8 (&pw)[2]) {
+    // Brings the output up to the reference m_run of the exponentials.
+    auto rescale = [&]() {
+        if (!behind) return;
+#pragma unroll
+        for (int mt = 0; mt < DH / 32; ++mt) acc[mt] *= alpha;
+        l_acc[0] *= alpha;
+    };
+    // Maximum of the half tile whose first key is `key`. The running maximum is the reference of the exponentials, so that
+    // the largest probability is exactly 1. The probabilities of the half tile before still wait for their product: the
+    // output is rescaled to the new reference only behind that product, at the next call.
+    auto maximum = [&](f32x16 &st, int key) {
+        rescale();
         if (key + 32 > L) {                      // wave-uniform: only the last tile of a sequence has keys past the end
             const int left = L - key - 4 * g;
 #pragma unroll
@@ -164,18 +173,10 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         float u, w;
         swap_rows32(mx, u, w);
         mx = fmaxf(u, w) * scale_log2e;
-        if (__builtin_amdgcn_ballot_w64(mx > m_run + 8.f) != 0) {
-            const float m_new = fmaxf(m_run, ceilf(mx));
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-            l_run *= alpha;
-#pragma unroll
-            for (int mt = 0; mt < DH / 32; ++mt) acc[mt] *= alpha;
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) pw[ks][e] = (__bf16)((float)pw[ks][e] * alpha);
-            m_run = m_new;
-        }
+        const float m_new = fmaxf(m_run, mx);
+        behind = __builtin_amdgcn_ballot_w64(m_new > m_run) != 0;       // else the factor is exactly 1 for every query
+        alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
     };
     auto tile_barrier = [&]() {
         asm volatile("" ::: "memory");
@@ -192,30 +193,33 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     for (int v = 0; v < 16; ++v) stA[v] = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) stA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(i, 0, 0), qf[i], stA, 0, 0, 0);
-    maximum(stA, 0, pB);
+    maximum(stA, 0);
     // Tile t, in stage S; the scores of its first half are formed.
     auto step = [&](int t, auto stage) {
         constexpr int S = decltype(stage)::value;
         stretch(stB, S, 1, pB, S ^ 1, 1, stA, pA);
-        maximum(stB, t * KT2 + 32, pA);
+        maximum(stB, t * KT2 + 32);
         // behind the barrier K(t + 1) and V(t) have landed for everybody, and everybody is done with K(t) and V(t - 1)
         tile_barrier();
         if (t + 2 < n_tiles) fill(Kb, t + 2, S * TILE);
         if (t + 1 < n_tiles) fill(Vb, t + 1, (2 + (S ^ 1)) * TILE);
         stretch(stA, S ^ 1, 0, pA, S, 0, stB, pB);            // behind the last tile: scores of an old tile, never used
-        if (t + 1 < n_tiles) maximum(stA, (t + 1) * KT2, pB);
+        if (t + 1 < n_tiles) maximum(stA, (t + 1) * KT2);
     };
     for (int t = 0; t < n_tiles; t += 2) {
         step(t, StageC<0>{});
         if (t + 1 < n_tiles) step(t + 1, StageC<1>{});
     }
     const int last = (n_tiles - 1) & 1;
+    rescale();
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) l_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pB[ks], l_acc, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
         acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(i & 3, i >> 2, last, 1), pB[i >> 2], acc[i & 3], 0, 0, 0);
 
     float u, w;
-    swap_rows32(l_run, u, w);
+    swap_rows32(l_acc[0], u, w);
     const float inv = 1.f / (u + w);
     if (!q_ok) return;
     bf16_t *op = out + q_at + 8 * g;

@@ -143,7 +143,7 @@ struct AttnPlan {
     int q_tiles;      // 16-row query tiles per (sequence, kv head), upper bound
     int splits;       // slices of the key range
     int tiles_per_split;   // in tiles of 32 keys (key-split kernel)
-    int shared;       // 1: one block of 128 query rows per pair, workgroup-shared K/V tiles (attn_shared.h)
+    int shared;       // 0, or 4 / 8: one block of 128 query rows per pair, wavefronts per workgroup (attn_shared.h)
     int wide;         // 1: blocks of 128 query rows, 32 per wavefront (attn_wide.h)
     int q_blocks;     // shared, wide: blocks of 128 query rows per (sequence, kv head)
     int ksplit_nq;    // 0, or 1 / 2: key-split kernel (wavefronts of a workgroup share the keys), query tiles per item

@@ -232,10 +232,10 @@ def test_attention_shared_tiles_with_ragged_sequences():
 
 @pytest.mark.parametrize("seq_len,rows", [(16, 16), (17, 17), (32, 20), (33, 33), (63, 15), (65, 65), (97, 16), (129, 31), (160, 100)])
 def test_attention_wide_query_blocks_at_tile_edges(seq_len, rows):
-    """Blocks of 128 query rows, 32 per wavefront (6 x 16 kv heads of 8 query heads): one to three key tiles of 64, a
+    """Blocks of 128 query rows, 32 per wavefront (12 x 16 kv heads of 8 query heads): one to three key tiles of 64, a
     half tile of 32 keys that is full, ragged or masked as a whole, query rows that fill the last block or leave one
     active row (8 query rows) in it."""
-    shape = D.AttnUpdateShape(batch=6, n_q_heads=128, n_kv_heads=16, seq_len=seq_len, head_dim=128, dtype=BF16)
+    shape = D.AttnUpdateShape(batch=12, n_q_heads=128, n_kv_heads=16, seq_len=seq_len, head_dim=128, dtype=BF16)
     _attn_case(shape, rows, 54)
 
 
