@@ -87,7 +87,7 @@ Layout make_layout(const dkv_model_desc &m, const dkv_run_desc &r) {
     y.head_fused = true;
     y.head_records = 1;
     for (int c = 1; c <= y.cand_cap; ++c) {
-        GemmPlan p = dkv_gemm_plan(m.dtype, c, m.vocab, m.d_model);
+        GemmPlan p = dkv_gemm_plan(m.dtype, c, m.vocab, m.d_model, true);
         if (p.split_k > 1) {
             size_t a = (size_t)p.split_k * c * m.vocab;
             if (a > pf) pf = a;
@@ -442,7 +442,7 @@ extern "C" int dkv_denoise_step(dkv_ctx *c, int32_t step, const int32_t *forced_
     c->last_step_captured = c->capture != nullptr;
     // vocabulary head on the candidate rows only (same result as projecting every active row)
     if ((rc = dkv_launch_gather_rows(dt, s, cands, c->a, c->cand_row, c->counts, c->a_c, d))) return rc;
-    GemmPlan hp = dkv_gemm_plan(dt, cands, m.vocab, d);
+    GemmPlan hp = dkv_gemm_plan(dt, cands, m.vocab, d, true);
     if (c->lay.head_fused) {
         // softmax maximum, sum and arg max per column tile leave the projection's epilogue and a small kernel merges
         // the tiles of a row: the [candidates, vocab] logits are never written (unless the caller asks for them)

@@ -83,7 +83,8 @@ struct GemmPlan {
     int frac_units; // 0, or K tiles per workgroup when workgroups take 3/4 of a tile's K range each
     int flags;     // GEMM_FLAG_* launch options of the gemm_dma kinds
 };
-GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k);
+// `one_slice`: K is not split (products whose epilogue needs whole sums: the vocabulary statistics)
+GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, bool one_slice = false);
 int dkv_gemm_plan_valid(int dtype, int k, GemmPlan p);
 
 // Per (candidate row, vocabulary range): running maximum of the logits, sum of exp(x - max) over the range,

@@ -176,7 +176,7 @@ int effective_split(int k, int split) {
 
 }  // namespace
 
-GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k) {
+GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, bool one_slice) {
     GemmPlan p;
     p.split_k = 1;
     p.frac_units = 0;
@@ -190,29 +190,30 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k) {
         return p;
     }
     // Tile shape and K split: the candidate with the smallest predicted launch time. The prediction is a
-    // small model of this kernel on MI355X, its constants fitted to a sweep of every (tile shape, split)
-    // over the layer shapes of the 8B and 7B models at 16..12288 rows (mean loss against the best measured
-    // candidate 2 %, worst 24 %):
-    //   a workgroup needs, per K tile, the longer of filling its LDS stage (~49 GB/s per compute unit, and
-    //   ~14 TB/s over all workgroups in flight) and its MFMAs (~5.3 TFLOP/s per compute unit);
+    // small model of these kernels on MI355X, its constants fitted to two sweeps of every (tile shape, split)
+    // over the layer and vocabulary shapes of the 8B and 7B models at 31 row counts from 16 to 12288, each launch timed
+    // together with the row kernel that consumes it, on weights that no cache holds (mean loss against the best
+    // measured candidate 1.1 %, worst 14 %; with the constants of the 4-wavefront kernels for all tiles 5.8 % and 70 %):
+    //   a workgroup of the 4-wavefront tiles needs, per K tile, the longer of filling its LDS stage (52 GB/s per compute
+    //   unit, 14.5 TB/s over all workgroups in flight) and its MFMAs (5.7 TFLOP/s per compute unit);
+    //   a workgroup of the 8-wavefront tiles needs the times of kPingPong, alone and with the whole chip at work;
     //   workgroups run in rounds of 256 (one per compute unit), a partly filled round costs a full one;
     //   no launch beats streaming its operands and results once;
-    //   K slices add the write and re-read of their partial sums by the consumer.
-    // Tiles of 96 and 192 columns exist because 12288 / 96 = 128 and 24576 / 192 = 128 column tiles make
-    // exactly one or two full rounds where 128- and 256-column tiles leave a quarter of the chip idle
-    // (256x192 does the same for 257..512 rows of the widest projection).
-    constexpr double kFillPerCu = 48785.0, kFlopsPerCu = 5332277.0, kFillAll = 14076233.0;   // bytes, flops per us
-    constexpr double kStream = 7841520.0, kReduce = 1819886.0;                                  // bytes per us
-    constexpr double kLaunch = 3.5, kPipeFill = 0.7, kReduceFixed = 1.7;                        // us
+    //   every further K slice adds the write and re-read of its partial sums by the consumer.
+    // Tiles of 96 and 192 columns or rows exist because 12288 / 96 = 128 and 24576 / 192 = 128 column tiles make
+    // exactly one or two full rounds where 128- and 256-column tiles leave a quarter of the chip idle, and 129..192 or
+    // 257..384 rows fill one or two 192-row tiles (320 rows of the 8B vocabulary: 821 -> 393 us).
+    constexpr double kFillPerCu = 52032.0, kFlopsPerCu = 5698686.0, kFillAll = 14478510.0;   // bytes, flops per us
+    constexpr double kStream = 7841520.0, kReduce = 1849696.0;                                  // bytes per us
+    constexpr double kLaunch = 3.5, kPipeFill = 0.7, kPipeFill8 = 0.16, kReduceFixed = 3.2;     // us
+    struct { int kind; double alone, full; } constexpr kPingPong[] = {                          // us per K tile
+        {GEMM_DMA_256x256, 1.207, 1.336}, {GEMM_DMA_256x192, 1.041, 1.092}, {GEMM_DMA_192x256, 0.980, 1.078}};
     static const int kSplits[] = {1, 2, 3, 4, 6, 8};
     const int kt_total = k / BK;
     double best = 0.0;
     p.kind = -1;
     for (int kind = 0; kind <= GEMM_DMA_LAST; ++kind) {
         const KindInfo &ki = kKinds[kind];
-        // 192-row tiles are for thousands of rows, where 6144 = 32 x 192 rows against 4096 columns make two full
-        // rounds of workgroups (128x256 tiles: three rounds of smaller tiles; 256x256: one and a half)
-        if (kind == GEMM_DMA_192x256 && m_upper < 4 * ki.bm) continue;
         if (ki.bm > 32 && ki.bm >= 4 * m_upper) continue;       // mostly padding
         if (ki.bm < 128 && m_upper > 4 * ki.bm) continue;       // W re-read too often
         const int tiles = ceil_div(m_upper, ki.bm) * ceil_div(n, ki.bn);
@@ -220,19 +221,28 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k) {
         for (int s : kSplits) {
             const int nk = ceil_div(kt_total, s);
             if (ceil_div(kt_total, nk) != s || (s > 1 && nk < 8)) continue;
+            if (s > 1 && (one_slice || m_upper > 2048)) continue;       // beyond the sweep: thousands of rows fill the chip
             const long wgs = (long)tiles * s;
             const long rounds = (wgs + 255) / 256;
-            double t_tile = fill / kFillPerCu;
-            if (flops / kFlopsPerCu > t_tile) t_tile = flops / kFlopsPerCu;
             const double in_flight = (double)(wgs < 256 ? wgs : 256);
-            if (in_flight * fill / kFillAll > t_tile) t_tile = in_flight * fill / kFillAll;
-            // (the 192x256 tile's fill and MFMA times are equal, so neither hides behind the other: measured 5 % above
-            // the model where the 256x256 tile meets it)
-            double t = rounds * (nk * t_tile * (kind == GEMM_DMA_192x256 ? 1.05 : 1.0) + kPipeFill);
+            double t_rounds = 0.0;             // per K tile, over all rounds
+            for (const auto &pp : kPingPong)
+                if (pp.kind == kind) {
+                    const double last = pp.full * (double)(wgs - (rounds - 1) * 256) / 256.0;
+                    t_rounds = (rounds - 1) * pp.full + (last > pp.alone ? last : pp.alone);
+                }
+            const bool eight = t_rounds > 0.0;
+            if (!eight) {
+                double t_tile = fill / kFillPerCu;
+                if (flops / kFlopsPerCu > t_tile) t_tile = flops / kFlopsPerCu;
+                if (in_flight * fill / kFillAll > t_tile) t_tile = in_flight * fill / kFillAll;
+                t_rounds = rounds * t_tile;
+            }
+            double t = nk * t_rounds + rounds * (eight ? kPipeFill8 : kPipeFill);
             const double stream = (2.0 * n * k + 2.0 * m_upper * (double)k + 4.0 * s * m_upper * (double)n) / kStream;
             if (stream > t) t = stream;
             t += kLaunch;
-            if (s > 1) t += (s + 1) * 4.0 * m_upper * (double)n / kReduce + kReduceFixed;
+            if (s > 1) t += (s - 1) * 4.0 * m_upper * (double)n / kReduce + kReduceFixed;
             if (p.kind < 0 || t < best) {
                 best = t;
                 p.kind = kind;
@@ -240,16 +250,20 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k) {
             }
         }
     }
-    // Launch options, from the same sweep: a staggered K start pays when there is one row of tiles
-    // (all workgroups of a K slice would otherwise read the same A columns at once); weights that are read once
-    // (one row of tiles) are streamed with the non-temporal hint; the XCD-grouped order
-    // pays for the largest tiles once there are enough tile rows to form 4-row groups.
+    // Launch options, from the same sweeps: a staggered K start pays when there is one row of tiles
+    // (all workgroups of a K slice would otherwise read the same A columns at once), and with two or three rows of tiles
+    // and several rounds of workgroups where the rows are a multiple of 4 KB apart, so that equal columns sit in the same
+    // memory channels (14 % less time at K = 4096 over 1000 workgroups, none at K = 3584 or with one round); weights that
+    // are read once (one row of tiles) are streamed with the non-temporal hint; the XCD-grouped order
+    // pays once there are enough tile rows to form groups, for every tile on wide products (10-17 % less time from 24576
+    // columns up), elsewhere for the largest tiles.
     const int tiles_m = ceil_div(m_upper, kKinds[p.kind].bm);
-    if (tiles_m == 1) p.flags |= GEMM_FLAG_STAGGER;
+    const long wgs = (long)tiles_m * ceil_div(n, kKinds[p.kind].bn) * p.split_k;
+    if (tiles_m == 1 || (tiles_m <= 3 && p.split_k == 1 && wgs > 512 && k % 2048 == 0)) p.flags |= GEMM_FLAG_STAGGER;
     // (not for matrices small enough to stay in the 256 MB last-level cache from one step to the next)
     if (tiles_m == 1 && (size_t)n * k * 2 >= ((size_t)32 << 20)) p.flags |= GEMM_FLAG_STREAM_W;
-    if (((p.kind == GEMM_DMA_256x256 || p.kind == GEMM_DMA_256x192 || p.kind == GEMM_DMA_192x256) && tiles_m >= 4) ||
-        (p.kind == GEMM_DMA_128x256 && tiles_m >= 6))
+    if (tiles_m >= 4 && (n >= 24576 || p.kind == GEMM_DMA_256x256 || p.kind == GEMM_DMA_256x192 || p.kind == GEMM_DMA_192x256 ||
+                         (p.kind == GEMM_DMA_128x256 && tiles_m >= 6)))
         p.flags |= GEMM_FLAG_XCD_GROUP;
     // Giving 256 workgroups 3/4 of a tile's K range each (frac_units, kept for experiments through
     // dkv_gemm_with) was measured to take the same time as two full slices, so it is never planned.
