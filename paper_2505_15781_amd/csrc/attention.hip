@@ -202,17 +202,20 @@ __device__ __forceinline__ void store4(bf16_t *p, f32x4 v) {
                                                (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
 }
 
-// Generic kernel: one wavefront per (row, head), keys in chunks of 64. Scores: a lane per key. Output: DH / 4 lanes per
-// key with four dims each, so the V rows are read coalesced and only the last step reduces over lanes (with a whole
-// output vector per lane that was DH wavefront reductions: 64 rows x 4 heads x 64 keys of 32 floats, 11.1 -> 6.9 us).
+// Generic kernel: one wavefront per (row, head), keys in chunks of 64. Scores and softmax state: a lane per key of the
+// chunk, each with its own running maximum. Output: DH / 4 lanes per key with four dims each, so the V rows are read
+// coalesced; a lane keeps one sum per key place that it serves, and only the last step adds those up and reduces over
+// lanes (with a whole output vector per lane that was DH wavefront reductions: 64 rows x 4 heads x 64 keys of 32 floats,
+// 11.1 -> 7 us). The sums run in the order of a butterfly over the 64 key places, as with one output vector per lane, so
+// that candidates of nearly equal confidence keep their order.
 template <typename T, int DH>
 __global__ __launch_bounds__(256) void attn_generic(const T *__restrict__ Q, const T *__restrict__ Kc,
                                                     const T *__restrict__ Vc,
                                                     const int *__restrict__ row_off, T *__restrict__ out,
                                                     int batch, int Hq, int Hkv, int L, int rows_cap,
                                                     float scale) {
-    constexpr int LPK = DH / 4, KPP = 64 / LPK;         // lanes per key, keys per pass of the second product
-    __shared__ float prob[4][64];
+    constexpr int LPK = DH / 4, KPP = 64 / LPK, NJ = 64 / KPP;      // lanes per key, keys per pass, passes per chunk
+    __shared__ float2 state[4][64];                                 // (rescale, probability) of each key place
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long pair = (long)blockIdx.x * 4 + wave;
     const int total_rows = min(row_off[batch], rows_cap);
@@ -225,41 +228,61 @@ __global__ __launch_bounds__(256) void attn_generic(const T *__restrict__ Q, con
     const T *Kb = Kc + ((size_t)b * Hkv + kvh) * (size_t)L * DH;
     const T *Vb = Vc + ((size_t)b * Hkv + kvh) * (size_t)L * DH;
     const int kk = lane / LPK, d = (lane % LPK) * 4;
-    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    f32x4 o[NJ];                                                    // key places kk + KPP j
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
+    auto share = [&](float2 x) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        state[wave][lane] = x;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
     for (int k0 = 0; k0 < L; k0 += 64) {
         const T *kp = Kb + (size_t)min(k0 + lane, L - 1) * DH;
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < DH / 4; ++i) {
             const f32x4 q = load4(qp + 4 * i), k = load4(kp + 4 * i);
-            s = fmaf(q[0], k[0], fmaf(q[1], k[1], fmaf(q[2], k[2], fmaf(q[3], k[3], s))));
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s = fmaf(q[v], k[v], s);
         }
-        s = k0 + lane < L ? s * scale : -INFINITY;
-        const float mn = fmaxf(m, wave_max(s));          // finite: every chunk holds a key
+        s *= scale;
+        const float mn = fmaxf(m, s);
         const float a = expf(m - mn), p = expf(s - mn);
-        l = l * a + p;
-        m = mn;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        prob[wave][lane] = p;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        o *= a;
-        const int n = min(64, L - k0);
-#pragma unroll 8
-        for (int j = 0; j < n; j += KPP) {
-            const int key = j + kk;                       // past the end: probability zero, last row
-            const float w = prob[wave][key];
-            o += w * load4(Vb + (size_t)min(k0 + key, L - 1) * DH + d);
+        if (k0 + lane < L) {
+            l = l * a + p;
+            m = mn;
+        }
+        share(make_float2(a, p));
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int key = k0 + KPP * j + kk;
+            const float2 ap = state[wave][KPP * j + kk];
+            const f32x4 v = load4(Vb + (size_t)min(key, L - 1) * DH + d);
+            if (key < L) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[j][i] = fmaf(ap.y, v[i], o[j][i] * ap.x);
+            }
         }
     }
-    const float inv = 1.f / wave_sum(l);
+    const float Mx = wave_max(m);
+    const float w = (m == -INFINITY) ? 0.f : expf(m - Mx);
+    const float inv = 1.f / wave_sum(l * w);
+    share(make_float2(w, 0.f));
 #pragma unroll
-    for (int x = LPK; x < 64; x <<= 1)
+    for (int j = 0; j < NJ; ++j) o[j] *= state[wave][KPP * j + kk].x;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] += __shfl_xor(o[i], x, 64);
-    if (kk == 0) store4(out + (size_t)pair * DH + d, o * inv);
+    for (int x = NJ / 2; x > 0; x >>= 1)
+#pragma unroll
+        for (int j = 0; j < x; ++j) o[j] += o[j + x];
+    f32x4 y = o[0];
+#pragma unroll
+    for (int x = 32; x >= LPK; x >>= 1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i] += __shfl_xor(y[i], x, 64);
+    if (kk == 0) store4(out + (size_t)pair * DH + d, y * inv);
 }
 
 template <typename T>

@@ -113,11 +113,11 @@ def test_eight_wavefront_tiles_at_short_k_and_tile_edges(kind, k_tiles, m, n):
     check_close(y, x.astype(np.float64) @ w.astype(np.float64).T, 1e-5, f"{kind} {m}x{n}x{k}")
 
 
-@pytest.mark.parametrize("m,n,k", [(1, 2, 4), (16, 16, 64), (17, 30, 60), (64, 130, 68), (65, 16, 1028), (512, 4096, 64),
-                                   (513, 4096, 64)])
+@pytest.mark.parametrize("m,n,k", [(1, 2, 4), (16, 16, 64), (17, 30, 60), (64, 130, 68), (65, 16, 1028), (128, 4096, 64),
+                                   (129, 4096, 64), (16, 16, 128), (20, 20, 132)])
 def test_fp32_projection_of_few_rows_at_tile_edges(m, n, k):
-    """16x16 tiles with K dealt to four wavefronts in pieces of 16: row, column and K remainders, and the two sides of
-    the line beyond which 64x64 tiles take over. fp32 sums of at most 1028 products."""
+    """16x16 tiles, K in pieces of 128: row, column and K remainders, and the two sides of the line beyond which 64x64
+    tiles take over. fp32 sums of at most 1028 products."""
     import paper_2505_15781_amd as P
     x = D.normal_f32(14, 1, (m, k))
     w = D.normal_f32(14, 2, (n, k), std=0.02)
