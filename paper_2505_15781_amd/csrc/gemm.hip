@@ -219,9 +219,9 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, bool one_slice) {
         const int tiles = ceil_div(m_upper, ki.bm) * ceil_div(n, ki.bn);
         const double fill = (ki.bm + ki.bn) * 128.0, flops = 2.0 * ki.bm * ki.bn * BK;
         for (int s : kSplits) {
+            if (s > 1 && (one_slice || m_upper > 2048)) break;          // beyond the sweep: thousands of rows fill the chip
             const int nk = ceil_div(kt_total, s);
             if (ceil_div(kt_total, nk) != s || (s > 1 && nk < 8)) continue;
-            if (s > 1 && (one_slice || m_upper > 2048)) continue;       // beyond the sweep: thousands of rows fill the chip
             const long wgs = (long)tiles * s;
             const long rounds = (wgs + 255) / 256;
             const double in_flight = (double)(wgs < 256 ? wgs : 256);
