@@ -27,11 +27,6 @@ template <int V> struct StageC { static constexpr int value = V; };
 // 4 different groups (transposing reads: 32 bytes of 4 rows each).
 __device__ __forceinline__ int wide_swizzle(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
 
-// 16 bytes per lane from base + voff into LDS at lds_addr + 16 * lane (base, lds_addr wave-uniform); awaited with vmcnt
-__device__ __forceinline__ void wide_dma16(uint32_t voff, const void *base, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
-}
-
 constexpr int WIDE_LDS_BYTES = 4 * 64 * 256;         // K0 K1 V0 V1
 
 __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_wide(
@@ -63,7 +58,7 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
         for (int i = 0; i < DI; ++i) {
             const int row = 4 * (i * NW + wave) + l4;
-            wide_dma16((uint32_t)min(row, L - 1 - t * KT2) * ROW + chunk[i], base + (size_t)t * TILE,
+            dma16_at((uint32_t)min(row, L - 1 - t * KT2) * ROW + chunk[i], base + (size_t)t * TILE,
                        lds_base + dst + 4 * (i * NW + wave) * ROW);
         }
     };

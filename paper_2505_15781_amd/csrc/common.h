@@ -67,6 +67,21 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
     return t;
 }
 
+// 16 bytes per lane from global memory into LDS at lds_addr + 16 * lane (lds_addr and base wave-uniform): from a pointer of
+// each lane, the same with the non-temporal hint, and from a wave-uniform base with a byte offset of each lane. Issued
+// through inline assembly so that the compiler does not serialise a ring of such loads on its own conservative wait;
+// completion is awaited explicitly with vmcnt. A load to LDS reads M0 too early in the cycle after M0 was written: one
+// wait state is needed in between (the compiler puts it in for its own code, but does not look inside an asm text).
+__device__ __forceinline__ void dma16(const void *g, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_addr) : "memory", "m0");
+}
+__device__ __forceinline__ void dma16_nt(const void *g, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "s"(lds_addr) : "memory", "m0");
+}
+__device__ __forceinline__ void dma16_at(uint32_t voff, const void *base, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
+}
+
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 

@@ -11,18 +11,10 @@ namespace {
 constexpr int BK = 64;   // K elements per LDS tile (8 chunks of 8 bf16)
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
-// 16 bytes per lane from global memory into LDS at lds_addr + 16 * lane (lds_addr wave-uniform).
-// Issued through inline assembly so that the compiler does not serialise the ring on its own
-// conservative wait; completion is awaited explicitly with vmcnt below.
-__device__ __forceinline__ void dma16(const void *g, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_addr) : "memory", "m0");
-}
-// The same with the non-temporal hint: for weights that no other workgroup will read again (one row of tiles),
-// so that they do not push the activations out of L2. Measured on cold weights: 5-11 % less time for the QKV
+// Weights that no other workgroup will read again (one row of tiles) are fetched with the non-temporal hint
+// (dma16_nt), so that they do not push the activations out of L2. Measured on cold weights: 5-11 % less time for the QKV
 // and gate/up shapes at 16-128 rows; with several rows of tiles the hint costs up to 2x, hence the flag.
-__device__ __forceinline__ void dma16_nt(const void *g, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "s"(lds_addr) : "memory", "m0");
-}
+
 // s_waitcnt immediate: vmcnt(n) [bits 3:0 and 15:14], lgkmcnt(0) when `lgkm0`, expcnt untouched
 __device__ __forceinline__ constexpr int waitcnt_imm(int n, bool lgkm0) {
     return (n & 15) | ((n >> 4) << 14) | 0x0070 | (lgkm0 ? 0 : 0x0F00);

@@ -25,11 +25,6 @@
 //   6144 x 4096 x 12288 (192x256)      592 -> 475 us                     4096 x 37888 x 3584   1078 -> 825 us
 #pragma once
 
-// 16 bytes per lane from base + voff into LDS at lds_addr + 16 * lane (base and lds_addr wave-uniform)
-__device__ __forceinline__ void dma16_at(uint32_t voff, const void *base, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
-}
-
 // all but the newest VM vector memory operations of this wavefront are done, and all its LDS operations
 template <int VM> __device__ __forceinline__ void wait_all_but() {
     static_assert(VM >= 0 && VM < 64, "vmcnt is a 6-bit counter");
