@@ -190,10 +190,14 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, bool one_slice) {
         return p;
     }
     // Tile shape and K split: the candidate with the smallest predicted launch time. The prediction is a
-    // small model of these kernels on MI355X, its constants fitted to two sweeps of every (tile shape, split)
-    // over the layer and vocabulary shapes of the 8B and 7B models at 31 row counts from 16 to 12288, each launch timed
-    // together with the row kernel that consumes it, on weights that no cache holds (mean loss against the best
-    // measured candidate 1.1 %, worst 14 %; with the constants of the 4-wavefront kernels for all tiles 5.8 % and 70 %):
+    // small model of these kernels on MI355X, its constants fitted to two sweeps of the (tile shape, split) pairs
+    // over the layer and vocabulary shapes of the 8B and 7B models at 31 row counts from 16 to 12288 (beyond 2048 rows
+    // unsplit only), each launch timed together with the row kernel that consumes it, on weights that no cache holds
+    // (mean loss against the best measured candidate 1.1 %, worst 14 %; with the constants of the 4-wavefront kernels for
+    // all tiles 5.8 % and 70 %). A third sweep, of splits 1 to 8 at 2048 to 8192 rows over six layer shapes and seven narrow
+    // ones (512 to 3072 columns), was not fitted to: mean loss 0.7 %, worst 14 %. Slices pay there too: 3584 x 18944 at 2049
+    // rows 313 -> 248 us, 512 x 4096 at 2049 rows 41 -> 25, 1024 x 8192 at 3072 rows 83 -> 63, 4096 x 12288 at 4352 rows
+    // 471 -> 421 us.
     //   a workgroup of the 4-wavefront tiles needs, per K tile, the longer of filling its LDS stage (52 GB/s per compute
     //   unit, 14.5 TB/s over all workgroups in flight) and its MFMAs (5.7 TFLOP/s per compute unit);
     //   a workgroup of the 8-wavefront tiles needs the times of kPingPong, alone and with the whole chip at work;
@@ -203,13 +207,24 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, bool one_slice) {
     // Tiles of 96 and 192 columns or rows exist because 12288 / 96 = 128 and 24576 / 192 = 128 column tiles make
     // exactly one or two full rounds where 128- and 256-column tiles leave a quarter of the chip idle, and 129..192 or
     // 257..384 rows fill one or two 192-row tiles (320 rows of the 8B vocabulary: 821 -> 393 us).
+    // Products of more than 768 tiles are not sliced: a last round that is nearly empty is a small part of theirs (4096 x
+    // 12288 at 9217 rows, 592 tiles: 2 slices 865 against 896 us; 3584 x 18944 at 14017 rows, 770: 1725 against 1788).
+    // The planner runs for every row count that a run can have when the run is set up, so divisions are kept out of the
+    // inner loop.
     constexpr double kFillPerCu = 52032.0, kFlopsPerCu = 5698686.0, kFillAll = 14478510.0;   // bytes, flops per us
-    constexpr double kStream = 7841520.0, kReduce = 1849696.0;                                  // bytes per us
+    constexpr double kPerStream = 1.0 / 7841520.0, kPerReduce = 1.0 / 1849696.0;                // us per byte
     constexpr double kLaunch = 3.5, kPipeFill = 0.7, kPipeFill8 = 0.16, kReduceFixed = 3.2;     // us
-    struct { int kind; double alone, full; } constexpr kPingPong[] = {                          // us per K tile
-        {GEMM_DMA_256x256, 1.207, 1.336}, {GEMM_DMA_256x192, 1.041, 1.092}, {GEMM_DMA_192x256, 0.980, 1.078}};
-    static const int kSplits[] = {1, 2, 3, 4, 6, 8};
+    struct PingPong { double alone, full; };                                                    // us per K tile
+    constexpr PingPong kPingPong[] = {{}, {}, {}, {}, {1.207, 1.336}, {}, {}, {1.041, 1.092}, {0.980, 1.078}};
+    static_assert(GEMM_DMA_256x256 == 4 && GEMM_DMA_256x192 == 7 && GEMM_DMA_192x256 == 8 && GEMM_DMA_LAST == 8, "order of kPingPong");
     const int kt_total = k / BK;
+    struct { int s, nk; } slices[6];       // K slices worth trying, K tiles of each
+    int n_slices = 0;
+    for (int s : {1, 2, 3, 4, 6, 8}) {
+        const int nk = ceil_div(kt_total, s);
+        if (s == 1 || (!one_slice && nk >= 8 && ceil_div(kt_total, nk) == s)) slices[n_slices++] = {s, nk};
+    }
+    const double product = 4.0 * m_upper * (double)n, operands = 2.0 * n * k + 2.0 * m_upper * (double)k;
     double best = 0.0;
     p.kind = -1;
     for (int kind = 0; kind <= GEMM_DMA_LAST; ++kind) {
@@ -218,31 +233,26 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, bool one_slice) {
         if (ki.bm < 128 && m_upper > 4 * ki.bm) continue;       // W re-read too often
         const int tiles = ceil_div(m_upper, ki.bm) * ceil_div(n, ki.bn);
         const double fill = (ki.bm + ki.bn) * 128.0, flops = 2.0 * ki.bm * ki.bn * BK;
-        for (int s : kSplits) {
-            if (s > 1 && (one_slice || m_upper > 2048)) break;          // beyond the sweep: thousands of rows fill the chip
-            const int nk = ceil_div(kt_total, s);
-            if (ceil_div(kt_total, nk) != s || (s > 1 && nk < 8)) continue;
-            const long wgs = (long)tiles * s;
-            const long rounds = (wgs + 255) / 256;
-            const double in_flight = (double)(wgs < 256 ? wgs : 256);
-            double t_rounds = 0.0;             // per K tile, over all rounds
-            for (const auto &pp : kPingPong)
-                if (pp.kind == kind) {
-                    const double last = pp.full * (double)(wgs - (rounds - 1) * 256) / 256.0;
-                    t_rounds = (rounds - 1) * pp.full + (last > pp.alone ? last : pp.alone);
-                }
-            const bool eight = t_rounds > 0.0;
-            if (!eight) {
-                double t_tile = fill / kFillPerCu;
-                if (flops / kFlopsPerCu > t_tile) t_tile = flops / kFlopsPerCu;
-                if (in_flight * fill / kFillAll > t_tile) t_tile = in_flight * fill / kFillAll;
-                t_rounds = rounds * t_tile;
+        const double t_cu = fill / kFillPerCu > flops / kFlopsPerCu ? fill / kFillPerCu : flops / kFlopsPerCu;
+        const double t_all = fill / kFillAll;                   // per workgroup in flight
+        const PingPong &pp = kPingPong[kind];
+        const bool eight = pp.full > 0.0;
+        for (int i = 0; i < n_slices && (i == 0 || tiles <= 768); ++i) {
+            const int s = slices[i].s;
+            const long wgs = (long)tiles * s, rounds = (wgs + 255) / 256;
+            double t_rounds;                   // per K tile, over all rounds
+            if (eight) {
+                const double last = pp.full * (double)(wgs - (rounds - 1) * 256) * (1.0 / 256.0);
+                t_rounds = (rounds - 1) * pp.full + (last > pp.alone ? last : pp.alone);
+            } else {
+                const double all = (double)(wgs < 256 ? wgs : 256) * t_all;
+                t_rounds = rounds * (all > t_cu ? all : t_cu);
             }
-            double t = nk * t_rounds + rounds * (eight ? kPipeFill8 : kPipeFill);
-            const double stream = (2.0 * n * k + 2.0 * m_upper * (double)k + 4.0 * s * m_upper * (double)n) / kStream;
+            double t = slices[i].nk * t_rounds + rounds * (eight ? kPipeFill8 : kPipeFill);
+            const double stream = (operands + s * product) * kPerStream;
             if (stream > t) t = stream;
             t += kLaunch;
-            if (s > 1) t += (s - 1) * 4.0 * m_upper * (double)n / kReduce + kReduceFixed;
+            if (s > 1) t += (s - 1) * product * kPerReduce + kReduceFixed;
             if (p.kind < 0 || t < best) {
                 best = t;
                 p.kind = kind;

@@ -1,0 +1,28 @@
+"""The launch plans of the library (host code, no GPU): what a call of given sizes is routed to."""
+import ctypes as C
+
+TILES = ("dma_32x128", "dma_64x128", "dma_128x128", "dma_128x256", "dma_256x256", "dma_128x96", "dma_128x192", "dma_256x192",
+         "dma_192x256", "reg_64x128", "simt")
+EIGHT_WAVEFRONTS = ("dma_256x256", "dma_256x192", "dma_192x256")
+STAGGER, XCD_GROUP, STREAM_W = 1, 2, 8
+
+
+class GemmPlan(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("kind", "split_k", "frac_units", "flags")]
+
+    @property
+    def tile(self):
+        return TILES[self.kind]
+
+    def grid(self, m, n):
+        """(rows of tiles, workgroups)"""
+        bm, bn = (int(x) for x in self.tile.split("_")[1].split("x"))
+        rows = -(-m // bm)
+        return rows, rows * -(-n // bn) * self.split_k
+
+
+def gemm_plan(m, n, k, one_slice=False, dtype=0):
+    from paper_2505_15781_amd import binding
+    f = binding.lib._Z13dkv_gemm_planiiiib
+    f.restype, f.argtypes = GemmPlan, [C.c_int] * 4 + [C.c_bool]
+    return f(dtype, m, n, k, one_slice)

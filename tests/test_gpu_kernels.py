@@ -42,9 +42,10 @@ def test_projection_planned_launch_on_a_weight_matrix_that_is_streamed(m):
 
 
 @pytest.mark.parametrize("m,n,k", [(150, 24576, 4096), (192, 12288, 4096), (320, 12288, 2048), (384, 24576, 1024), (513, 3584, 4096),
-                                   (600, 45000, 2048), (1500, 4096, 4096), (2048, 4608, 3584), (2049, 4608, 3584)])
-def test_projection_planned_launch_from_150_to_2049_rows(m, n, k):
-    """Row counts at which the planner takes 192-row tiles, slices K at hundreds to 2048 rows (and not beyond), and
+                                   (600, 45000, 2048), (1500, 4096, 4096), (2048, 4608, 3584), (2049, 4608, 3584),
+                                   (2049, 512, 4096), (2304, 3584, 18944), (3072, 1024, 8192)])
+def test_projection_planned_launch_from_150_to_3072_rows(m, n, k):
+    """Row counts at which the planner takes 192-row tiles, slices K at hundreds to thousands of rows, and
     staggers the K start over two or three rows of tiles and several rounds of workgroups. fp32 sums of k products of
     N(0, 1) and N(0, 0.02^2): rounding stays below 1e-6 of the largest value, the bar of the other projections is 1e-5."""
     import paper_2505_15781_amd as P
