@@ -264,14 +264,16 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, bool one_slice) {
     // (all workgroups of a K slice would otherwise read the same A columns at once), and with two or three rows of tiles
     // and several rounds of workgroups where the rows are a multiple of 4 KB apart, so that equal columns sit in the same
     // memory channels (14 % less time at K = 4096 over 1000 workgroups, none at K = 3584 or with one round); weights that
-    // are read once (one row of tiles) are streamed with the non-temporal hint; the XCD-grouped order
+    // are read once (one row of tiles) are streamed with the non-temporal hint by the 4-wavefront tiles (in the 8-wavefront
+    // loop, which has no such loads, the hint measured 0-13 % slower with K slices and between 5 % faster and 4 % slower
+    // without); the XCD-grouped order
     // pays once there are enough tile rows to form groups, for every tile on wide products (10-17 % less time from 24576
     // columns up), elsewhere for the largest tiles.
     const int tiles_m = ceil_div(m_upper, kKinds[p.kind].bm);
     const long wgs = (long)tiles_m * ceil_div(n, kKinds[p.kind].bn) * p.split_k;
     if (tiles_m == 1 || (tiles_m <= 3 && p.split_k == 1 && wgs > 512 && k % 2048 == 0)) p.flags |= GEMM_FLAG_STAGGER;
     // (not for matrices small enough to stay in the 256 MB last-level cache from one step to the next)
-    if (tiles_m == 1 && (size_t)n * k * 2 >= ((size_t)32 << 20)) p.flags |= GEMM_FLAG_STREAM_W;
+    if (tiles_m == 1 && kPingPong[p.kind].full == 0.0 && (size_t)n * k * 2 >= ((size_t)32 << 20)) p.flags |= GEMM_FLAG_STREAM_W;
     if (tiles_m >= 4 && (n >= 24576 || p.kind == GEMM_DMA_256x256 || p.kind == GEMM_DMA_256x192 || p.kind == GEMM_DMA_192x256 ||
                          (p.kind == GEMM_DMA_128x256 && tiles_m >= 6)))
         p.flags |= GEMM_FLAG_XCD_GROUP;

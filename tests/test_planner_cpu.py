@@ -1,7 +1,7 @@
 """The rules by which projection and attention calls choose their kernels (host code)."""
 import pytest
 
-from plans import gemm_plan
+from plans import EIGHT_WAVEFRONTS, STREAM_W, gemm_plan
 
 
 @pytest.mark.parametrize("m,n,k", [(2049, 512, 4096), (4096, 512, 4096), (2304, 3584, 18944), (3072, 1024, 8192), (5000, 1024, 4096)])
@@ -15,3 +15,17 @@ def test_k_is_sliced_at_thousands_of_rows_where_few_columns_leave_the_chip_idle(
 @pytest.mark.parametrize("m,n,k", [(6144, 24576, 4096), (12288, 37888, 3584), (4096, 12288, 4096)])
 def test_k_is_not_sliced_where_the_tiles_fill_the_chip(m, n, k):
     assert gemm_plan(m, n, k).split_k == 1
+
+
+def test_the_streaming_hint_is_planned_only_for_tiles_that_follow_it():
+    """The 8-wavefront tiles have no non-temporal loads: a plan with the flag would claim what the launch does not do."""
+    asked = 0
+    for n, k in [(12288, 4096), (24576, 4096), (37888, 3584), (126464, 4096), (152064, 3584), (3584, 18944)]:
+        for m in range(1, 257):
+            for one_slice in (False, True):
+                p = gemm_plan(m, n, k, one_slice)
+                if p.flags & STREAM_W:
+                    asked += 1
+                    assert p.tile not in EIGHT_WAVEFRONTS, (m, n, k, p.tile)
+                    assert p.grid(m, n)[0] == 1
+    assert asked > 500
