@@ -190,16 +190,16 @@ __global__ __launch_bounds__(256) void attn_merge(const float *__restrict__ part
 }
 
 // Four consecutive elements as floats.
-__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4_el *>(p); }
 __device__ __forceinline__ f32x4 load4(const bf16_t *p) {
-    const uint2 v = *reinterpret_cast<const uint2 *>(p);
+    const u32x2 v = *reinterpret_cast<const bf16x4_el *>(p);
     return f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
                  __uint_as_float(v.y & 0xffff0000u)};
 }
-__device__ __forceinline__ void store4(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
+__device__ __forceinline__ void store4(float *p, f32x4 v) { *reinterpret_cast<f32x4_el *>(p) = v; }
 __device__ __forceinline__ void store4(bf16_t *p, f32x4 v) {
-    *reinterpret_cast<uint2 *>(p) = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                                               (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+    *reinterpret_cast<bf16x4_el *>(p) = u32x2{(uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
+                                              (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16)};
 }
 
 // Generic kernel: one wavefront per (row, head), keys in chunks of 64. Scores and softmax state: a lane per key of the

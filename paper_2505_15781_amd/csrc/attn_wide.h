@@ -232,6 +232,6 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             }
             const auto p0 = __builtin_amdgcn_permlane32_swap(y[0], y[2], false, false);
             const auto p1 = __builtin_amdgcn_permlane32_swap(y[1], y[3], false, false);
-            *reinterpret_cast<uint4 *>(op + 32 * mt + 8 * c) = make_uint4(p0[0], p1[0], p0[1], p1[1]);
+            *reinterpret_cast<bf16x8_el *>(op + 32 * mt + 8 * c) = u32x4{p0[0], p1[0], p0[1], p1[1]};
         }
 }

@@ -13,6 +13,14 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(8))) float f32x8;
 
+// The same widths for memory that is only known to be aligned to its elements (caller's fp32 and bf16 arrays where no wider
+// alignment is asked for): the loads and stores are the same instructions, which take any such address.
+typedef f32x4 __attribute__((aligned(4))) f32x4_el;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef u32x2 __attribute__((aligned(2))) bf16x4_el;      // four bf16
+typedef u32x4 __attribute__((aligned(2))) bf16x8_el;      // eight bf16
+
 #define DKV_WAVE 64
 
 void dkv_set_error(const char *fmt, ...);

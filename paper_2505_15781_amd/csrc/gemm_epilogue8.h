@@ -8,7 +8,7 @@
 template <int MT, int NT>
 __device__ __forceinline__ void store_tile8(const f32x4 (&acc)[2][2][MT][NT], float *out, int row0, int col0, int M, int N,
                                             int lane) {
-    const bool vec = (N & 3) == 0;             // 16-byte alignment of every row
+    const bool vec = (N & 3) == 0;             // four columns of a row or none
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -22,7 +22,7 @@ __device__ __forceinline__ void store_tile8(const f32x4 (&acc)[2][2][MT][NT], fl
                     const int n = col0 + (b * NT + j) * 16 + 4 * (lane >> 4);
                     if (m >= M) continue;
                     if (vec) {
-                        if (n < N) *reinterpret_cast<f32x4 *>(row + n) = acc[h][b][i][j];
+                        if (n < N) *reinterpret_cast<f32x4_el *>(row + n) = acc[h][b][i][j];
                     } else {
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
@@ -68,7 +68,7 @@ __device__ __forceinline__ void run_epilogue8(const f32x4 (&acc)[2][2][MT][NT], 
             const unsigned char *src = lds + r * STRIDE + ch * 16;
             bf16_t *dst = f + (size_t)m * F + c;
             if ((F & 7) == 0) {
-                if (c < F) *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(src);
+                if (c < F) *reinterpret_cast<bf16x8_el *>(dst) = *reinterpret_cast<const u32x4 *>(src);
             } else {
                 for (int v = 0; v < 8; ++v)
                     if (c + v < F) dst[v] = reinterpret_cast<const bf16_t *>(src)[v];

@@ -28,8 +28,8 @@ __global__ __launch_bounds__(256) void gemm_f32_few_rows(const float *__restrict
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             const int e = tid + 256 * i, row = e / (KC / 4), k = kb + e % (KC / 4) * 4, kc = min(k, K - 4);
-            ra[i] = *reinterpret_cast<const f32x4 *>(A + (size_t)min(m0 + row, m_upper - 1) * K + kc);
-            rw[i] = *reinterpret_cast<const f32x4 *>(W + (size_t)min(n0 + row, N - 1) * K + kc);
+            ra[i] = *reinterpret_cast<const f32x4_el *>(A + (size_t)min(m0 + row, m_upper - 1) * K + kc);
+            rw[i] = *reinterpret_cast<const f32x4_el *>(W + (size_t)min(n0 + row, N - 1) * K + kc);
         }
     };
     float acc = 0.f;

@@ -295,6 +295,50 @@ def test_attention_generic_paths():
                None, 43, ragged=[7])
 
 
+def _shifted(t):
+    """A copy of t that starts one element behind a 16-byte boundary."""
+    buf = torch.empty(t.numel() + 17, dtype=t.dtype, device=t.device)
+    lead = (-buf.data_ptr() % 16) // t.element_size() + 1
+    view = buf[lead:lead + t.numel()].view(t.shape)
+    assert view.data_ptr() % 16 == t.element_size()
+    return view.copy_(t)
+
+
+@pytest.mark.parametrize("dtype,dh", [(FP32, 32), (FP32, 128), (BF16, 32)])
+def test_generic_attention_takes_arrays_at_any_element_boundary(dtype, dh):
+    """Where the header asks for no alignment, four-element loads and stores may start at any element: bit-identical."""
+    import paper_2505_15781_amd as P
+    B, Hq, Hkv, L, A = 2, 4, 2, 70, 9
+    c = D.attn_update_case(D.AttnUpdateShape(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=L, head_dim=dh, dtype=dtype), A, 56)
+    idx, off = torch.from_numpy(c["active_idx"]).cuda(), torch.from_numpy(c["active_off"]).cuda()
+    got = []
+    for place in (lambda t: t, _shifted):
+        # the cache update moves whole 16-byte pieces: the cache and the new rows stay on their boundaries
+        kc, vc, kn, vn = (_dev(c[n], dtype) for n in ("k_cache", "v_cache", "k_new", "v_new"))
+        q = place(_dev(c["q"], dtype))
+        out = place(torch.zeros_like(q))
+        P.attn_update(kc, vc, q, kn, vn, idx, off, out, B * A, A, dtype, None)
+        got.append(out.clone())
+    torch.cuda.synchronize()
+    assert torch.equal(*got)
+
+
+@pytest.mark.parametrize("dtype,kind,m,n,k,options", [(FP32, "simt", 20, 24, 132, 0), (BF16, "dma_256x256", 40, 72, 128, 0),
+                                                      (BF16, "dma_192x256", 40, 72, 128, 0), (BF16, "dma_256x192", 40, 80, 128, 4)])
+def test_projection_writes_results_at_any_element_boundary(dtype, kind, m, n, k, options):
+    """fp32 product, fp32 operands and the bf16 result of the fused SwiGLU one element behind a 16-byte boundary."""
+    import paper_2505_15781_amd as P
+    from paper_2505_15781_amd import binding as b
+    x, w = _dev(D.normal_f32(15, 1, (m, k), bf16=True), dtype), _dev(D.normal_f32(15, 2, (n, k), bf16=True), dtype)
+    y = P.gemm(x, w, dtype, kind=kind, split_k=1, options=options)
+    ys = _shifted(torch.zeros_like(y))
+    if dtype == FP32:                       # bf16 operands travel in 16-byte pieces
+        x, w = _shifted(x), _shifted(w)
+    b._check(b.lib.dkv_gemm_with(b._ptr(x), b._ptr(w), b._ptr(ys), m, n, k, dtype, b.GEMM_KINDS[kind], 1, options, None, 0, b._stream()))
+    torch.cuda.synchronize()
+    assert torch.equal(y, ys)
+
+
 def test_attention_no_rows_is_a_no_op():
     shape = D.AttnUpdateShape(batch=2, n_q_heads=4, n_kv_heads=2, seq_len=64, head_dim=128, dtype=BF16)
     _attn_case(shape, 0, 51)
