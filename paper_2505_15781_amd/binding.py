@@ -79,7 +79,7 @@ lib.dkv_attn_update_workspace_bytes.argtypes = [c_i32] * 7
 lib.dkv_attn_update.argtypes = [c_vp] * 8 + [c_i32] * 8 + [c_vp, c_sz, c_vp]
 lib.dkv_attn_update_static.argtypes = [c_vp] * 8 + [c_i32] * 8 + [c_vp]
 STATIC_SCRATCH_BYTES = 4 << 20
-_marshal.bind(C.cast(lib.dkv_attn_update, c_vp).value, C.cast(lib.dkv_attn_update_static, c_vp).value)
+_marshal.bind(C.cast(lib.dkv_attn_update, c_vp).value, C.cast(lib.dkv_attn_update_static, c_vp).value, c_i32)
 lib.dkv_concat_reorder.argtypes = [c_vp] * 7 + [c_i32] * 6 + [c_vp]
 lib.dkv_peak_copy.argtypes = [c_vp, c_vp, c_sz, c_vp]
 lib.dkv_peak_read.argtypes = [c_vp, c_vp, c_sz, c_vp]

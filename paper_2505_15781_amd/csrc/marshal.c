@@ -17,7 +17,8 @@ typedef int (*attn_update_static_fn)(void *, void *, const void *, const void *,
 
 static attn_update_fn f_attn_update;
 static attn_update_static_fn f_attn_update_static;
-static PyObject *s_data_ptr, *s_shape, *s_nbytes;
+static PyObject *s_data_ptr, *s_shape, *s_nbytes, *s_value;
+static PyObject *c_int_type;      /* ctypes.c_int32 */
 
 /* address of a tensor's first element, NULL for None; -1 with an exception set on failure */
 static int get_ptr(PyObject *t, void **p) {
@@ -30,23 +31,20 @@ static int get_ptr(PyObject *t, void **p) {
     return PyErr_Occurred() ? -1 : 0;
 }
 
-/* up to `max` sizes of a tensor; returns the number of dimensions, -1 with an exception set on failure */
-static Py_ssize_t get_shape(PyObject *t, int32_t *dims, Py_ssize_t max) {
-    PyObject *s = PyObject_GetAttr(t, s_shape);
-    if (!s) return -1;
-    if (!PyTuple_Check(s)) {
-        Py_DECREF(s);
-        PyErr_SetString(PyExc_TypeError, "shape is not a tuple");
-        return -1;
-    }
-    const Py_ssize_t n = PyTuple_GET_SIZE(s);
-    for (Py_ssize_t i = 0; i < n && i < max; ++i) dims[i] = (int32_t)PyLong_AsLong(PyTuple_GET_ITEM(s, i));
-    Py_DECREF(s);
-    return PyErr_Occurred() ? -1 : n;
-}
-
+/* a whole number of 32 bits, as ctypes takes it for an int32 argument: int, anything with __index__, or a ctypes int; a
+ * number that does not fit is an error (it would name other sizes than the caller's) */
 static int get_i32(PyObject *o, int32_t *v) {
+    PyObject *held = NULL;
+    if (!PyLong_Check(o) && c_int_type) {
+        const int is_c_int = PyObject_IsInstance(o, c_int_type);
+        if (is_c_int < 0) return -1;
+        if (is_c_int) {
+            if (!(held = PyObject_GetAttr(o, s_value))) return -1;
+            o = held;
+        }
+    }
     const long x = PyLong_AsLong(o);
+    Py_XDECREF(held);
     if (x == -1 && PyErr_Occurred()) return -1;
     if (x < INT32_MIN || x > INT32_MAX) {
         PyErr_SetString(PyExc_OverflowError, "argument does not fit 32 bits");
@@ -54,6 +52,25 @@ static int get_i32(PyObject *o, int32_t *v) {
     }
     *v = (int32_t)x;
     return 0;
+}
+
+/* up to `max` sizes of a tensor; returns the number of dimensions, -1 with an exception set on failure */
+static Py_ssize_t get_shape(PyObject *t, int32_t *dims, Py_ssize_t max) {
+    PyObject *s = PyObject_GetAttr(t, s_shape);
+    if (!s) return -1;
+    if (!PyTuple_Check(s)) {
+        PyObject *seq = PySequence_Tuple(s);
+        Py_DECREF(s);
+        if (!(s = seq)) return -1;
+    }
+    Py_ssize_t n = PyTuple_GET_SIZE(s);
+    for (Py_ssize_t i = 0; i < n && i < max; ++i)
+        if (get_i32(PyTuple_GET_ITEM(s, i), &dims[i])) {
+            n = -1;
+            break;
+        }
+    Py_DECREF(s);
+    return n;
 }
 
 /* (k_cache, v_cache, q, k_new, v_new, active_idx, active_off, out, rows, max_rows_per_seq, dtype, workspace, stream) for
@@ -112,16 +129,20 @@ static PyObject *call_attn_update(PyObject *const *a, Py_ssize_t n, int with_wor
 static PyObject *py_attn_update(PyObject *self, PyObject *const *a, Py_ssize_t n) { return call_attn_update(a, n, 1); }
 static PyObject *py_attn_update_static(PyObject *self, PyObject *const *a, Py_ssize_t n) { return call_attn_update(a, n, 0); }
 
-/* bind(address of dkv_attn_update, address of dkv_attn_update_static) */
+/* bind(address of dkv_attn_update, address of dkv_attn_update_static, ctypes.c_int32) */
 static PyObject *py_bind(PyObject *self, PyObject *const *a, Py_ssize_t n) {
-    if (n != 2) {
-        PyErr_SetString(PyExc_TypeError, "two addresses are expected");
+    if (n != 3) {
+        PyErr_SetString(PyExc_TypeError, "two addresses and the integer type are expected");
         return NULL;
     }
     void *x = PyLong_AsVoidPtr(a[0]), *y = PyLong_AsVoidPtr(a[1]);
     if (PyErr_Occurred()) return NULL;
     f_attn_update = (attn_update_fn)x;
     f_attn_update_static = (attn_update_static_fn)y;
+    PyObject *old = c_int_type;
+    Py_INCREF(a[2]);
+    c_int_type = a[2];
+    Py_XDECREF(old);
     Py_RETURN_NONE;
 }
 
@@ -137,5 +158,6 @@ PyMODINIT_FUNC PyInit__marshal(void) {
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_shape = PyUnicode_InternFromString("shape");
     s_nbytes = PyUnicode_InternFromString("nbytes");
-    return s_data_ptr && s_shape && s_nbytes ? PyModule_Create(&module) : NULL;
+    s_value = PyUnicode_InternFromString("value");
+    return s_data_ptr && s_shape && s_nbytes && s_value ? PyModule_Create(&module) : NULL;
 }
