@@ -109,11 +109,12 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-_raw_stream = torch._C._cuda_getCurrentRawStream      # the handle alone, without a Stream object around it
+# the handle alone, without a Stream object around it; not in every build of torch
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream if _raw_stream is None else _raw_stream(torch.cuda.current_device())
 
 
 def _tdtype(dtype):

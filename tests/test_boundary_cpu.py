@@ -97,3 +97,16 @@ def test_kernel_kind_numbers_of_the_header_and_the_binding_agree():
     for tag, (rows, cols) in tiles.items():
         mt, nt, wm, wn = (int(x) for x in re.match(r"gemm_dma<\*,(\d),(\d),(\d),(\d),\d>", names[defs[tag]]).groups())
         assert (32 * mt * wm, 32 * nt * wn) == (rows, cols), tag
+
+
+def test_the_binding_imports_without_torch_internals():
+    """Planning and workspace sizes need no GPU build of torch: a torch without the raw-stream function still imports."""
+    import subprocess, sys
+    code = ("import torch, ctypes as C\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "from paper_2505_15781_amd import binding as b\n"
+            "assert b.lib.dkv_gemm_workspace_bytes(2, 128, 64, b.FP32) == 0\n"
+            "torch.cuda.current_stream = lambda: type('S', (), {'cuda_stream': 77})()\n"
+            "assert b._stream() == 77\n")
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
