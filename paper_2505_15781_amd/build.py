@@ -49,7 +49,8 @@ def build(verbose=False, incremental=False):
     with ThreadPoolExecutor(max(1, min(8, len(jobs)))) as ex:
         list(ex.map(lambda c: _run(c, verbose), jobs))
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB], verbose)
-    _run([os.environ.get("CC", "gcc"), "-O2", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
+    # plain C by the same compiler; needs the Python headers, not the HIP runtime
+    _run([HIPCC, "-no-hip-rt", "-x", "c", "-O2", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
           os.path.join(CSRC, "marshal.c"), "-o", MARSHAL], verbose)
     return LIB
 

@@ -5,6 +5,9 @@
  * are handed over as addresses at import, so this module links against nothing.
  *
  * Tensors are asked for data_ptr(), shape and nbytes by name: no dependence on torch's headers or layout. */
+/* Only the stable ABI (Python 3.10 and later): the module's file name says nothing about the interpreter it was built
+ * with, so nothing of that interpreter's object layout may be compiled in. */
+#define Py_LIMITED_API 0x030A0000
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stddef.h>
@@ -24,7 +27,7 @@ static PyObject *c_int_type;      /* ctypes.c_int32 */
 static int get_ptr(PyObject *t, void **p) {
     *p = NULL;
     if (t == Py_None) return 0;
-    PyObject *v = PyObject_CallMethodNoArgs(t, s_data_ptr);
+    PyObject *v = PyObject_CallMethodObjArgs(t, s_data_ptr, NULL);
     if (!v) return -1;
     *p = PyLong_AsVoidPtr(v);
     Py_DECREF(v);
@@ -63,9 +66,9 @@ static Py_ssize_t get_shape(PyObject *t, int32_t *dims, Py_ssize_t max) {
         Py_DECREF(s);
         if (!(s = seq)) return -1;
     }
-    Py_ssize_t n = PyTuple_GET_SIZE(s);
+    Py_ssize_t n = PyTuple_Size(s);
     for (Py_ssize_t i = 0; i < n && i < max; ++i)
-        if (get_i32(PyTuple_GET_ITEM(s, i), &dims[i])) {
+        if (get_i32(PyTuple_GetItem(s, i), &dims[i])) {
             n = -1;
             break;
         }

@@ -74,3 +74,19 @@ def test_shapes_may_be_any_sequence_of_four_sizes(call):
     for shape in ((3, 2, 70), (1, 3, 2, 70, 64)):
         with pytest.raises(ValueError):
             call(k_cache=Fake(16, shape))
+
+
+def test_the_module_uses_only_the_stable_abi():
+    """Its file name carries no interpreter version: whatever it refers to has to be the same in every Python from 3.10 on."""
+    import shutil, subprocess
+    from paper_2505_15781_amd import binding as b
+    if not shutil.which("nm"):
+        pytest.skip("no nm")
+    out = subprocess.run(["nm", "-D", "--undefined-only", b._marshal.__file__], capture_output=True, text=True, check=True).stdout
+    used = {line.split()[-1] for line in out.splitlines() if "Py" in line}
+    stable = {"PyErr_Occurred", "PyErr_SetString", "PyEval_RestoreThread", "PyEval_SaveThread", "PyExc_IndexError", "PyExc_OverflowError",
+              "PyExc_RuntimeError", "PyExc_TypeError", "PyExc_ValueError", "PyLong_AsLong", "PyLong_AsSize_t", "PyLong_AsVoidPtr",
+              "PyLong_FromLong", "PyModule_Create2", "PyObject_CallMethodObjArgs", "PyObject_GetAttr", "PyObject_IsInstance",
+              "PySequence_Tuple", "PyTuple_GetItem", "PyTuple_Size", "PyType_GetFlags", "PyUnicode_InternFromString", "_Py_Dealloc",
+              "_Py_NoneStruct", "Py_IncRef", "Py_DecRef"}
+    assert used and used <= stable, used - stable
