@@ -88,10 +88,6 @@ Layout make_layout(const dkv_model_desc &m, const dkv_run_desc &r) {
     y.head_records = 1;
     for (int c = 1; c <= y.cand_cap; ++c) {
         GemmPlan p = dkv_gemm_plan(m.dtype, c, m.vocab, m.d_model, true);
-        if (p.split_k > 1) {
-            size_t a = (size_t)p.split_k * c * m.vocab;
-            if (a > pf) pf = a;
-        }
         // the epilogue needs the tile kernel with one K slice for every candidate count of the run
         if (!dkv_gemm_can_fuse_head(m.dtype, m.d_model, p)) y.head_fused = false;
         else if ((size_t)c * dkv_gemm_tiles_n(p, m.vocab) > y.head_records) y.head_records = (size_t)c * dkv_gemm_tiles_n(p, m.vocab);
@@ -460,12 +456,7 @@ extern "C" int dkv_denoise_step(dkv_ctx *c, int32_t step, const int32_t *forced_
         if ((rc = dkv_launch_head_merge(s, cands, c->head_part, eh.head_tiles, c->counts, c->cand_tok, c->cand_conf, c->status))) return rc;
     } else {
         float *lg = logits_out ? logits_out : c->logits;
-        if (hp.split_k == 1) {
-            if ((rc = timed_gemm(c, c->a_c, c->lm_head, lg, cands, n_cand, m.vocab, d, hp))) return rc;
-        } else {
-            if ((rc = timed_gemm(c, c->a_c, c->lm_head, c->part, cands, n_cand, m.vocab, d, hp))) return rc;
-            if ((rc = dkv_launch_reduce_partials(s, c->part, hp.split_k, (size_t)cands * m.vocab, lg, (size_t)cands * m.vocab))) return rc;
-        }
+        if ((rc = timed_gemm(c, c->a_c, c->lm_head, lg, cands, n_cand, m.vocab, d, hp))) return rc;
         if ((rc = dkv_launch_head_stats(s, cands, lg, c->counts, m.vocab, m.mask_id, c->cand_tok, c->cand_conf, c->status,
                                         c->head_part))) return rc;
     }

@@ -52,7 +52,6 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu
     const bf16_t *Kb = Kc + ((size_t)b * Hkv + kvh) * (size_t)L * DH;
     const bf16_t *Vb = Vc + ((size_t)b * Hkv + kvh) * (size_t)L * DH;
     const int n_tiles = (L + KT2 - 1) / KT2;
-    const int t0 = 0, t1 = n_tiles;
 
     // per thread: CH chunks (16 B) of K and of V per tile, in register set A or B on their way to LDS
     constexpr int NT = 64 * NW, CH = KT2 * (DH / 8) / NT;
@@ -134,55 +133,52 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) __attribute__((amdgpu_waves_per_eu
             }
     };
 
-    // Tile t0 + i is multiplied out of LDS stage i & 1. t0 and t1 are uniform for the workgroup, so every
+    // Tile t is multiplied out of LDS stage t & 1. The number of tiles is the same for the whole launch, so every
     // wavefront passes the same barriers. The steady-state loops issue the same loads on every pass, without a
     // branch around them, so the wait in front of a tile store counts exactly that tile's loads (behind a
     // conditional load the compiler can only wait for everything, which would put the prefetch in front of the
     // products it is meant to overlap); the last tiles, which prefetch less, are peeled off.
-    if (t0 < t1) {
-        load_tile(t0, kA, vA);
-        store_tile(0, kA, vA);
-        int t = t0;
-        if (NW == 8) {
-            // one workgroup per compute unit: while a tile is multiplied, the next one waits in one register set
-            // and the one after it is being fetched into the other (16 registers per set)
-            if (t + 1 < t1) load_tile(t + 1, kA, vA);
+    load_tile(0, kA, vA);
+    store_tile(0, kA, vA);
+    int t = 0;
+    if (NW == 8) {
+        // one workgroup per compute unit: while a tile is multiplied, the next one waits in one register set
+        // and the one after it is being fetched into the other (16 registers per set)
+        if (t + 1 < n_tiles) load_tile(t + 1, kA, vA);
+        __syncthreads();
+        for (; t + 3 < n_tiles; t += 2) {
+            load_tile(t + 2, kB, vB);
+            multiply(t, 0);
+            store_tile(1, kA, vA);
             __syncthreads();
-            for (; t + 3 < t1; t += 2) {
-                load_tile(t + 2, kB, vB);
-                multiply(t, 0);
-                store_tile(1, kA, vA);
-                __syncthreads();
-                load_tile(t + 3, kA, vA);
-                multiply(t + 1, 1);
+            load_tile(t + 3, kA, vA);
+            multiply(t + 1, 1);
+            store_tile(0, kB, vB);
+            __syncthreads();
+        }
+        // one to three tiles are left: t in stage 0, t + 1 on its way in set A
+        if (t + 2 < n_tiles) load_tile(t + 2, kB, vB);
+        multiply(t, 0);
+        if (t + 1 < n_tiles) {
+            store_tile(1, kA, vA);
+            __syncthreads();
+            multiply(t + 1, 1);
+            if (t + 2 < n_tiles) {
                 store_tile(0, kB, vB);
                 __syncthreads();
+                multiply(t + 2, 0);
             }
-            // one to three tiles are left: t in stage 0, t + 1 on its way in set A
-            if (t + 2 < t1) load_tile(t + 2, kB, vB);
-            multiply(t, 0);
-            if (t + 1 < t1) {
-                store_tile(1, kA, vA);
-                __syncthreads();
-                multiply(t + 1, 1);
-                if (t + 2 < t1) {
-                    store_tile(0, kB, vB);
-                    __syncthreads();
-                    multiply(t + 2, 0);
-                }
-            }
-        } else {
-            // two workgroups per compute unit cover each other's waits: one tile ahead is enough
-            __syncthreads();
-            for (; t + 1 < t1; ++t) {
-                const int stage = (t - t0) & 1;
-                load_tile(t + 1, kA, vA);
-                multiply(t, stage);
-                store_tile(stage ^ 1, kA, vA);
-                __syncthreads();
-            }
-            multiply(t, (t - t0) & 1);
         }
+    } else {
+        // two workgroups per compute unit cover each other's waits: one tile ahead is enough
+        __syncthreads();
+        for (; t + 1 < n_tiles; ++t) {
+            load_tile(t + 1, kA, vA);
+            multiply(t, t & 1);
+            store_tile((t & 1) ^ 1, kA, vA);
+            __syncthreads();
+        }
+        multiply(t, t & 1);
     }
 
 #pragma unroll
