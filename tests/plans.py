@@ -26,3 +26,22 @@ def gemm_plan(m, n, k, one_slice=False, dtype=0):
     f = binding.lib._Z13dkv_gemm_planiiiib
     f.restype, f.argtypes = GemmPlan, [C.c_int] * 4 + [C.c_bool]
     return f(dtype, m, n, k, one_slice)
+
+
+class AttnPlan(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("use_mfma", "q_tiles", "splits", "tiles_per_split", "shared", "wide", "q_blocks", "ksplit_nq",
+                                       "ksplit_waves", "q_groups")]
+
+    @property
+    def kernel(self):
+        """'generic', 'wide', 'shared8', 'shared4', or 'ksplit' with query tiles per item and wavefronts, e.g. 'ksplit2x8'"""
+        if not self.use_mfma:
+            return "generic"
+        return "wide" if self.wide else f"shared{self.shared}" if self.shared else f"ksplit{self.ksplit_nq}x{self.ksplit_waves}"
+
+
+def attn_plan(shape, max_rows_per_seq):
+    from paper_2505_15781_amd import binding
+    f = binding.lib._Z13dkv_attn_planiiiiiii
+    f.restype, f.argtypes = AttnPlan, [C.c_int] * 7
+    return f(shape.dtype, shape.batch, shape.n_q_heads, shape.n_kv_heads, shape.seq_len, shape.head_dim, max_rows_per_seq)

@@ -8,6 +8,7 @@ from dkv_inputs.configs import BF16, FP32
 from oracle.attn_update import attn_update as oracle_attn_update
 from helpers import rel_err
 from gpu_parity import check_close, tolerances
+from plans import attn_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -172,8 +173,11 @@ def test_projection_kernel_rejects_shapes_it_cannot_take():
     check_close(y, x.float().cpu().numpy().astype(np.float64) @ w.float().cpu().numpy().astype(np.float64).T, 1e-5, "reg")
 
 
-def _attn_case(shape, n_active, seed, ragged=None, q_scale=1.0):
+def _attn_case(shape, n_active, seed, ragged=None, q_scale=1.0, kernel=None):
+    """`kernel`: the route that the case is there for (a changed dispatch must not leave a kernel without its tests)."""
     import paper_2505_15781_amd as P
+    if kernel:
+        assert attn_plan(shape, n_active if ragged is None else max(ragged)).kernel == kernel
     c = D.attn_update_case(shape, n_active, seed, ragged=ragged)
     c["q"] = c["q"] * np.float32(q_scale)            # a power of two: still exact bfloat16 values
     dt = shape.dtype
@@ -217,33 +221,31 @@ def test_attention_key_slices_across_workgroups(dh):
 
 
 def test_attention_many_query_tiles_per_head():
-    """Enough query rows per kv head for the kernel whose wavefronts share K/V tiles (GQA group of 8 and
-    79 rows: 40 tiles = 5 full blocks of 8), and a count that leaves its last block almost empty (66 rows:
-    33 tiles)."""
+    """Several blocks of 128 query rows per kv head (GQA group of 8 and 79 rows: 5 blocks, almost all full), and a count
+    that leaves the last block almost empty (66 rows: 16 of its 128 query rows)."""
     shape = D.AttnUpdateShape(batch=16, n_q_heads=128, n_kv_heads=16, seq_len=300, head_dim=128, dtype=BF16)
-    _attn_case(shape, 79, 36)
-    _attn_case(shape, 66, 37)
+    _attn_case(shape, 79, 36, kernel="wide")
+    _attn_case(shape, 66, 37, kernel="wide")
 
 
 @pytest.mark.parametrize("seq_len", [64, 100, 192, 300, 512])
-def test_attention_shared_tiles_eight_wavefronts(seq_len):
-    """Fewer than two workgroups per compute unit for the shared-tile kernel (4 x 16 kv heads x 5 blocks = 320):
-    its 8-wavefront form, which keeps two tiles on their way. Key counts of 1, 2 (ragged), 3, 5 (ragged) and 8
-    tiles take both exits of its two-tile loop; 66 rows leave the last block almost empty."""
+def test_attention_wide_blocks_over_one_to_eight_key_tiles(seq_len):
+    """Several blocks of query rows per pair (4 x 16 kv heads x 4 or 5 blocks): key counts of 1, 2 (ragged), 3, 5 (ragged)
+    and 8 tiles, i.e. odd and even numbers of the tiles that alternate between the two LDS stages; 66 rows leave the last
+    block almost empty."""
     shape = D.AttnUpdateShape(batch=4, n_q_heads=128, n_kv_heads=16, seq_len=seq_len, head_dim=128, dtype=BF16)
     n = min(79, seq_len)
-    _attn_case(shape, n, 44)
-    _attn_case(shape, min(66, seq_len), 45)
+    _attn_case(shape, n, 44, kernel="wide")
+    _attn_case(shape, min(66, seq_len), 45, kernel="wide")
 
 
-def test_attention_shared_tiles_with_ragged_sequences():
-    """Shared-tile kernel over sequences with no active row at all, with every position active (first and last
-    included) and with a few: in its 8-wavefront form (one block of query tiles per (sequence, kv head), K/V
-    fetched with the streaming hint) and in its 4-wavefront form (several blocks per pair)."""
+def test_attention_wide_blocks_with_ragged_sequences():
+    """Sequences with no active row at all, with every position active (first and last included) and with a few: one block
+    of query rows per (sequence, kv head), and several."""
     shape = D.AttnUpdateShape(batch=4, n_q_heads=64, n_kv_heads=64, seq_len=300, head_dim=128, dtype=BF16)
-    _attn_case(shape, None, 52, ragged=[100, 0, 128, 5])
+    _attn_case(shape, None, 52, ragged=[100, 0, 128, 5], kernel="wide")
     shape = D.AttnUpdateShape(batch=4, n_q_heads=128, n_kv_heads=16, seq_len=300, head_dim=128, dtype=BF16)
-    _attn_case(shape, None, 53, ragged=[79, 0, 300, 5])
+    _attn_case(shape, None, 53, ragged=[79, 0, 300, 5], kernel="wide")
 
 
 @pytest.mark.parametrize("seq_len,rows", [(16, 16), (17, 17), (32, 20), (33, 33), (63, 15), (65, 65), (97, 16), (129, 31), (160, 100)])
@@ -252,15 +254,21 @@ def test_attention_wide_query_blocks_at_tile_edges(seq_len, rows):
     half tile of 32 keys that is full, ragged or masked as a whole, query rows that fill the last block or leave one
     active row (8 query rows) in it."""
     shape = D.AttnUpdateShape(batch=12, n_q_heads=128, n_kv_heads=16, seq_len=seq_len, head_dim=128, dtype=BF16)
-    _attn_case(shape, rows, 54)
+    _attn_case(shape, rows, 54, kernel="wide")
 
 
-@pytest.mark.parametrize("seq_len", [768, 769, 900])
+@pytest.mark.parametrize("seq_len", [768, 769, 832, 833, 900])
 def test_attention_one_query_block_over_long_sequences(seq_len):
-    """One block of query rows per (sequence, kv head) and at least 12 key tiles: the kernel with two tiles on their way,
-    both exits of its two-tile loop; sequences without active rows and with a full block."""
+    """One block of query rows per (sequence, kv head) and at least 12 key tiles: the kernels that share K/V tiles between 8
+    wavefronts (fewer than 512 pairs, two tiles on their way) and 4 (from 512 on). Full and ragged last tiles, 12 to 15
+    tiles: both exits of the two-tile loop; sequences without active rows, with a full block, and, in the grouped form,
+    with query rows of one active row in several heads."""
     shape = D.AttnUpdateShape(batch=4, n_q_heads=64, n_kv_heads=64, seq_len=seq_len, head_dim=128, dtype=BF16)
-    _attn_case(shape, None, 55, ragged=[100, 0, 128, 5])
+    _attn_case(shape, None, 55, ragged=[100, 0, 128, 5], kernel="shared8")
+    shape = D.AttnUpdateShape(batch=16, n_q_heads=32, n_kv_heads=32, seq_len=seq_len, head_dim=128, dtype=BF16)
+    _attn_case(shape, None, 57, ragged=[100, 0, 128, 5] + [65, 127, 1, 33] * 3, kernel="shared4")
+    shape = D.AttnUpdateShape(batch=32, n_q_heads=64, n_kv_heads=16, seq_len=seq_len, head_dim=128, dtype=BF16)
+    _attn_case(shape, None, 58, ragged=[17, 0, 32, 5] * 8, kernel="shared4")
 
 
 @pytest.mark.parametrize("dh", [128, 64])
@@ -275,15 +283,18 @@ def test_attention_many_small_items(dh):
 def test_attention_peaked_and_flat_softmax(q_scale):
     """Scores with a standard deviation of 16 (after the 1/sqrt(d_h)): almost one-hot probabilities, running maxima
     that keep rising over the key tiles and rescale the output; and all-zero queries: every key weighs the same, the
-    output is the mean of V. Through the key-split, both shared-tile and the generic kernels."""
-    _attn_case(D.AttnUpdateShape(batch=2, n_q_heads=4, n_kv_heads=2, seq_len=1031, head_dim=128, dtype=BF16),
-               None, 46, ragged=[3, 40], q_scale=q_scale)
-    _attn_case(D.AttnUpdateShape(batch=4, n_q_heads=128, n_kv_heads=16, seq_len=300, head_dim=128, dtype=BF16),
-               79, 47, q_scale=q_scale)
-    _attn_case(D.AttnUpdateShape(batch=16, n_q_heads=128, n_kv_heads=16, seq_len=200, head_dim=128, dtype=BF16),
-               66, 48, q_scale=q_scale)
-    _attn_case(D.AttnUpdateShape(batch=2, n_q_heads=4, n_kv_heads=4, seq_len=70, head_dim=32, dtype=FP32),
-               None, 49, ragged=[9, 33], q_scale=q_scale)
+    output is the mean of V. Through every kernel: key-split with 8 and 4 wavefronts, wide query blocks, both forms of the
+    shared tiles, generic."""
+    for shape, n, seed, ragged, kernel in [
+            (D.AttnUpdateShape(batch=2, n_q_heads=4, n_kv_heads=2, seq_len=1031, head_dim=128, dtype=BF16), None, 46, [3, 40], "ksplit2x8"),
+            (D.AttnUpdateShape(batch=20, n_q_heads=16, n_kv_heads=16, seq_len=150, head_dim=128, dtype=BF16), 40, 50, None, "ksplit2x4"),
+            (D.AttnUpdateShape(batch=4, n_q_heads=128, n_kv_heads=16, seq_len=300, head_dim=128, dtype=BF16), 79, 47, None, "wide"),
+            (D.AttnUpdateShape(batch=16, n_q_heads=128, n_kv_heads=16, seq_len=200, head_dim=128, dtype=BF16), 66, 48, None, "wide"),
+            (D.AttnUpdateShape(batch=4, n_q_heads=64, n_kv_heads=64, seq_len=833, head_dim=128, dtype=BF16), None, 59, [100, 0, 128, 5], "shared8"),
+            (D.AttnUpdateShape(batch=16, n_q_heads=32, n_kv_heads=32, seq_len=833, head_dim=128, dtype=BF16), None, 60,
+             [128, 0, 70, 5] + [65, 127, 1, 33] * 3, "shared4"),
+            (D.AttnUpdateShape(batch=2, n_q_heads=4, n_kv_heads=4, seq_len=70, head_dim=32, dtype=FP32), None, 49, [9, 33], "generic")]:
+        _attn_case(shape, n, seed, ragged=ragged, q_scale=q_scale, kernel=kernel)
 
 
 def test_attention_generic_paths():

@@ -1,7 +1,10 @@
 """The rules by which projection and attention calls choose their kernels (host code)."""
 import pytest
 
-from plans import EIGHT_WAVEFRONTS, STREAM_W, gemm_plan
+import dkv_inputs as D
+from dkv_inputs.configs import BF16
+
+from plans import EIGHT_WAVEFRONTS, STREAM_W, attn_plan, gemm_plan
 
 
 @pytest.mark.parametrize("m,n,k", [(2049, 512, 4096), (4096, 512, 4096), (2304, 3584, 18944), (3072, 1024, 8192), (5000, 1024, 4096)])
@@ -29,3 +32,15 @@ def test_the_streaming_hint_is_planned_only_for_tiles_that_follow_it():
                     assert p.tile not in EIGHT_WAVEFRONTS, (m, n, k, p.tile)
                     assert p.grid(m, n)[0] == 1
     assert asked > 500
+
+
+def test_every_attention_kernel_is_planned_where_its_measurements_say():
+    """Both sides of each line of the dispatch (bf16, head_dim 128)."""
+    def kernel(batch, q_heads, kv_heads, seq_len, rows):
+        return attn_plan(D.AttnUpdateShape(batch, q_heads, kv_heads, seq_len, 128, dtype=BF16), rows).kernel
+
+    assert kernel(8, 32, 32, 1024, 64) == "ksplit2x4" and kernel(8, 32, 32, 1024, 65) == "shared8"          # four query tiles
+    assert kernel(6, 32, 32, 768, 128) == "shared8" and kernel(5, 32, 32, 768, 128).startswith("ksplit")      # 192 blocks
+    assert kernel(8, 32, 32, 767, 128) == "wide" and kernel(8, 32, 32, 768, 129) == "wide"                    # long, one block
+    assert kernel(15, 32, 32, 768, 128) == "shared8" and kernel(16, 32, 32, 768, 128) == "shared4"            # 512 pairs
+    assert kernel(16, 28, 4, 768, 129) == "wide" and kernel(8, 32, 32, 1024, 512) == "wide"
