@@ -45,3 +45,26 @@ def attn_plan(shape, max_rows_per_seq):
     f = binding.lib._Z13dkv_attn_planiiiiiii
     f.restype, f.argtypes = AttnPlan, [C.c_int] * 7
     return f(shape.dtype, shape.batch, shape.n_q_heads, shape.n_kv_heads, shape.seq_len, shape.head_dim, max_rows_per_seq)
+
+
+class HeadEpilogue(C.Structure):
+    _fields_ = [("kind", C.c_int), ("out", C.c_void_p), ("head_part", C.c_void_p), ("head_tiles", C.c_int), ("mask_id", C.c_int),
+                ("status", C.c_void_p)]
+
+
+def launch_head(x, w, tile, mask_id, status, rows=None, logits=None):
+    """The vocabulary projection with the softmax statistics in its epilogue, on a given tile kernel (K in one slice).
+    Returns the records [m][column tiles][4] as int32 (max and sum are float bits, then the arg max)."""
+    import torch
+    from paper_2505_15781_amd import binding as b
+    m, k = x.shape
+    n = w.shape[0]
+    bn = int(tile.split("x")[1])
+    tiles = -(-n // bn)
+    part = torch.full((m, tiles, 4), 0x7fc00123, dtype=torch.int32, device=x.device)
+    ep = HeadEpilogue(2, b._ptr(logits), part.data_ptr(), tiles, mask_id, status.data_ptr())
+    f = b.lib._Z20dkv_launch_gemm_headPKvS0_iPKiii8GemmPlanRK12GemmEpilogueP12ihipStream_t
+    f.restype = C.c_int
+    f.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_int, GemmPlan, C.POINTER(HeadEpilogue), C.c_void_p]
+    b._check(f(x.data_ptr(), w.data_ptr(), m, b._ptr(rows), n, k, GemmPlan(TILES.index(tile), 1, 0, 0), C.byref(ep), b._stream()))
+    return part

@@ -8,7 +8,7 @@ from dkv_inputs.configs import BF16, FP32
 from oracle.attn_update import attn_update as oracle_attn_update
 from helpers import rel_err
 from gpu_parity import check_close, tolerances
-from plans import attn_plan
+from plans import attn_plan, launch_head
 
 pytestmark = pytest.mark.gpu
 
@@ -128,6 +128,57 @@ def test_eight_wavefront_tiles_at_short_k_and_tile_edges(kind, k_tiles, m, n):
     w = D.normal_f32(13, 2, (n, k), std=0.02, bf16=True)
     y = P.gemm(_dev(x, BF16), _dev(w, BF16), BF16, kind=kind, split_k=1).cpu().numpy()
     check_close(y, x.astype(np.float64) @ w.astype(np.float64).T, 1e-5, f"{kind} {m}x{n}x{k}")
+
+
+@pytest.mark.parametrize("tile", ["dma_256x256", "dma_256x192", "dma_192x256", "dma_128x192"])
+@pytest.mark.parametrize("rows_off,cols_off", [(-1, -1), (1, 1), (0, 0), (-60, 2), (1, 3)])
+def test_vocabulary_statistics_of_the_tile_kernels(tile, rows_off, cols_off):
+    """Per row and column tile: maximum, sum of exp(x - max), lowest arg max, MASK and columns past the end excluded. Rows and
+    columns just below, at and above one tile (and two tiles of columns), widths of every remainder by 4; planted: equal
+    maxima in two lanes, two wavefronts and two tiles, MASK as the largest logit, a NaN row, a row past the device's count.
+    Maximum and arg max are those of the kernel's own fp32 logits, exactly. The sum adds at most 256 exponentials of |x - max|
+    < 64: exp2 of a product rounded to 2^-24 of at most 93 has an error below 93 ln 2 2^-24 = 4e-6, the additions less."""
+    import paper_2505_15781_amd as P
+    bm, bn = (int(v) for v in tile.split("_")[1].split("x"))
+    m, n, k = bm + rows_off, 2 * bn + cols_off, 192
+    x, w = D.normal_f32(16, 1, (m, k), std=0.25, bf16=True), D.normal_f32(16, 2, (n, k), std=0.25, bf16=True)
+    mask_id = 37
+    ties = {3: (5, 6), 7: (17, 90), 20: (2, bn - 1), 33: (bn - 2, bn + 8), 40: (100, 100 + 4)}       # row: equal columns
+    for r, (lo, hi) in ties.items():
+        w[hi] = w[lo]
+        x[r] = 4 * w[lo]
+    x[11] = 4 * w[mask_id]
+    x[50] = np.nan
+    dead = m - 1                                     # not counted by the device: neither read nor written
+    x[dead] = np.nan
+    xd, wd = _dev(x, BF16), _dev(w, BF16)
+    count = torch.tensor([m - 1], dtype=torch.int32, device="cuda")
+    logits = torch.zeros((m, n), dtype=torch.float32, device="cuda")
+    status = torch.zeros(2, dtype=torch.int32, device="cuda")
+    got = launch_head(xd, wd, tile, mask_id, status[:1], count, logits)
+    again = launch_head(xd, wd, tile, mask_id, status[:1], count)              # logits not written
+    xd[50] = 0
+    launch_head(xd, wd, tile, mask_id, status[1:], count)
+    assert status.tolist() == [1, 0]
+    live = [r for r in range(m - 1) if r != 50]
+    assert torch.equal(got[live], again[live])
+    lg, got = logits.cpu().numpy(), got.cpu()
+    ref = x[live].astype(np.float64) @ w.astype(np.float64).T
+    check_close(lg[live], ref, 1e-5, f"{tile} logits {m}x{n}")
+    assert (got[dead] == 0x7fc00123).all() and not lg[dead].any()
+    mx, sm, ix = got[..., 0].contiguous().view(torch.float32).numpy(), got[..., 1].contiguous().view(torch.float32).numpy(), got[..., 2].numpy()
+    for t in range(got.shape[1]):
+        cols = np.arange(t * bn, min(n, (t + 1) * bn))
+        cols = cols[cols != mask_id]
+        part = lg[np.ix_(live, cols)]
+        assert np.array_equal(mx[live, t], part.max(axis=1))
+        assert np.array_equal(ix[live, t], cols[part.argmax(axis=1)])
+        want = np.exp(part.astype(np.float64) - part.max(axis=1, keepdims=True)).sum(axis=1)
+        assert np.max(np.abs(sm[live, t] - want) / want) <= 1e-5
+    for r, (lo, hi) in ties.items():
+        if r in live:
+            assert lg[r, lo] == lg[r, hi] == lg[r].max() and ix[r, 0] == lo
+    assert lg[11].argmax() == mask_id
 
 
 @pytest.mark.parametrize("m,n,k", [(1, 2, 4), (16, 16, 64), (17, 30, 60), (64, 130, 68), (65, 16, 1028), (128, 4096, 64),
