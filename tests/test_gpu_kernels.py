@@ -8,7 +8,7 @@ from dkv_inputs.configs import BF16, FP32
 from oracle.attn_update import attn_update as oracle_attn_update
 from helpers import rel_err
 from gpu_parity import check_close, tolerances
-from plans import attn_plan, launch_head
+from plans import STAGGER, XCD_GROUP, attn_plan, gemm_plan, launch_head
 
 pytestmark = pytest.mark.gpu
 
@@ -42,14 +42,24 @@ def test_projection_planned_launch_on_a_weight_matrix_that_is_streamed(m):
     check_close(y, x.astype(np.float64) @ w.astype(np.float64).T, 1e-5, f"gemm {m}x{n}x{k}")
 
 
-@pytest.mark.parametrize("m,n,k", [(150, 24576, 4096), (192, 12288, 4096), (320, 12288, 2048), (384, 24576, 1024), (513, 3584, 4096),
-                                   (600, 45000, 2048), (1500, 4096, 4096), (2048, 4608, 3584), (2049, 4608, 3584),
-                                   (2049, 512, 4096), (2304, 3584, 18944), (3072, 1024, 8192)])
-def test_projection_planned_launch_from_150_to_3072_rows(m, n, k):
-    """Row counts at which the planner takes 192-row tiles, slices K at hundreds to thousands of rows, and
-    staggers the K start over two or three rows of tiles and several rounds of workgroups. fp32 sums of k products of
+@pytest.mark.parametrize("m,n,k,rule", [
+    (150, 24576, 4096, "sliced"), (192, 12288, 4096, "sliced"), (320, 12288, 2048, ""), (384, 24576, 1024, "192 rows"),
+    (513, 3584, 4096, "sliced, 192 rows"), (600, 45000, 2048, "grouped, 192 rows"), (1500, 4096, 4096, "sliced, grouped"),
+    (2048, 4608, 3584, "grouped"), (2049, 4608, 3584, "grouped"), (2049, 512, 4096, "sliced"), (2304, 3584, 18944, "sliced, grouped"),
+    (3072, 1024, 8192, "sliced, grouped"), (384, 70000, 2048, "staggered"), (513, 50000, 2048, "staggered, 192 rows")])
+def test_projection_planned_launch_from_150_to_3072_rows(m, n, k, rule):
+    """Row counts at which the planner takes 192-row tiles, slices K at hundreds to thousands of rows, groups the tiles by XCD,
+    and staggers the K start over two or three rows of tiles and several rounds of workgroups; `rule`: what the plan has to
+    be for the case to be worth running. fp32 sums of k products of
     N(0, 1) and N(0, 0.02^2): rounding stays below 1e-6 of the largest value, the bar of the other projections is 1e-5."""
     import paper_2505_15781_amd as P
+    p = gemm_plan(m, n, k)
+    rows, workgroups = p.grid(m, n)
+    assert (p.split_k > 1) == ("sliced" in rule)
+    assert (rows > 1 and p.flags & STAGGER != 0) == ("staggered" in rule)
+    assert (p.flags & XCD_GROUP != 0) == ("grouped" in rule)
+    assert "192 rows" not in rule or p.tile == "dma_192x256"
+    assert "staggered" not in rule or workgroups > 512
     g = torch.Generator(device="cuda").manual_seed(m + n)
     x = torch.randn((m, k), generator=g, device="cuda").to(torch.bfloat16)
     w = (torch.randn((n, k), generator=g, device="cuda") * 0.02).to(torch.bfloat16)
