@@ -110,3 +110,13 @@ def test_the_binding_imports_without_torch_internals():
             "assert b._stream() == 77\n")
     res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr
+
+
+def test_traffic_ratios_of_the_bench_are_those_of_the_profile():
+    """bench.py calls them measured: every entry has to stand in the tracked table, under the same kernel name."""
+    text = open(os.path.join(ROOT, "profiles", "projection_cfg2_hbm_traffic_pmc.txt")).read()
+    table = {f"gemm_dma<*,{m.group(1).replace(' ', '')}>": float(m.group(2))
+             for m in re.finditer(r"^#\s+gemm_dma<0, ([\d, ]+)>.* MB\s+([\d.]+)$", text, flags=re.M)}
+    src = open(os.path.join(ROOT, "bench.py")).read()
+    ratios = eval(re.search(r"^MEASURED_TRAFFIC_RATIO = (\{.*?\})", src, flags=re.S | re.M).group(1))
+    assert len(table) == 8 and ratios == table
