@@ -6,7 +6,8 @@
 // multiplies its 32 query rows against the shared tile, so a K or V fragment read from LDS feeds 32 queries.
 //
 // Why: with 16-row tiles the loop was a chain product -> softmax -> product in every wavefront, and the two wavefronts of a
-// SIMD did the same part at the same time: matrix pipes busy 35 %, vector issue 49 %, their sum and little overlap. Here
+// SIMD did the same part at the same time: matrix pipes busy 33 %, vector issue 48 %, their sum and little overlap (here 45
+// and 53 %). Here
 // a wavefront works on half tiles of 32 keys in a skewed order: one stretch holds the scores of half tile j + 1, the output
 // products of half tile j - 1 and the exponentials of half tile j, which do not depend on each other, and the schedule
 // deals them out one MFMA, one or two LDS reads, three vector instructions at a time. The running sum is a product with a
@@ -14,9 +15,10 @@
 // workgroups share a compute unit and cover each other's barrier (one per tile).
 // Per call, with the scatter launch, before and after (same card): 8 sequences x 32 heads x 1024 keys, 512 rows 127.4 ->
 // 119.0 us; 4 x 32 heads x 1536 keys, 1536 rows 231 -> 218 us; 16 x 4 kv heads of 7, 768 keys, up to 129 rows 41.5 -> 35.3
-// us. What bounds it: vector instructions, a quarter of them the rescaling of the output, which some query of the 32
-// needs at most half tiles. A reference that lags the maximum by up to 2^8 saves those (another 8-14 %), but then the
-// largest probability is no longer exactly 1 and the error against float64 grows by up to 10 %: not done.
+// us. What bounds it: vector instructions, 278 per wavefront and tile next to 37 MFMAs, 105 of them the rescaling of the
+// output, which some query of the 32 needs at 26 of 32 half tiles (independent scores). A reference that lags the maximum
+// by up to 2^8 saves those (another 8-14 %), but then the largest probability is no longer exactly 1 and the error against
+// float64 grows by up to 10 %: not done.
 #pragma once
 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;

@@ -10,7 +10,7 @@
 // holding registers. The LDS layout XOR-swizzles the 16-byte chunks of a 128-byte row with (row >> 1)
 // so a fragment read of 16 consecutive rows touches every bank once; the swizzle is applied by choosing
 // which global chunk each lane fetches. Fragment reads run one K sub-step ahead of the MFMAs, across tile
-// boundaries. Measured on MI355X a compute unit sustains about 60 GB/s of such fills whatever the depth,
+// boundaries. Measured on MI355X a compute unit sustains 50-60 GB/s of such fills whatever the depth,
 // so the tile shapes below are chosen to keep the bytes each workgroup pulls (W tile + A tile) small
 // relative to its MFMA work, and K is split across workgroups only as far as needed to fill 256 CUs.
 // Two launch options, both measured: `stagger` starts each workgroup's K loop at a different tile (unsplit
@@ -267,8 +267,12 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, bool one_slice) {
     // are read once (one row of tiles) are streamed with the non-temporal hint by the 4-wavefront tiles (in the 8-wavefront
     // loop, which has no such loads, the hint measured 0-13 % slower with K slices and between 5 % faster and 4 % slower
     // without); the XCD-grouped order
-    // pays once there are enough tile rows to form groups, for every tile on wide products (10-17 % less time from 24576
-    // columns up), elsewhere for the largest tiles.
+    // pays once there are enough tile rows to form groups, for the largest tiles everywhere, for every tile on wide
+    // products. With it against without, 400 to 2048 rows: 128x128 1.0-1.08 of the time at 8192 columns, 0.95-1.03 at 12288
+    // and 16384, 0.89-0.98 at 20480 and 24576, 0.83-0.91 at 32768; 128x256 0.96-1.03 from 12288 to 20480, 0.94-1.0 at 24576,
+    // 0.92-0.99 at 32768; 128x192 0.85-1.0 except at 12288 (1.0-1.06) and 24576 (0.97-1.04). Between 12288 and 24576 columns
+    // the tiles planned with four rows and more are 128x256 and the 8-wavefront ones, so the line costs nothing there; below
+    // 12288 it leaves out 128x192 tiles, which would gain.
     const int tiles_m = ceil_div(m_upper, kKinds[p.kind].bm);
     const long wgs = (long)tiles_m * ceil_div(n, kKinds[p.kind].bn) * p.split_k;
     if (tiles_m == 1 || (tiles_m <= 3 && p.split_k == 1 && wgs > 512 && k % 2048 == 0)) p.flags |= GEMM_FLAG_STAGGER;

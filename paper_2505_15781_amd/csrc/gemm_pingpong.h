@@ -2,11 +2,11 @@
 // fetching operands and multiplying (included by gemm_kernel.h inside its namespace).
 //
 // Why: with thousands of rows the projections are bound by the matrix pipes under the card's power limit, and by how
-// many cycles those pipes wait. Measured on registers only, with random operands: MFMA 32x32x16 runs at 1.73-1.83
-// PFLOP/s (the clock falls to 1.65 GHz), 16x16x32 at 2.05 PFLOP/s, but only with two wavefronts per SIMD (one wavefront
-// issues a 16-cycle MFMA every 25 cycles). So the tile is multiplied with 16x16x32 by 8 wavefronts, two per SIMD, one of
-// each group. Fragment reads of all 8 wavefronts move 192 KB through LDS per 256x256x64 step, 75 % of the port's
-// 128 B/cycle: they have to be spread evenly under the MFMAs, which the alternation does.
+// many cycles those pipes wait. Measured on registers only, with random operands: MFMA 32x32x16 runs at 1.88 PFLOP/s,
+// 16x16x32 at 2.12-2.14 (2.41-2.48 with operands of zeros). So the tile is multiplied with 16x16x32, by 8 wavefronts, two
+// per SIMD, one of each group, of which one fetches while the other multiplies. Fragment reads of all 8 wavefronts move
+// 192 KB through LDS per 256x256x64 step, 75 % of the port's 128 B/cycle: they have to be spread evenly under the MFMAs,
+// which the alternation does.
 //
 // Schedule: a wavefront's 32 MT x 32 NT part of the tile is worked on as 2 x 2 quarters (row half A0 / A1, column half
 // B0 / B1), one quarter (2 MT NT MFMAs) per phase. A phase is a fetch slot (LDS reads of the fragments it needs, the
@@ -19,10 +19,12 @@
 //   multiplies   A0 B0        A0 B1        A1 B1        A1 B0
 // A region is refilled as soon as both groups have read it (one barrier later), so with two LDS stages a load has 6
 // to 7 phases, 3000 cycles and more, to land: longer than a miss under load, which one tile of lookahead (2048 cycles)
-// is not. A K step of 256x256x64 takes 2180 cycles of the 2048 its MFMAs need. Against the 4-wavefront loop that these
-// tiles had before (one wavefront per SIMD, 32x32x16, one K tile ahead), same box:
+// is not. At 6144 rows a K step of 256x256x64 takes 2460 cycles of which its MFMAs need 2048, 192x256x64 2240-2270 and
+// 256x192x64 2450-2470 of 1536 each; over whole launches the matrix pipes are busy 60-69 % of the cycles. Against the
+// 4-wavefront loop that these tiles had before (one wavefront per SIMD, 32x32x16, one K tile ahead), same box:
 //   6144 x 24576 x 4096 with SwiGLU   1112 -> 872 us (1.42 PFLOP/s)      6144 x 12288 x 4096   566 -> 489 us
 //   6144 x 4096 x 12288 (192x256)      592 -> 475 us                     4096 x 37888 x 3584   1078 -> 825 us
+// (on other cards 872-939, 489-564, 472-484 and 800-860 us)
 #pragma once
 
 // all but the newest VM vector memory operations of this wavefront are done, and all its LDS operations
