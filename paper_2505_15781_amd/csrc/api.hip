@@ -87,7 +87,7 @@ Layout make_layout(const dkv_model_desc &m, const dkv_run_desc &r) {
     y.head_fused = true;
     y.head_records = 1;
     for (int c = 1; c <= y.cand_cap; ++c) {
-        GemmPlan p = dkv_gemm_plan(m.dtype, c, m.vocab, m.d_model, true);
+        GemmPlan p = dkv_gemm_plan(m.dtype, c, m.vocab, m.d_model, SLICES_NONE);
         // the epilogue needs the tile kernel with one K slice for every candidate count of the run
         if (!dkv_gemm_can_fuse_head(m.dtype, m.d_model, p)) y.head_fused = false;
         else if ((size_t)c * dkv_gemm_tiles_n(p, m.vocab) > y.head_records) y.head_records = (size_t)c * dkv_gemm_tiles_n(p, m.vocab);
@@ -438,7 +438,7 @@ extern "C" int dkv_denoise_step(dkv_ctx *c, int32_t step, const int32_t *forced_
     c->last_step_captured = c->capture != nullptr;
     // vocabulary head on the candidate rows only (same result as projecting every active row)
     if ((rc = dkv_launch_gather_rows(dt, s, cands, c->a, c->cand_row, c->counts, c->a_c, d))) return rc;
-    GemmPlan hp = dkv_gemm_plan(dt, cands, m.vocab, d, true);
+    GemmPlan hp = dkv_gemm_plan(dt, cands, m.vocab, d, SLICES_NONE);
     if (c->lay.head_fused) {
         // softmax maximum, sum and arg max per column tile leave the projection's epilogue and a small kernel merges
         // the tiles of a row: the [candidates, vocab] logits are never written (unless the caller asks for them)
@@ -703,7 +703,7 @@ extern "C" int dkv_concat_reorder(const void *k_cached, const void *v_cached, co
 
 extern "C" size_t dkv_gemm_workspace_bytes(int32_t m, int32_t n, int32_t k, int32_t dtype) {
     if (m < 1 || n < 1 || k < 1) return 0;
-    GemmPlan p = dkv_gemm_plan(dtype, m, n, k);
+    GemmPlan p = dkv_gemm_plan(dtype, m, n, k, SLICES_LAUNCH);
     return p.split_k > 1 ? (size_t)p.split_k * m * n * 4 : 0;
 }
 
@@ -751,7 +751,7 @@ extern "C" int dkv_gemm_with(const void *x, const void *w, void *yv, int32_t m, 
 extern "C" int dkv_gemm(const void *x, const void *w, float *y, int32_t m, int32_t n, int32_t k, int32_t dtype,
                         void *workspace, size_t workspace_bytes, void *stream) {
     if (m < 1 || n < 1 || k < 1) { dkv_set_error("bad argument"); return DKV_E_INVALID_ARG; }
-    GemmPlan p = dkv_gemm_plan(dtype, m, n, k);
+    GemmPlan p = dkv_gemm_plan(dtype, m, n, k, SLICES_LAUNCH);
     const int options = ((p.flags & GEMM_FLAG_STAGGER) ? DKV_GEMM_OPT_STAGGER : 0) |
                         ((p.flags & GEMM_FLAG_XCD_GROUP) ? DKV_GEMM_OPT_XCD_GROUP : 0) |
                         ((p.flags & GEMM_FLAG_STREAM_W) ? DKV_GEMM_OPT_STREAM_W : 0);

@@ -21,11 +21,15 @@ class GemmPlan(C.Structure):
         return rows, rows * -(-n // bn) * self.split_k
 
 
-def gemm_plan(m, n, k, one_slice=False, dtype=0):
+CONSUMER, ONE_SLICE, OWN_LAUNCH = 0, 1, 2          # who adds the K slices up
+
+
+def gemm_plan(m, n, k, slices_go_to=CONSUMER, dtype=0):
+    """The plan of a projection inside a step; OWN_LAUNCH: of dkv_gemm."""
     from paper_2505_15781_amd import binding
-    f = binding.lib._Z13dkv_gemm_planiiiib
-    f.restype, f.argtypes = GemmPlan, [C.c_int] * 4 + [C.c_bool]
-    return f(dtype, m, n, k, one_slice)
+    f = binding.lib._Z13dkv_gemm_planiiiii
+    f.restype, f.argtypes = GemmPlan, [C.c_int] * 5
+    return f(dtype, m, n, k, slices_go_to)
 
 
 class AttnPlan(C.Structure):

@@ -8,7 +8,7 @@ from dkv_inputs.configs import BF16, FP32
 from oracle.attn_update import attn_update as oracle_attn_update
 from helpers import rel_err
 from gpu_parity import check_close, tolerances
-from plans import STAGGER, XCD_GROUP, attn_plan, gemm_plan, launch_head
+from plans import OWN_LAUNCH, STAGGER, XCD_GROUP, attn_plan, gemm_plan, launch_head
 
 pytestmark = pytest.mark.gpu
 
@@ -43,8 +43,8 @@ def test_projection_planned_launch_on_a_weight_matrix_that_is_streamed(m):
 
 
 @pytest.mark.parametrize("m,n,k,rule", [
-    (150, 24576, 4096, "sliced"), (192, 12288, 4096, "sliced"), (320, 12288, 2048, ""), (384, 24576, 1024, "192 rows"),
-    (513, 3584, 4096, "sliced, 192 rows"), (600, 45000, 2048, "grouped, 192 rows"), (1500, 4096, 4096, "sliced, grouped"),
+    (150, 24576, 4096, "sliced"), (192, 12288, 4096, ""), (320, 12288, 2048, ""), (384, 24576, 1024, "192 rows"),
+    (513, 3584, 4096, "sliced, 192 rows"), (600, 45000, 2048, "grouped, 192 rows"), (1500, 4096, 4096, "grouped"),
     (2048, 4608, 3584, "grouped"), (2049, 4608, 3584, "grouped"), (2049, 512, 4096, "sliced"), (2304, 3584, 18944, "sliced, grouped"),
     (3072, 1024, 8192, "sliced, grouped"), (384, 70000, 2048, "staggered"), (513, 50000, 2048, "staggered, 192 rows")])
 def test_projection_planned_launch_from_150_to_3072_rows(m, n, k, rule):
@@ -53,7 +53,7 @@ def test_projection_planned_launch_from_150_to_3072_rows(m, n, k, rule):
     be for the case to be worth running. fp32 sums of k products of
     N(0, 1) and N(0, 0.02^2): rounding stays below 1e-6 of the largest value, the bar of the other projections is 1e-5."""
     import paper_2505_15781_amd as P
-    p = gemm_plan(m, n, k)
+    p = gemm_plan(m, n, k, OWN_LAUNCH)
     rows, workgroups = p.grid(m, n)
     assert (p.split_k > 1) == ("sliced" in rule)
     assert (rows > 1 and p.flags & STAGGER != 0) == ("staggered" in rule)
