@@ -29,6 +29,30 @@ template <int V> struct StageC { static constexpr int value = V; };
 // 4 different groups (transposing reads: 32 bytes of 4 rows each).
 __device__ __forceinline__ int wide_swizzle(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
 
+// Work item of this workgroup in launches of 257 to 511 workgroups, where some compute units get two: as attn_item, but the
+// blocks that hold query rows come first. A workgroup without rows leaves at once, and where it stood between others the
+// hardware put two busy workgroups on one unit and left others empty (11 sequences x 8 kv heads of 3, 10 to 115 rows: 1024
+// keys 35.9 -> 27.3 us, 4096 keys 113 -> 82; with no such sequences level to 1 % slower). With at most 256 workgroups every one
+// has a unit, with 512 every unit has two. A lane per (sequence, kv head) pair of the XCD counts its blocks; a prefix sum
+// over the lanes finds the pair of this workgroup.
+__device__ __forceinline__ bool wide_item_compact(const int *row_off, int pairs, int Hkv, int G, int q_blocks, int &pair, int &qb) {
+    const int lane = threadIdx.x & 63, slot = blockIdx.x >> 3, p = lane * 8 + (blockIdx.x & 7), b = min(p, pairs - 1) / Hkv;
+    const int n = p < pairs ? min(((row_off[b + 1] - row_off[b]) * G + 127) / 128, q_blocks) : 0;
+    int upto = n;                                  // inclusive prefix sum: within rows of 16 lanes, then across the rows
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, true);
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, true);
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, true);
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, true);
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xa, 0xf, false);
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x143, 0xc, 0xf, false);
+    const unsigned long long behind = __builtin_amdgcn_ballot_w64(upto > slot);
+    if (!behind) return false;
+    const int at = __builtin_ctzll(behind);
+    pair = at * 8 + (blockIdx.x & 7);
+    qb = slot - (__builtin_amdgcn_readlane(upto, at) - __builtin_amdgcn_readlane(n, at));
+    return true;
+}
+
 constexpr int WIDE_LDS_BYTES = 4 * 64 * 256;         // K0 K1 V0 V1
 
 __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_wide(
@@ -44,7 +68,11 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int qi = lane & 31, g = lane >> 5, l16 = lane & 15, l4 = lane >> 4;
     const uint32_t lds_base = (uint32_t)(size_t)(lds_ptr_t)smem_raw;
     int pair, qb;
-    if (!attn_item(blockIdx.x, batch * Hkv, q_blocks, pair, qb)) return;
+    if (gridDim.x > 256 && gridDim.x < 512) {          // at most 64 pairs on an XCD
+        if (!wide_item_compact(row_off, batch * Hkv, Hkv, G, q_blocks, pair, qb)) return;
+    } else if (!attn_item(blockIdx.x, batch * Hkv, q_blocks, pair, qb)) {
+        return;
+    }
     const int kvh = pair % Hkv, b = pair / Hkv;
     const int r0 = row_off[b], nq = (row_off[b + 1] - r0) * G, mb0 = qb * NW * 32;
     if (mb0 >= nq) return;                       // uniform for the workgroup

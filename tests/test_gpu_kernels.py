@@ -309,6 +309,20 @@ def test_attention_wide_blocks_with_ragged_sequences():
     _attn_case(shape, None, 53, ragged=[79, 0, 300, 5], kernel="wide")
 
 
+@pytest.mark.parametrize("batch,heads,kv_heads,seq_len,ragged,grid", [
+    (7, 24, 6, 170, [0, 33, 170, 0, 64, 1, 0], 288), (7, 35, 5, 200, [128, 0, 0, 7, 200, 0, 19], 440),
+    (15, 32, 32, 130, [0, 128, 3, 0, 127, 65, 0, 1] + [128, 0, 2, 64, 0, 5, 90], 480), (6, 32, 32, 260, [260, 0, 129, 128, 1, 257], 0)])
+def test_attention_wide_blocks_with_rows_come_first(batch, heads, kv_heads, seq_len, ragged, grid):
+    """Launches of 257 to 511 workgroups hand out the blocks that hold query rows before the others, counted per XCD over its
+    (sequence, kv head) pairs: pairs that are no multiple of 8 (42 and 35), sequences without rows first, in between and
+    last, exactly full blocks, 60 pairs on an XCD; and a launch beyond (576), which keeps the plain order."""
+    shape = D.AttnUpdateShape(batch=batch, n_q_heads=heads, n_kv_heads=kv_heads, seq_len=seq_len, head_dim=128, dtype=BF16)
+    p = attn_plan(shape, max(ragged))
+    workgroups = -(-batch * kv_heads // 8) * 8 * p.q_blocks
+    assert workgroups == grid or (grid == 0 and workgroups >= 512)
+    _attn_case(shape, None, 61, ragged=ragged, kernel="wide")
+
+
 @pytest.mark.parametrize("seq_len,rows", [(16, 16), (17, 17), (32, 20), (33, 33), (63, 15), (65, 65), (97, 16), (129, 31), (160, 100)])
 def test_attention_wide_query_blocks_at_tile_edges(seq_len, rows):
     """Blocks of 128 query rows, 32 per wavefront (12 x 16 kv heads of 8 query heads): one to three key tiles of 64, a
