@@ -189,10 +189,11 @@ __global__ __launch_bounds__(256) void attn_merge(const float *__restrict__ part
     }
 }
 
-// Four consecutive elements as floats.
-__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4_el *>(p); }
-__device__ __forceinline__ f32x4 load4(const bf16_t *p) {
-    const u32x2 v = *reinterpret_cast<const bf16x4_el *>(p);
+// Four consecutive elements as they are stored, and as floats.
+__device__ __forceinline__ f32x4 raw4(const float *p) { return *reinterpret_cast<const f32x4_el *>(p); }
+__device__ __forceinline__ u32x2 raw4(const bf16_t *p) { return *reinterpret_cast<const bf16x4_el *>(p); }
+__device__ __forceinline__ f32x4 floats(f32x4 v) { return v; }
+__device__ __forceinline__ f32x4 floats(u32x2 v) {
     return f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
                  __uint_as_float(v.y & 0xffff0000u)};
 }
@@ -207,7 +208,9 @@ __device__ __forceinline__ void store4(bf16_t *p, f32x4 v) {
 // coalesced; a lane keeps one sum per key place that it serves, and only the last step adds those up and reduces over
 // lanes (with a whole output vector per lane that was DH wavefront reductions: 64 rows x 4 heads x 64 keys of 32 floats,
 // 11.1 -> 7 us). The sums run in the order of a butterfly over the 64 key places, as with one output vector per lane, so
-// that candidates of nearly equal confidence keep their order.
+// that candidates of nearly equal confidence keep their order. What bounds it at few rows is a memory latency per batch of
+// loads and chunk: 2 sequences x 4 heads of 64 floats, 23 rows, 1300 keys 135 -> 64 us with whole batches in flight (92 with
+// one output vector per lane), 8 x 16 heads of 128, 37 rows, 2500 keys 3008 -> 924 us (2292).
 template <typename T, int DH>
 __global__ __launch_bounds__(256) void attn_generic(const T *__restrict__ Q, const T *__restrict__ Kc,
                                                     const T *__restrict__ Vc,
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(256) void attn_generic(const T *__restrict__ Q, con
                                                     float scale) {
     constexpr int LPK = DH / 4, KPP = 64 / LPK, NJ = 64 / KPP;      // lanes per key, keys per pass, passes per chunk
     __shared__ float2 state[4][64];                                 // (rescale, probability) of each key place
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long pair = (long)blockIdx.x * 4 + wave;
     const int total_rows = min(row_off[batch], rows_cap);
     if (pair >= (long)total_rows * Hq) return;
@@ -239,14 +242,37 @@ __global__ __launch_bounds__(256) void attn_generic(const T *__restrict__ Q, con
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
+    // fp32 queries come through the scalar cache; bf16 ones, which may start at an odd element, stay in registers
+    constexpr bool Q_REGS = sizeof(T) == 2;
+    f32x4 qr[Q_REGS ? DH / 4 : 1];
+    if constexpr (Q_REGS) {
+#pragma unroll
+        for (int i = 0; i < DH / 4; ++i) qr[i] = floats(raw4(qp + 4 * i));
+    }
+    // The loads of a batch of K pieces, and of V rows, are all issued before the first is used (left to itself, and behind a
+    // branch for the last keys of a sequence, the compiler waited for one or two at a time).
+    constexpr int KB = DH / 4 < 16 ? DH / 4 : 16, VB = DH == 128 ? 8 : NJ;
     for (int k0 = 0; k0 < L; k0 += 64) {
+        const bool whole = k0 + 64 <= L;
+        decltype(raw4(Kb)) vr[VB], kr[KB];
+        auto load_v = [&](int j0) {
+#pragma unroll
+            for (int j = 0; j < VB; ++j) vr[j] = raw4(Vb + (size_t)min(k0 + KPP * (j0 + j) + kk, L - 1) * DH + d);
+        };
         const T *kp = Kb + (size_t)min(k0 + lane, L - 1) * DH;
         float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < DH / 4; ++i) {
-            const f32x4 q = load4(qp + 4 * i), k = load4(kp + 4 * i);
+        for (int i0 = 0; i0 < DH / 4; i0 += KB) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) s = fmaf(q[v], k[v], s);
+            for (int i = 0; i < KB; ++i) kr[i] = raw4(kp + 4 * (i0 + i));
+            if (i0 + KB == DH / 4) load_v(0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < KB; ++i) {
+                const f32x4 q = Q_REGS ? qr[i0 + i] : floats(raw4(qp + 4 * (i0 + i))), k = floats(kr[i]);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) s = fmaf(q[v], k[v], s);
+            }
         }
         s *= scale;
         const float mn = fmaxf(m, s);
@@ -257,24 +283,53 @@ __global__ __launch_bounds__(256) void attn_generic(const T *__restrict__ Q, con
         }
         share(make_float2(a, p));
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int key = k0 + KPP * j + kk;
-            const float2 ap = state[wave][KPP * j + kk];
-            const f32x4 v = load4(Vb + (size_t)min(key, L - 1) * DH + d);
-            if (key < L) {
+        for (int j0 = 0; j0 < NJ; j0 += VB) {
+            if (j0) {
+                load_v(j0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            auto add = [&](int j) {
+                const float2 ap = state[wave][KPP * (j0 + j) + kk];
+                const f32x4 v = floats(vr[j]);
+                f32x4 x;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o[j][i] = fmaf(ap.y, v[i], o[j][i] * ap.x);
+                for (int i = 0; i < 4; ++i) x[i] = fmaf(ap.y, v[i], o[j0 + j][i] * ap.x);
+                return x;
+            };
+            if (whole) {
+#pragma unroll
+                for (int j = 0; j < VB; ++j) o[j0 + j] = add(j);
+            } else {
+#pragma unroll
+                for (int j = 0; j < VB; ++j) {
+                    const f32x4 x = add(j);
+                    const bool use = k0 + KPP * (j0 + j) + kk < L;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[j0 + j][i] = use ? x[i] : o[j0 + j][i];
+                }
             }
         }
     }
     const float Mx = wave_max(m);
     const float w = (m == -INFINITY) ? 0.f : expf(m - Mx);
-    const float inv = 1.f / wave_sum(l * w);
+    const float lt = wave_sum(l * w), lt_other = __shfl_xor(lt, 32, 64);
     share(make_float2(w, 0.f));
+    // The first step of a butterfly over lanes takes one product exactly and the other rounded: of places p and p + 32 the
+    // lower one in the lanes below 32, the upper one in the others; so does that of the sum. The result of dim d comes from
+    // lane d & 63, as it did when every lane held a whole output vector.
+    const bool upper = d & 32;
+    const float inv = 1.f / (upper ? lt_other : lt);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) o[j] *= state[wave][KPP * j + kk].x;
+    for (int j = 0; j < NJ / 2; ++j) {
+        const float wl = state[wave][KPP * j + kk].x, wu = state[wave][KPP * (j + NJ / 2) + kk].x;
 #pragma unroll
-    for (int x = NJ / 2; x > 0; x >>= 1)
+        for (int i = 0; i < 4; ++i) {
+            const float lo = o[j][i], up = o[j + NJ / 2][i];
+            o[j][i] = fmaf(upper ? up : lo, upper ? wu : wl, (upper ? lo : up) * (upper ? wl : wu));
+        }
+    }
+#pragma unroll
+    for (int x = NJ / 4; x > 0; x >>= 1)
 #pragma unroll
         for (int j = 0; j < x; ++j) o[j] += o[j + x];
     f32x4 y = o[0];

@@ -425,6 +425,31 @@ def test_projection_writes_results_at_any_element_boundary(dtype, kind, m, n, k,
     assert torch.equal(y, ys)
 
 
+@pytest.mark.parametrize("dtype,dh,seq_len,bits", [
+    (FP32, 32, 70, "27f06425927224fcafa23fd4605d4719676c91d7"),
+    (FP32, 32, 1300, "b8d71dbcf465e04db1147b46de1d5486de8bc196"),
+    (FP32, 64, 64, "8130a4842fe545111c01d83211251a7cee0988e7"),
+    (FP32, 64, 1300, "104d3c3b317fe1e15631335c5e67f7972f10d35e"),
+    (FP32, 128, 64, "efed2095d0de6a39965b4edbfca5487e638c6c11"),
+    (FP32, 128, 517, "809ec4c9b3fd6be1aec076ee1aa3038aa9d830a4"),
+    (BF16, 32, 200, "b025b4d48950a493e2bcf393f768665cf67e162d")])
+def test_generic_attention_keeps_the_order_of_its_sums(dtype, dh, seq_len, bits):
+    """Two candidates of a step can be equal but for a rounding, so another order of the sums, or another choice of which
+    product is rounded before it is added, would commit the other one: the results are held to the bits that one output
+    vector per lane and a butterfly over the lanes gave (SHA-1 of the output array), over one chunk of 64 keys and many, whole
+    and cut."""
+    import hashlib
+    import paper_2505_15781_amd as P
+    B, Hq, Hkv, A = 2, 4, 2, 31
+    c = D.attn_update_case(D.AttnUpdateShape(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=seq_len, head_dim=dh, dtype=dtype), A, 64)
+    kc, vc, kn, vn, q = (_dev(c[n], dtype) for n in ("k_cache", "v_cache", "k_new", "v_new", "q"))
+    out = torch.zeros_like(q)
+    P.attn_update(kc, vc, q, kn, vn, torch.from_numpy(c["active_idx"]).cuda(), torch.from_numpy(c["active_off"]).cuda(), out, B * A, A,
+                  dtype, None)
+    got = hashlib.sha1(out.view(torch.int16 if dtype == BF16 else torch.int32).cpu().numpy().tobytes()).hexdigest()
+    assert got == bits
+
+
 def test_attention_no_rows_is_a_no_op():
     shape = D.AttnUpdateShape(batch=2, n_q_heads=4, n_kv_heads=2, seq_len=64, head_dim=128, dtype=BF16)
     _attn_case(shape, 0, 51)
