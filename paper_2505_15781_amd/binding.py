@@ -67,7 +67,7 @@ class ProfEntry(C.Structure):
 # (0 fp32 product, 1 fused SwiGLU, 2 vocabulary statistics), which the report does not tell apart
 PROF_KINDS = ("gemm_dma<*,1,1,1,4,4>", "gemm_dma<*,2,1,1,4,4>", "gemm_dma<*,2,2,2,2,3>", "gemm_dma<*,2,4,2,2,3>",
               "gemm_dma<*,4,2,2,4,2>", "gemm_dma<*,1,3,4,1,4>", "gemm_dma<*,2,3,2,2,3>", "gemm_dma<*,2,3,4,2,2>",
-              "gemm_dma<*,3,2,2,4,2>", "gemm_reg",
+              "gemm_dma<*,3,2,2,4,2>", "gemm_stream, gemm_reg",
               "gemm_simt",
               "attention")
 GEMM_KINDS = {"dma_32x128": 0, "dma_64x128": 1, "dma_128x128": 2, "dma_128x256": 3, "dma_256x256": 4,

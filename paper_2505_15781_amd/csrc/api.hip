@@ -197,7 +197,8 @@ int timed_gemm(dkv_ctx *c, const void *A, const void *W, float *out, int m, cons
     const double es = (double)c->es;
     // output bytes: fp32 [M, N], or the fused SwiGLU's [M, N/2] elements
     const double out_bytes = (p.flags & GEMM_FLAG_SWIGLU) ? es * m * (n / 2) : 4.0 * m * n;
-    return timed(c, p.kind, ((double)m * k + (double)n * k) * es + out_bytes,
+    const int slot = dkv_gemm_is_stream(p.kind) ? (int)GEMM_REG_64x128 : p.kind;
+    return timed(c, slot, ((double)m * k + (double)n * k) * es + out_bytes,
                  2.0 * m * n * k,
                  [&] { return dkv_launch_gemm(c->m.dtype, A, W, out, m, m, m_dev, n, k, p, c->stream); });
 }
@@ -717,6 +718,10 @@ extern "C" int dkv_gemm_with(const void *x, const void *w, void *yv, int32_t m, 
         return DKV_E_INVALID_ARG;
     }
     if (dtype != DKV_BF16 && dtype != DKV_FP32) { dkv_set_error("unknown dtype"); return DKV_E_INVALID_ARG; }
+    if (kind >= GEMM_KINDS) {      // kernels without a public number
+        dkv_set_error("unknown projection kernel %d", kind);
+        return DKV_E_UNSUPPORTED;
+    }
     GemmPlan p;
     p.kind = kind;
     p.split_k = split_k < 0 ? 2 : split_k;

@@ -76,7 +76,7 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
 }
 
 // 16 bytes per lane from global memory into LDS at lds_addr + 16 * lane (lds_addr and base wave-uniform): from a pointer of
-// each lane, the same with the non-temporal hint, and from a wave-uniform base with a byte offset of each lane. Issued
+// each lane and from a wave-uniform base with a byte offset of each lane, both also with the non-temporal hint. Issued
 // through inline assembly so that the compiler does not serialise a ring of such loads on its own conservative wait;
 // completion is awaited explicitly with vmcnt. A load to LDS reads M0 too early in the cycle after M0 was written: one
 // wait state is needed in between (the compiler puts it in for its own code, but does not look inside an asm text).
@@ -90,6 +90,10 @@ __device__ __forceinline__ void dma16_at(uint32_t voff, const void *base, uint32
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 
+__device__ __forceinline__ void dma16_at_nt(uint32_t voff, const void *base, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
+}
+
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
@@ -99,6 +103,9 @@ static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 enum { GEMM_DMA_32x128 = 0, GEMM_DMA_64x128, GEMM_DMA_128x128, GEMM_DMA_128x256, GEMM_DMA_256x256,
        GEMM_DMA_128x96, GEMM_DMA_128x192, GEMM_DMA_256x192, GEMM_DMA_192x256, GEMM_REG_64x128, GEMM_SIMT, GEMM_KINDS };
 enum { GEMM_DMA_LAST = GEMM_DMA_192x256 };      // the gemm_dma tile kernels are the kinds 0 .. GEMM_DMA_LAST
+// Kinds that only dkv_gemm_plan hands out, for projections inside a step (dkv_gemm_with takes the numbers of dkv.h, which end
+// before): gemm_stream.h, one row of tiles. A profile counts them with GEMM_REG_64x128, whose K they never have.
+enum { GEMM_STREAM_256x96 = GEMM_KINDS, GEMM_STREAM_256x64, GEMM_STREAM_LAST = GEMM_STREAM_256x64 };
 enum { GEMM_FLAG_STAGGER = 1, GEMM_FLAG_XCD_GROUP = 2, GEMM_FLAG_SWIGLU = 4, GEMM_FLAG_STREAM_W = 8 };
 struct GemmPlan {
     int kind;      // GEMM_* kernel and tile shape
@@ -155,6 +162,7 @@ DKV_DECLARE_DISPATCH(head)
 // Rows >= *m_dev (when m_dev != nullptr) are neither read nor written.
 // With GEMM_FLAG_SWIGLU in plan.flags (gemm_dma kinds, one K slice, W rows interleaved gate_j, up_j): `partial` is
 // instead a bf16 [m][n/2] array that receives silu(gate_j) * up_j, and no fp32 product is written.
+inline bool dkv_gemm_is_stream(int kind) { return kind >= GEMM_STREAM_256x96 && kind <= GEMM_STREAM_LAST; }
 bool dkv_gemm_can_fuse_swiglu(int dtype, int n, int k, const GemmPlan &p);
 int dkv_launch_gemm(int dtype, const void *A, const void *W, float *partial, int m_upper, int m_cap,
                     const int *m_dev, int n, int k, GemmPlan plan, hipStream_t stream);

@@ -262,6 +262,36 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
             }
         }
     }
+    // One row of tiles of 256 rows, inside a step: the kernels of gemm_stream.h, by the same model with a time per K tile and a
+    // fixed part of their own. Fitted to 162 launches with their consumers (129 to 256 rows, 18 layer shapes of 1024 to 37888
+    // columns, cold weights): the choice loses 0.4 % on average and 6 % at worst against the best of either, and gains 3.6 %
+    // over the plan without them: 7-20 % where the tiles make whole rounds of a long K (24576 x 4096, 22016 x 4096,
+    // 3584 x 18944, 4096 x 12288), nothing where K is short (4096 x 4096: 1.06-1.11 of the time) or the rounds do not fit
+    // (37888 x 3584: 1.13-1.21). With up to 128 rows the 128-row tiles are level (24576 x 4096 at 128 rows 43.3 against 51.6 us).
+    if (slices_go_to == SLICES_CONSUMER && m_upper > 128 && m_upper <= 256) {
+        struct Stream { int kind, bn; double alone, full; };                                    // us per K tile
+        constexpr Stream kStream[] = {{GEMM_STREAM_256x96, 96, 0.52, 0.56}, {GEMM_STREAM_256x64, 64, 0.44, 0.44}};
+        constexpr double kPipeFillStream = 6.5;
+        for (const Stream &st : kStream) {
+            const int tiles = ceil_div(n, st.bn);
+            for (int i = 0; i < n_slices && (i == 0 || tiles <= 768); ++i) {
+                const int s = slices[i].s;
+                const long wgs = (long)tiles * s, rounds = (wgs + 255) / 256;
+                const double last = st.full * (double)(wgs - (rounds - 1) * 256) * (1.0 / 256.0);
+                double t = slices[i].nk * ((rounds - 1) * st.full + (last > st.alone ? last : st.alone)) + rounds * kPipeFillStream;
+                const double stream = (operands + s * product) * kPerStream;
+                if (stream > t) t = stream;
+                t += kLaunch;
+                if (s > 1) t += (s - 1) * product * kPerReduce + kReduceFixed;
+                if (t < best) {
+                    best = t;
+                    p.kind = st.kind;
+                    p.split_k = s;
+                }
+            }
+        }
+        if (dkv_gemm_is_stream(p.kind)) return p;
+    }
     // Launch options, from the same sweeps: a staggered K start pays when there is one row of tiles
     // (all workgroups of a K slice would otherwise read the same A columns at once), and with two or three rows of tiles
     // and several rounds of workgroups where the rows are a multiple of 4 KB apart, so that equal columns sit in the same
@@ -289,12 +319,12 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
 }
 
 bool dkv_gemm_can_fuse_swiglu(int dtype, int n, int k, const GemmPlan &p) {
-    return dtype == DKV_BF16 && p.kind <= GEMM_DMA_LAST && p.split_k == 1 && p.frac_units == 0 && (k % BK) == 0 &&
-           (n & 1) == 0;
+    return dtype == DKV_BF16 && (p.kind <= GEMM_DMA_LAST || dkv_gemm_is_stream(p.kind)) && p.split_k == 1 && p.frac_units == 0 &&
+           (k % BK) == 0 && (n & 1) == 0;
 }
 
 int dkv_gemm_plan_valid(int dtype, int k, GemmPlan p) {
-    if (p.split_k < 1 || p.kind < 0 || p.kind >= GEMM_KINDS || p.frac_units < 0) return 0;
+    if (p.split_k < 1 || p.kind < 0 || (p.kind >= GEMM_KINDS && !dkv_gemm_is_stream(p.kind)) || p.frac_units < 0) return 0;
     if (p.frac_units) {
         // a 3/4 share: every tile is covered by exactly two workgroups
         if (p.kind > GEMM_DMA_LAST || dtype != DKV_BF16 || (k % BK) != 0) return 0;
@@ -333,7 +363,7 @@ int dkv_launch_gemm(int dtype, const void *A, const void *W, float *partial, int
         dkv_set_error("projection plan (kind %d, split %d) does not fit dtype %d, K %d", p.kind, p.split_k, dtype, k);
         return DKV_E_UNSUPPORTED;
     }
-    if (p.kind <= GEMM_DMA_LAST) {
+    if (p.kind <= GEMM_DMA_LAST || dkv_gemm_is_stream(p.kind)) {
         GemmEpilogue ep;
         if (p.flags & GEMM_FLAG_SWIGLU) {
             if (p.split_k != 1 || p.frac_units) {

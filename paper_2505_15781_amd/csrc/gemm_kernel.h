@@ -72,6 +72,7 @@ __device__ __forceinline__ TileWork next_tile_work(int &unit, int unit_end, int 
 }
 
 #include "gemm_pingpong.h"
+#include "gemm_stream.h"
 
 template <int EPI, int MT, int NT, int WM, int WN, int STAGES>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_dma(const bf16_t *__restrict__ A,
@@ -257,6 +258,10 @@ int launch_dma(const void *A, const void *W, float *P, int m_upper, int m_cap, c
 template <int EPI>
 int dispatch_dma(const void *A, const void *W, float *partial, int m_upper, int m_cap, const int *m_dev, int n, int k,
                  const GemmPlan &p, const GemmEpilogue &ep, hipStream_t stream) {
+    if constexpr (EPI != EPI_HEAD) {
+        if (p.kind == GEMM_STREAM_256x96) return launch_stream<EPI, 3>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, ep, stream);
+        if (p.kind == GEMM_STREAM_256x64) return launch_stream<EPI, 2>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, ep, stream);
+    }
     switch (p.kind) {
         case GEMM_DMA_32x128:
             return launch_dma<EPI, 1, 1, 1, 4, 4>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);

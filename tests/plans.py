@@ -72,3 +72,21 @@ def launch_head(x, w, tile, mask_id, status, rows=None, logits=None):
     f.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_int, GemmPlan, C.POINTER(HeadEpilogue), C.c_void_p]
     b._check(f(x.data_ptr(), w.data_ptr(), m, b._ptr(rows), n, k, GemmPlan(TILES.index(tile), 1, 0, 0), C.byref(ep), b._stream()))
     return part
+
+
+STREAM_TILES = {"stream_256x96": 11, "stream_256x64": 12}      # kinds that only the planner hands out, for projections inside a step
+
+
+def launch_stream(x, w, tile, split, rows=None, swiglu=False):
+    """A projection of at most 256 rows on one of STREAM_TILES: fp32 [split][m][n], or bf16 [m][n / 2] with the SwiGLU epilogue;
+    NaN where the launch writes nothing. `rows`: device count of rows, at most m."""
+    import torch
+    from paper_2505_15781_amd import binding as b
+    (m, k), n = x.shape, w.shape[0]
+    out = torch.full((m, n // 2) if swiglu else (split, m, n), float("nan"), dtype=torch.bfloat16 if swiglu else torch.float32, device=x.device)
+    f = b.lib._Z15dkv_launch_gemmiPKvS0_PfiiPKiii8GemmPlanP12ihipStream_t
+    f.restype = C.c_int
+    f.argtypes = [C.c_int] + [C.c_void_p] * 3 + [C.c_int] * 2 + [C.c_void_p] + [C.c_int] * 2 + [GemmPlan, C.c_void_p]
+    b._check(f(0, x.data_ptr(), w.data_ptr(), out.data_ptr(), m, m, b._ptr(rows), n, k,
+               GemmPlan(STREAM_TILES[tile], split, 0, 4 if swiglu else 0), b._stream()))
+    return out

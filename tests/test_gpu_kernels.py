@@ -8,7 +8,7 @@ from dkv_inputs.configs import BF16, FP32
 from oracle.attn_update import attn_update as oracle_attn_update
 from helpers import rel_err
 from gpu_parity import check_close, tolerances
-from plans import OWN_LAUNCH, STAGGER, XCD_GROUP, attn_plan, gemm_plan, launch_head
+from plans import OWN_LAUNCH, STAGGER, STREAM_TILES, XCD_GROUP, attn_plan, gemm_plan, launch_head, launch_stream
 
 pytestmark = pytest.mark.gpu
 
@@ -66,6 +66,31 @@ def test_projection_planned_launch_from_150_to_3072_rows(m, n, k, rule):
     y = P.gemm(x, w, BF16).double()
     ref = x.double() @ w.double().T
     assert ((y - ref).norm() / ref.norm()).item() <= 1e-5 and ((y - ref).abs().max() / ref.abs().max()).item() <= 1e-5
+
+
+@pytest.mark.parametrize("tile", sorted(STREAM_TILES))
+@pytest.mark.parametrize("m,n,k,split,rows", [(256, 384, 1024, 1, None), (129, 200, 64, 1, None), (255, 97, 128, 1, 131), (1, 1000, 192, 1, None),
+                                              (250, 1000, 2048, 3, None), (193, 96, 704, 2, 64), (256, 3000, 4096, 8, 256)])
+def test_projection_of_one_row_of_tiles(tile, m, n, k, split, rows):
+    """One to eleven K tiles per slice (fewer than the stages, odd and even against the pairs in which weights are fetched), ragged
+    columns, more workgroups than one round, and a device-side row count below the bound: rows past it are not written. Sums
+    of k products of N(0, 1) and N(0, 0.02^2), as for the other projection kernels."""
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    x = torch.randn((m, k), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((n, k), generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+    got = launch_stream(x, w, tile, split, None if rows is None else torch.tensor([rows], dtype=torch.int32, device="cuda"))
+    live = m if rows is None else rows
+    assert torch.isnan(got[:, live:]).all() and not torch.isnan(got[:, :live]).any()
+    ref = x[:live].double() @ w.double().T
+    err = got[:, :live].double().sum(0) - ref
+    assert (err.norm() / ref.norm()).item() <= 1e-5 and (err.abs().max() / ref.abs().max()).item() <= 1e-5
+    if split == 1 and n % 2 == 0:
+        y = launch_stream(x, w, tile, 1, swiglu=True)
+        full = x.double() @ w.double().T
+        want = torch.nn.functional.silu(full[:, 0::2]) * full[:, 1::2]
+        # the result is rounded to bf16: half a unit of 8 significant bits, at most 2^-8 of the value; the sums as above
+        excess = ((y.double() - want).abs() - 2.0 ** -8 * want.abs()).max() / want.abs().max()
+        assert excess.item() <= 1e-5
 
 
 @pytest.mark.parametrize("kind,split", [("dma_32x128", 1), ("dma_32x128", 3), ("dma_64x128", 2), ("dma_128x128", 1),

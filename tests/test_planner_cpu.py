@@ -4,7 +4,7 @@ import pytest
 import dkv_inputs as D
 from dkv_inputs.configs import BF16
 
-from plans import CONSUMER, EIGHT_WAVEFRONTS, ONE_SLICE, OWN_LAUNCH, STREAM_W, attn_plan, gemm_plan
+from plans import CONSUMER, EIGHT_WAVEFRONTS, ONE_SLICE, OWN_LAUNCH, STREAM_TILES, STREAM_W, attn_plan, gemm_plan
 
 
 @pytest.mark.parametrize("m,n,k", [(2049, 512, 4096), (4096, 512, 4096), (2304, 3584, 18944), (3072, 1024, 8192), (5000, 1024, 4096)])
@@ -42,6 +42,17 @@ def test_the_streaming_hint_is_planned_only_for_tiles_that_follow_it():
                     assert p.tile not in EIGHT_WAVEFRONTS, (m, n, k, p.tile)
                     assert p.grid(m, n)[0] == 1
     assert asked > 500
+
+
+def test_one_row_of_wide_tiles_is_planned_up_to_256_rows_inside_a_step():
+    """Both sides of each line: the row counts, who asks, and shapes whose tiles do not make whole rounds or whose K is short."""
+    stream = set(STREAM_TILES.values())
+    for n, k in [(24576, 4096), (3584, 18944), (4096, 12288)]:
+        assert gemm_plan(128, n, k).kind not in stream and gemm_plan(257, n, k).kind not in stream
+        assert gemm_plan(160, n, k).kind in stream and gemm_plan(256, n, k).kind in stream
+        assert gemm_plan(256, n, k, OWN_LAUNCH).kind not in stream and gemm_plan(256, n, k, ONE_SLICE).kind not in stream
+    for n, k in [(37888, 3584), (4096, 4096), (3584, 3584), (1024, 8192)]:
+        assert all(gemm_plan(m, n, k).kind not in stream for m in range(129, 257)), (n, k)
 
 
 def test_every_attention_kernel_is_planned_where_its_measurements_say():
