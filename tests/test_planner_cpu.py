@@ -65,3 +65,20 @@ def test_every_attention_kernel_is_planned_where_its_measurements_say():
     assert kernel(8, 32, 32, 767, 128) == "wide" and kernel(8, 32, 32, 768, 129) == "wide"                    # long, one block
     assert kernel(15, 32, 32, 768, 128) == "shared8" and kernel(16, 32, 32, 768, 128) == "shared4"            # 512 pairs
     assert kernel(16, 28, 4, 768, 129) == "wide" and kernel(8, 32, 32, 1024, 512) == "wide"
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,seq_len,rows,kernel,splits", [
+    (1, 32, 32, 512, 30, "ksplit1x8", 1), (4, 32, 32, 512, 32, "ksplit1x8", 1), (4, 32, 32, 512, 33, "ksplit2x8", 1),     # 256 items
+    (2, 32, 32, 736, 5, "ksplit1x8", 1), (2, 32, 32, 737, 5, "ksplit1x8", 3), (1, 32, 32, 737, 5, "ksplit1x8", 4),        # 24 tiles
+    (2, 32, 32, 1120, 20, "ksplit1x8", 1), (2, 32, 32, 1121, 16, "ksplit1x8", 3), (1, 32, 32, 1121, 20, "ksplit1x8", 3),  # 36 tiles
+    (5, 32, 32, 1024, 20, "ksplit2x8", 1), (4, 32, 32, 1121, 9, "ksplit1x8", 2), (1, 16, 16, 8192, 9, "ksplit1x8", 15),   # 128 items; long
+    (1, 28, 4, 1024, 9, "ksplit1x8", 1), (1, 28, 4, 1025, 9, "ksplit2x8", 2)])                                            # fewer than 8 pairs
+def test_key_split_items_hold_one_query_tile_while_each_has_a_compute_unit(batch, q_heads, kv_heads, seq_len, rows, kernel, splits):
+    """Both sides of each line; slices never make more workgroups than there are compute units, and the records of any call fit the
+    library's static scratch of 4 MiB."""
+    from paper_2505_15781_amd import binding as b
+    p = attn_plan(D.AttnUpdateShape(batch, q_heads, kv_heads, seq_len, 128, dtype=BF16), rows)
+    assert (p.kernel, p.splits) == (kernel, splits)
+    if splits > 1 and kernel == "ksplit1x8":
+        assert batch * kv_heads * p.q_groups * p.splits <= 256
+    assert b.lib.dkv_attn_update_workspace_bytes(batch, q_heads, kv_heads, seq_len, 128, BF16, rows) <= 4 << 20
