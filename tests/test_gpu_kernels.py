@@ -216,6 +216,43 @@ def test_vocabulary_statistics_of_the_tile_kernels(tile, rows_off, cols_off):
     assert lg[11].argmax() == mask_id
 
 
+@pytest.mark.parametrize("tile", ["dma_32x128", "dma_64x128", "dma_128x128", "dma_128x256", "dma_128x96"])
+@pytest.mark.parametrize("rows_off,tiles_n,cols_off,k", [(0, 1, 0, 64), (-1, 1, -90, 128), (1, 2, 1, 192), (-31, 3, -1, 256), (-16, 1, -64, 320)])
+def test_vocabulary_statistics_of_four_wavefronts(tile, rows_off, tiles_n, cols_off, k):
+    """The reductions over the 32 lanes of a row: columns that end in the first lanes, in the middle and at the end of a tile, every
+    logit twice a row (distances over lanes, wavefronts and tiles), a NaN row, one past the device's count; one to five K tiles,
+    fewer than are fetched ahead and more. Records against the kernel's own fp32 logits (maximum and arg max exactly, the sum to
+    the bound of the test above: no logit is further than 64 from the row's maximum), those against float64."""
+    bm, bn = (int(v) for v in tile.split("_")[1].split("x"))
+    m, n = max(bm + rows_off, 2), tiles_n * bn + cols_off
+    mask_id = n // 3
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    x = (torch.randn((m, k), generator=g, device="cuda") * 0.25).to(torch.bfloat16)
+    w = (torch.randn((n, k), generator=g, device="cuda") * 0.25).to(torch.bfloat16)
+    w[n - n // 2:] = w[:n // 2]
+    x[m - 1] = float("nan")
+    count = torch.tensor([m - 1], dtype=torch.int32, device="cuda")
+    logits, status = torch.zeros((m, n), dtype=torch.float32, device="cuda"), torch.zeros(2, dtype=torch.int32, device="cuda")
+    got = launch_head(x, w, tile, mask_id, status[:1], count, logits)
+    assert torch.equal(got, launch_head(x, w, tile, mask_id, status[:1], count))        # logits not written
+    assert (got[m - 1] == 0x7fc00123).all() and not logits[m - 1].any()
+    x[m - 2, k - 1] = float("nan")
+    launch_head(x, w, tile, mask_id, status[1:], count)
+    assert status.tolist() == [0, 1]
+    x[m - 2, k - 1] = 0
+    got, lg = launch_head(x, w, tile, mask_id, status[:1], count, logits)[:m - 1], logits[:m - 1]
+    ref = x[:m - 1].double() @ w.double().T
+    assert ((lg - ref).norm() / ref.norm()).item() <= 1e-5
+    lg[:, mask_id] = -float("inf")
+    part = torch.nn.functional.pad(lg, (0, -n % bn), value=-float("inf")).view(m - 1, -1, bn)
+    top = part.max(dim=2).values
+    assert torch.equal(got[..., 0].contiguous().view(torch.float32), top)
+    lowest = (part == top[..., None]).int().argmax(dim=2) + bn * torch.arange(part.shape[1], device="cuda")
+    assert torch.equal(got[..., 2], lowest.to(torch.int32))
+    want = (part.double() - top.double()[..., None]).exp().sum(dim=2)
+    assert ((got[..., 1].contiguous().view(torch.float32) - want).abs() / want).max().item() <= 1e-5
+
+
 @pytest.mark.parametrize("m,n,k", [(1, 2, 4), (16, 16, 64), (17, 30, 60), (64, 130, 68), (65, 16, 1028), (128, 4096, 64),
                                    (129, 4096, 64), (16, 16, 128), (20, 20, 132)])
 def test_fp32_projection_of_few_rows_at_tile_edges(m, n, k):
