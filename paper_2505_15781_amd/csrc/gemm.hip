@@ -154,7 +154,7 @@ struct KindInfo {
 };
 constexpr KindInfo kKinds[] = {
     {32, 128},    // GEMM_DMA_32x128   <1,1,1,4> 4 stages
-    {64, 128},    // GEMM_DMA_64x128   <2,1,1,4> 4 stages
+    {64, 128},    // GEMM_DMA_64x128   <2,1,1,4> 4 stages (vocabulary statistics: <1,2,2,2> 3 stages)
     {128, 128},   // GEMM_DMA_128x128  <2,2,2,2> 3 stages
     {128, 256},   // GEMM_DMA_128x256  <2,4,2,2> 3 stages
     {256, 256},   // GEMM_DMA_256x256  <4,2,2,4> 2 stages, 8 wavefronts

@@ -266,7 +266,15 @@ int dispatch_dma(const void *A, const void *W, float *partial, int m_upper, int 
         case GEMM_DMA_32x128:
             return launch_dma<EPI, 1, 1, 1, 4, 4>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
         case GEMM_DMA_64x128:
-            return launch_dma<EPI, 2, 1, 1, 4, 4>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
+            // The vocabulary has several rounds of column tiles and an epilogue of a few us. With three stages of LDS instead of
+            // four a compute unit holds two workgroups, one multiplying in the other's epilogue and first fills: 126464 x 4096
+            // at 33 / 48 / 64 rows 181 / 187 / 193 us -> 162 / 164 / 168, 152064 x 3584 204 / 211 / 219 -> 174 / 180 / 189,
+            // 32000 x 2048 30 -> 27 (2x2 wavefronts, halving the rows each one reduces: up to 2 % of that). The other
+            // projections keep four: they make about one round, where the deeper ring is worth 2-6 % (24576 x 4096 at 32 rows
+            // 34.2 against 36.3 us, 3584 x 18944 unsplit 114 against 126).
+            if constexpr (EPI == EPI_HEAD)
+                return launch_dma<EPI, 1, 2, 2, 2, 3>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
+            else return launch_dma<EPI, 2, 1, 1, 4, 4>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
         case GEMM_DMA_128x128:
             return launch_dma<EPI, 2, 2, 2, 2, 3>(A, W, partial, m_upper, m_cap, m_dev, n, k, p.split_k, p.frac_units, p.flags, ep, stream);
         case GEMM_DMA_128x256:
