@@ -201,11 +201,20 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
     //   a workgroup of the 4-wavefront tiles needs, per K tile, the longer of filling its LDS stage (52 GB/s per compute
     //   unit, 14.5 TB/s over all workgroups in flight) and its MFMAs (5.7 TFLOP/s per compute unit);
     //   a workgroup of the 8-wavefront tiles needs the times of kPingPong, alone and with the whole chip at work;
+    //   128x256 tiles have no second workgroup on the compute unit that would work in a round's first fills and epilogue, and
+    //   lose that time with every further round;
     //   workgroups run in rounds of 256 (one per compute unit), a partly filled round costs a full one;
     //   no launch beats streaming its operands and results once;
     //   every further K slice adds the write and re-read of its partial sums by the consumer; a reduction of its own also
     //   reads the first slice and is a launch more (fitted with dkv_gemm over 12 shapes at 8 to 5000 rows: mean loss 1.3 %;
     //   charged like the consumer's, 400 x 4608 x 3584 took 36.6 us in 4 slices against 29.2 in one).
+    // The times of 256x256 tiles and of a further round of 128x256 tiles are those of a chip that has been busy for 12 ms and
+    // more, as it is inside a step (261 shapes and row counts of 65 to 8192, launches with their consumers: mean loss 1.4 %
+    // with the constants of single launches, 1.0 % with these; what is planned differently: 37888 x 3584 at 257 to 384 rows,
+    // 192x256 for 128x256 tiles, 148 -> 133-140 us; 24576 x 4096 at 513 to 640 rows, the same, 151 -> 148; 4096 x 12288 at 410
+    // to 512 rows, 256x256 in 6 slices for 128x256 in 4, 72 -> 66; 3584 x 18944 at 480 to 512 rows, 256x256 in 8 slices for
+    // 256x192 in 6, 88 -> 84; 152064 x 3584 at 65 to 128 candidates, 192x256 for 128x256, level; no other plan
+    // of fewer than 257 rows).
     // Tiles of 96 and 192 columns or rows exist because 12288 / 96 = 128 and 24576 / 192 = 128 column tiles make
     // exactly one or two full rounds where 128- and 256-column tiles leave a quarter of the chip idle, and 129..192 or
     // 257..384 rows fill one or two 192-row tiles (320 rows of the 8B vocabulary: 821 -> 393 us).
@@ -215,9 +224,9 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
     // inner loop.
     constexpr double kFillPerCu = 52032.0, kFlopsPerCu = 5698686.0, kFillAll = 14478510.0;   // bytes, flops per us
     constexpr double kPerStream = 1.0 / 7841520.0, kPerReduce = 1.0 / 1849696.0;                // us per byte
-    constexpr double kLaunch = 3.5, kPipeFill = 0.7, kPipeFill8 = 0.16, kReduceFixed = 3.2;     // us
+    constexpr double kLaunch = 3.5, kPipeFill = 0.7, kPipeFill8 = 0.16, kReduceFixed = 3.2, kNextRound128x256 = 14.0;     // us
     struct PingPong { double alone, full; };                                                    // us per K tile
-    constexpr PingPong kPingPong[] = {{}, {}, {}, {}, {1.207, 1.336}, {}, {}, {1.041, 1.092}, {0.980, 1.078}};
+    constexpr PingPong kPingPong[] = {{}, {}, {}, {}, {1.130, 1.290}, {}, {}, {1.041, 1.092}, {0.980, 1.078}};
     static_assert(GEMM_DMA_256x256 == 4 && GEMM_DMA_256x192 == 7 && GEMM_DMA_192x256 == 8 && GEMM_DMA_LAST == 8, "order of kPingPong");
     const int kt_total = k / BK;
     struct { int s, nk; } slices[6];       // K slices worth trying, K tiles of each
@@ -251,6 +260,7 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
                 t_rounds = rounds * (all > t_cu ? all : t_cu);
             }
             double t = slices[i].nk * t_rounds + rounds * (eight ? kPipeFill8 : kPipeFill);
+            if (kind == GEMM_DMA_128x256) t += (rounds - 1) * kNextRound128x256;
             const double stream = (operands + s * product) * kPerStream;
             if (stream > t) t = stream;
             t += kLaunch;

@@ -20,6 +20,13 @@ def test_k_is_not_sliced_where_the_tiles_fill_the_chip(m, n, k):
     assert gemm_plan(m, n, k).split_k == 1
 
 
+@pytest.mark.parametrize("m,n,k,tile", [(294, 37888, 3584, "dma_192x256"), (384, 37888, 3584, "dma_192x256"), (640, 24576, 4096, "dma_192x256"),
+                                        (640, 12288, 4096, "dma_128x256"), (512, 4096, 12288, "dma_256x256")])
+def test_128x256_tiles_are_planned_for_one_round(m, n, k, tile):
+    """A second round of them (444 and 480 workgroups) costs more than its K tiles; one round (240) is theirs."""
+    assert gemm_plan(m, n, k).tile == tile
+
+
 @pytest.mark.parametrize("m,n,k", [(400, 4608, 3584), (700, 4608, 3584), (1024, 4608, 3584), (400, 12288, 4096)])
 def test_a_projection_on_its_own_pays_for_the_reduction_of_its_slices(m, n, k):
     """dkv_gemm adds the slices up in a launch of its own, a step's row kernel while it reads the product: where the slices
