@@ -90,3 +90,24 @@ def launch_stream(x, w, tile, split, rows=None, swiglu=False):
     b._check(f(0, x.data_ptr(), w.data_ptr(), out.data_ptr(), m, m, b._ptr(rows), n, k,
                GemmPlan(STREAM_TILES[tile], split, 0, 4 if swiglu else 0), b._stream()))
     return out
+
+
+def embed_norm(table, tokens, pos, seq, counts, gain, h, a, stamp, eps, step):
+    """The row kernel that begins a step: rows of the embedding table into h, their RMSNorm into a."""
+    import torch
+    from paper_2505_15781_amd import binding as b
+    f = b.lib._Z21dkv_launch_embed_normiP12ihipStream_tiiPKvPKiS4_S4_S4_PKfPfPvPiifi
+    f.restype = C.c_int
+    f.argtypes = [C.c_int, C.c_void_p, C.c_int, C.c_int] + [C.c_void_p] * 9 + [C.c_int, C.c_float, C.c_int]
+    b._check(f(0 if table.dtype == torch.bfloat16 else 1, b._stream(), h.shape[0], h.shape[1], table.data_ptr(), tokens.data_ptr(), pos.data_ptr(),
+               seq.data_ptr(), counts.data_ptr(), gain.data_ptr(), h.data_ptr(), a.data_ptr(), stamp.data_ptr(), tokens.shape[1], eps, step))
+
+
+def gather_rows(src, picks, counts, dst):
+    """dst[c] = src[picks[c]] for c below counts[1]."""
+    import torch
+    from paper_2505_15781_amd import binding as b
+    f = b.lib._Z22dkv_launch_gather_rowsiP12ihipStream_tiPKvPKiS4_Pvi
+    f.restype, f.argtypes = C.c_int, [C.c_int, C.c_void_p, C.c_int] + [C.c_void_p] * 4 + [C.c_int]
+    b._check(f(0 if src.dtype == torch.bfloat16 else 1, b._stream(), dst.shape[0], src.data_ptr(), picks.data_ptr(), counts.data_ptr(),
+               dst.data_ptr(), dst.shape[1]))

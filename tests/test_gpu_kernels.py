@@ -8,7 +8,7 @@ from dkv_inputs.configs import BF16, FP32
 from oracle.attn_update import attn_update as oracle_attn_update
 from helpers import rel_err
 from gpu_parity import check_close, tolerances
-from plans import OWN_LAUNCH, STAGGER, STREAM_TILES, XCD_GROUP, attn_plan, gemm_plan, launch_head, launch_stream
+from plans import OWN_LAUNCH, STAGGER, STREAM_TILES, XCD_GROUP, attn_plan, embed_norm, gather_rows, gemm_plan, launch_head, launch_stream
 
 pytestmark = pytest.mark.gpu
 
@@ -251,6 +251,37 @@ def test_vocabulary_statistics_of_four_wavefronts(tile, rows_off, tiles_n, cols_
     assert torch.equal(got[..., 2], lowest.to(torch.int32))
     want = (part.double() - top.double()[..., None]).exp().sum(dim=2)
     assert ((got[..., 1].contiguous().view(torch.float32) - want).abs() / want).max().item() <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [BF16, FP32])
+@pytest.mark.parametrize("d", [4, 252, 260, 1024, 1028, 2052, 4096, 4100, 8192])
+def test_embedded_rows_and_gathered_candidates_in_pieces_of_four(dtype, d):
+    """Row lengths around what one, four, eight and 16 wavefronts hold and two pieces a lane, a table that starts one element past
+    any alignment, rows past the device's counts. The residual rows and the gathered ones are copies; the norm adds d squares in
+    fp32 (lanes, then 64 and 16 of them: at most 28 additions in a row, 2^-24 each, half of it after the root) and rounds three
+    products and the reciprocal root: below 2^-19, and with bf16 (seven bits behind the leading one) half a unit of 2^-7 more."""
+    rows, L, V = 7, 11, 13
+    t = torch.bfloat16 if dtype == BF16 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(d)
+    table = torch.randn(V * d + 1, generator=g, device="cuda").to(t)[1:].view(V, d)
+    gain = (torch.rand(d + 1, generator=g, device="cuda") + 0.5)[1:]
+    tokens = torch.randint(V, (2, L), generator=g, device="cuda", dtype=torch.int32)
+    pos, seq = (torch.tensor(x, dtype=torch.int32, device="cuda") for x in ([0, 3, 10, 1, 2, 9, 0], [0, 0, 0, 1, 1, 1, 1]))
+    counts = torch.tensor([rows - 1, 3], dtype=torch.int32, device="cuda")
+    h, a = torch.zeros((rows, d), device="cuda"), torch.zeros((rows, d), dtype=t, device="cuda")
+    stamp = torch.zeros((2, L), dtype=torch.int32, device="cuda")
+    embed_norm(table, tokens, pos, seq, counts, gain, h, a, stamp, 1e-5, 5)
+    live = slice(0, rows - 1)
+    ids = tokens[seq[live].long(), pos[live].long()].long()
+    want = table[ids].double()
+    assert torch.equal(h[live].double(), want) and not h[rows - 1].any() and not a[rows - 1].any()
+    assert stamp.count_nonzero().item() == rows - 1 and (stamp[seq[live].long(), pos[live].long()] == 5).all()
+    want = want / (want.square().mean(dim=1, keepdim=True) + 1e-5).sqrt() * gain.double()
+    bound = 2.0 ** -19 + (2.0 ** -8 if dtype == BF16 else 0.0)
+    assert ((a[live].double() - want).abs() <= bound * want.abs()).all()
+    picked = torch.zeros((4, d), dtype=t, device="cuda")
+    gather_rows(a, torch.tensor([5, 0, 5, 2], dtype=torch.int32, device="cuda"), counts, picked)
+    assert torch.equal(picked[:3], a[[5, 0, 5]]) and not picked[3].any()
 
 
 @pytest.mark.parametrize("m,n,k", [(1, 2, 4), (16, 16, 64), (17, 30, 60), (64, 130, 68), (65, 16, 1028), (128, 4096, 64),
