@@ -5,8 +5,8 @@
 // many cycles those pipes wait. Measured on registers only, with random operands: MFMA 32x32x16 runs at 1.88 PFLOP/s,
 // 16x16x32 at 2.12-2.14 (2.41-2.48 with operands of zeros). So the tile is multiplied with 16x16x32, by 8 wavefronts, two
 // per SIMD, one of each group, of which one fetches while the other multiplies. Fragment reads of all 8 wavefronts move
-// 192 KB through LDS per 256x256x64 step, 75 % of the port's 128 B/cycle: they have to be spread evenly under the MFMAs,
-// which the alternation does.
+// 192 KB through LDS per 256x256x64 step, 37 % of its 2048 MFMA cycles at the 256 B/cycle that conflict-free 16-byte reads reach
+// (a loop of these reads alone), beside the fills' writes: they have to be spread evenly under the MFMAs, which the alternation does.
 //
 // Schedule: a wavefront's 32 MT x 32 NT part of the tile is worked on as 2 x 2 quarters (row half A0 / A1, column half
 // B0 / B1), one quarter (2 MT NT MFMAs) per phase. A phase is a fetch slot (LDS reads of the fragments it needs, the
