@@ -399,36 +399,40 @@ AttnPlan dkv_attn_plan(int dtype, int batch, int n_q_heads, int n_kv_heads, int 
         return p;
     }
     // One query tile per item while every item still has a compute unit of its own: the chain of a key tile (scores, softmax,
-    // output) is what a launch with few items waits for, and a second query tile makes it longer. Both measured, us per call,
+    // output) is what a launch with few items waits for, and a second query tile makes it longer. attn_item puts all workgroups
+    // of a pair on XCD pair % 8, so the fullest XCD counts: ceil(pairs / 8) pairs for 32 units. Both measured, us per call,
     // two tiles / one: 32 pairs, 512 keys, 30 rows 12.9 / 9.5; 96 pairs, 945 keys, 21 query rows 17.8 / 12.7; 4 pairs, 325 keys, 42 query rows
-    // 8.9 / 7.3; 128 pairs (256 items), 512 keys, 20 rows 14.1 / 10.7, 1024 keys 20.3 / 16.8. Beyond, two tiles read K/V half as
-    // often: 288 items, 512 keys 11.8 / 13.1 (4 wavefronts), 576 items 14.6 / 19.9.
+    // 8.9 / 7.3; 128 pairs (32 items on an XCD), 512 keys, 20 rows 14.1 / 10.7, 1024 keys 20.3 / 16.8. Beyond, two tiles read K/V half as
+    // often: 36 items on an XCD, 512 keys 11.8 / 13.1 (4 wavefronts); 4 pairs of 7 query heads each, 768 keys, 80 rows (35) 13.7 / 18.6;
+    // 12 pairs, 512 keys, 48 rows (42) 11.5 / 16.5. 330 calls whose plan depends on counting the XCD or the chip: 0.94 of the time
+    // of the latter on average, 1.03 at worst.
     // Fewer than 8 pairs (XCDs) over more than 1024 keys keep two tiles and the slices that go with them, although one tile is
     // 8-18 % faster there too: the call that the test of peaked softmax holds to the two-tile kernel with 8 wavefronts lies here.
     const long pairs = (long)batch * n_kv_heads;
     const int n_tiles = ceil_div(seq_len, KT);
     const bool few_pairs = pairs < 8 && seq_len > 1024;
-    p.ksplit_nq = p.q_tiles >= 2 && (few_pairs || pairs * p.q_tiles > 256) ? 2 : 1;
+    const long per_xcd = (pairs + 7) / 8;
+    p.ksplit_nq = p.q_tiles >= 2 && (few_pairs || per_xcd * p.q_tiles > 32) ? 2 : 1;
     p.q_groups = ceil_div(p.q_tiles, p.ksplit_nq);
-    const long items = pairs * p.q_groups;
+    const long items = per_xcd * p.q_groups;
     // 8 wavefronts per workgroup (one workgroup per compute unit) while that still gives every compute
     // unit at most one; beyond, 4 wavefronts so that two workgroups share a unit
-    p.ksplit_waves = items <= 256 ? 8 : 4;
-    // Keys are sliced over workgroups where items are few and their keys many, never into more workgroups than compute units
-    // (160 items of two query tiles, 1024 keys: one slice 22.0 us, two 30.5; 96 items of one, 1056 keys: two 12.4, three 16.4).
+    p.ksplit_waves = items <= 32 ? 8 : 4;
+    // Keys are sliced over workgroups where the items of an XCD are few and their keys many, never into more workgroups than it has
+    // units (20 items of two query tiles, 1024 keys: one slice 22.0 us, two 30.5; 12 items of one, 1056 keys: two 12.4, three 16.4).
     // A slice more pays for the merge launch, 3 us, from 24 key tiles of 128 dims on when every item has a pair to itself
     // (64 pairs, 768 keys 12.9 -> 12.3 us, 1200 keys 17.8 -> 14.6), from 36 when items share a pair, whose K/V the L2 then
     // holds, or when only two slices fit (32 items on 8 pairs: 29 tiles 10.6 -> 11.0, 38 tiles 12.1 -> 11.5). Four slices
-    // take most of it; three where four would take every unit (64 items, 1700 keys: three 15.8, four 16.6). Over 423 calls
-    // (8 to 1280 items, 68 to 2048 keys, head_dim 64 and 128): 0.908 of the time of the former rule on average, 1.02 at worst.
+    // take most of it; three where four would take every unit (8 items, 1700 keys: three 15.8, four 16.6).
     int s = 1;
     if (few_pairs) {
-        s = items < 192 ? (int)((384 + items - 1) / items) : 1;
+        const long all = pairs * p.q_groups;
+        s = all < 192 ? (int)((384 + all - 1) / all) : 1;
         if (s > n_tiles / 16) s = n_tiles / 16;             // two tiles per wavefront
-    } else if (items <= 128 && (long)n_tiles * head_dim >= 128L * (p.q_tiles > 1 || items > 96 ? 36 : 24)) {
+    } else if (items <= 16 && (long)n_tiles * head_dim >= 128L * (p.q_tiles > 1 || items > 12 ? 36 : 24)) {
         s = n_tiles / 16 > 4 ? n_tiles / 16 : 4;
-        if (s > 256 / items) s = (int)(256 / items);
-        if (s > 2 && s * items == 256) --s;
+        if (s > 32 / items) s = (int)(32 / items);
+        if (s > 2 && s * items == 32) --s;
     }
     p.tiles_per_split = ceil_div(n_tiles, s);
     p.splits = ceil_div(n_tiles, p.tiles_per_split);

@@ -75,17 +75,22 @@ def test_every_attention_kernel_is_planned_where_its_measurements_say():
 
 
 @pytest.mark.parametrize("batch,q_heads,kv_heads,seq_len,rows,kernel,splits", [
-    (1, 32, 32, 512, 30, "ksplit1x8", 1), (4, 32, 32, 512, 32, "ksplit1x8", 1), (4, 32, 32, 512, 33, "ksplit2x8", 1),     # 256 items
-    (2, 32, 32, 736, 5, "ksplit1x8", 1), (2, 32, 32, 737, 5, "ksplit1x8", 3), (1, 32, 32, 737, 5, "ksplit1x8", 4),        # 24 tiles
-    (2, 32, 32, 1120, 20, "ksplit1x8", 1), (2, 32, 32, 1121, 16, "ksplit1x8", 3), (1, 32, 32, 1121, 20, "ksplit1x8", 3),  # 36 tiles
-    (5, 32, 32, 1024, 20, "ksplit2x8", 1), (4, 32, 32, 1121, 9, "ksplit1x8", 2), (1, 16, 16, 8192, 9, "ksplit1x8", 15),   # 128 items; long
+    (1, 32, 32, 512, 30, "ksplit1x8", 1), (4, 32, 32, 512, 32, "ksplit1x8", 1), (4, 32, 32, 512, 33, "ksplit2x8", 1),     # 32 items per XCD
+    (1, 28, 4, 512, 73, "ksplit1x8", 1), (1, 28, 4, 512, 74, "ksplit2x8", 1), (1, 28, 4, 768, 140, "ksplit2x8", 1),       # 4 pairs
+    (3, 28, 4, 512, 36, "ksplit1x8", 1), (3, 28, 4, 512, 37, "ksplit2x8", 1),                                             # 12
+    (5, 28, 4, 512, 22, "ksplit1x8", 1), (5, 28, 4, 512, 23, "ksplit2x8", 1),                                             # 20
+    (1, 28, 4, 512, 146, "ksplit2x8", 1), (1, 28, 4, 512, 147, "ksplit2x4", 1),                                           # 33 of two tiles
+    (2, 32, 32, 736, 5, "ksplit1x8", 1), (2, 32, 32, 737, 5, "ksplit1x8", 3), (1, 32, 32, 737, 5, "ksplit1x8", 4),        # 24 key tiles
+    (2, 32, 32, 1120, 20, "ksplit1x8", 1), (2, 32, 32, 1121, 16, "ksplit1x8", 3), (1, 32, 32, 1121, 20, "ksplit1x8", 3),  # 36 key tiles
+    (3, 28, 4, 1536, 16, "ksplit1x8", 2), (3, 28, 4, 1536, 18, "ksplit1x8", 2), (3, 28, 4, 1536, 19, "ksplit1x8", 1),     # slices on 12 pairs
+    (5, 32, 32, 1024, 20, "ksplit2x8", 1), (4, 32, 32, 1121, 9, "ksplit1x8", 2), (1, 16, 16, 8192, 9, "ksplit1x8", 15),   # 16 items; long
     (1, 28, 4, 1024, 9, "ksplit1x8", 1), (1, 28, 4, 1025, 9, "ksplit2x8", 2)])                                            # fewer than 8 pairs
 def test_key_split_items_hold_one_query_tile_while_each_has_a_compute_unit(batch, q_heads, kv_heads, seq_len, rows, kernel, splits):
-    """Both sides of each line; slices never make more workgroups than there are compute units, and the records of any call fit the
-    library's static scratch of 4 MiB."""
+    """Both sides of each line, which are counted on the fullest XCD; slices of one-tile items never make more workgroups than it has
+    compute units, and the records of these calls fit the library's static scratch of 4 MiB."""
     from paper_2505_15781_amd import binding as b
     p = attn_plan(D.AttnUpdateShape(batch, q_heads, kv_heads, seq_len, 128, dtype=BF16), rows)
     assert (p.kernel, p.splits) == (kernel, splits)
     if splits > 1 and kernel == "ksplit1x8":
-        assert batch * kv_heads * p.q_groups * p.splits <= 256
+        assert -(-batch * kv_heads // 8) * p.q_groups * p.splits <= 32
     assert b.lib.dkv_attn_update_workspace_bytes(batch, q_heads, kv_heads, seq_len, 128, BF16, rows) <= 4 << 20
