@@ -606,7 +606,7 @@ int attn_update_impl(void *k_cache, void *v_cache, const void *q, const void *k_
                      const int32_t *active_idx, const int32_t *active_off, void *out, int32_t rows,
                      int32_t max_rows_per_seq, int32_t batch, int32_t n_q_heads, int32_t n_kv_heads,
                      int32_t seq_len, int32_t head_dim, int32_t dtype, void *workspace, size_t workspace_bytes,
-                     const char *workspace_name, void *stream) {
+                     bool fit_workspace, void *stream) {
     if (!k_cache || !v_cache || !active_off) { dkv_set_error("null argument"); return DKV_E_INVALID_ARG; }
     if (rows < 0 || batch < 1 || n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads || seq_len < 1 ||
         max_rows_per_seq < 0 || max_rows_per_seq > seq_len || rows > (long)batch * max_rows_per_seq) {
@@ -617,9 +617,10 @@ int attn_update_impl(void *k_cache, void *v_cache, const void *q, const void *k_
     if (rows == 0) return DKV_OK;
     if (!q || !k_new || !v_new || !active_idx || !out) { dkv_set_error("null argument"); return DKV_E_INVALID_ARG; }
     AttnPlan p = dkv_attn_plan(dtype, batch, n_q_heads, n_kv_heads, seq_len, head_dim, max_rows_per_seq);
+    if (fit_workspace) dkv_attn_fit_partials(p, workspace_bytes, batch, n_q_heads, n_kv_heads, seq_len, head_dim);
     size_t need = dkv_attn_partial_bytes(p, batch, n_q_heads, n_kv_heads, head_dim);
     if (need > workspace_bytes || (need && !workspace)) {
-        dkv_set_error("%s has %zu bytes, %zu needed", workspace_name, workspace_bytes, need);
+        dkv_set_error("workspace has %zu bytes, %zu needed", workspace_bytes, need);
         return DKV_E_WORKSPACE_TOO_SMALL;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -642,7 +643,7 @@ extern "C" int dkv_attn_update(void *k_cache, void *v_cache, const void *q, cons
                                size_t workspace_bytes, void *stream) {
     return attn_update_impl(k_cache, v_cache, q, k_new, v_new, active_idx, active_off, out, rows, max_rows_per_seq,
                             batch, n_q_heads, n_kv_heads, seq_len, head_dim, dtype, workspace, workspace_bytes,
-                            "workspace", stream);
+                            false, stream);
 }
 
 // ---- the same operation for callers that cannot allocate ------------------------------------------------
@@ -684,7 +685,7 @@ extern "C" int dkv_attn_update_static(void *k_cache, void *v_cache, const void *
     // the array has to start at zero; contents left by an earlier (larger) call are never read.
     return attn_update_impl(k_cache, v_cache, q, k_new, v_new, active_idx, active_off, out, rows, max_rows_per_seq,
                             batch, n_q_heads, n_kv_heads, seq_len, head_dim, dtype, ws, DKV_STATIC_SCRATCH_BYTES,
-                            "the library's static scratch array", stream);
+                            true, stream);
 }
 
 extern "C" int dkv_concat_reorder(const void *k_cached, const void *v_cached, const void *k_new, const void *v_new,

@@ -398,41 +398,56 @@ AttnPlan dkv_attn_plan(int dtype, int batch, int n_q_heads, int n_kv_heads, int 
         p.tiles_per_split = ceil_div(seq_len, 64);
         return p;
     }
-    // One query tile per item while every item still has a compute unit of its own: the chain of a key tile (scores, softmax,
-    // output) is what a launch with few items waits for, and a second query tile makes it longer. attn_item puts all workgroups
-    // of a pair on XCD pair % 8, so the fullest XCD counts: ceil(pairs / 8) pairs for 32 units. Both measured, us per call,
-    // two tiles / one: 32 pairs, 512 keys, 30 rows 12.9 / 9.5; 96 pairs, 945 keys, 21 query rows 17.8 / 12.7; 4 pairs, 325 keys, 42 query rows
-    // 8.9 / 7.3; 128 pairs (32 items on an XCD), 512 keys, 20 rows 14.1 / 10.7, 1024 keys 20.3 / 16.8. Beyond, two tiles read K/V half as
-    // often: 36 items on an XCD, 512 keys 11.8 / 13.1 (4 wavefronts); 4 pairs of 7 query heads each, 768 keys, 80 rows (35) 13.7 / 18.6;
-    // 12 pairs, 512 keys, 48 rows (42) 11.5 / 16.5. 330 calls whose plan depends on counting the XCD or the chip: 0.94 of the time
-    // of the latter on average, 1.03 at worst.
+    // Key-split kernel: query tiles per item (one or two) and key slices by a small model of the fullest XCD. attn_item puts all
+    // workgroups of a pair on XCD pair % 8, so an XCD has ceil(pairs / 8) pairs and 32 compute units for them, whatever the other
+    // XCDs do. In steps of one key tile and one query tile of a wavefront (about 2 us with 128 dims, half of it with 64):
+    //   a workgroup costs kFixed and the key tiles of a wavefront; a second query tile makes a step half as long again, but the
+    //   items half as many;
+    //   workgroups have 8 wavefronts, one on a compute unit, where all items of an XCD fit at once, otherwise 4 (0.88 of the time of
+    //   8 there, median of 347 plans); items of one tile go up to 64 of those (beyond, two tiles take 0.63-1.1 of the time);
+    //   slices go only into units that would stay idle (where the last one is taken as well: 3 % more), from 24 key tiles of
+    //   128 dims on, with two tiles for each wavefront beyond four slices, and cost a merge launch that reads them all.
+    // Fitted to 1291 calls (1 to 24 sequences, 1 to 64 K/V heads, 40 to 16384 keys, head_dim 64 and 128; up to 21 plans of each
+    // measured, K/V cold): the choice loses 1.2 % on average and 23 % at worst against the best. Lines at numbers of items and of
+    // key tiles before lost where keys are many, which slices of two-tile items then share: 36 pairs, 16384 keys, 64 rows 76.5 us
+    // with two tiles in three slices, 135 with one in one; 8192 keys 45 and 70; 8 pairs of 7 query heads, 8192 keys, 48 rows 41 and 57.
     // Fewer than 8 pairs (XCDs) over more than 1024 keys keep two tiles and the slices that go with them, although one tile is
-    // 8-18 % faster there too: the call that the test of peaked softmax holds to the two-tile kernel with 8 wavefronts lies here.
+    // 8-29 % faster there too: the call that the test of peaked softmax holds to the two-tile kernel with 8 wavefronts lies here.
     const long pairs = (long)batch * n_kv_heads;
-    const int n_tiles = ceil_div(seq_len, KT);
-    const bool few_pairs = pairs < 8 && seq_len > 1024;
     const long per_xcd = (pairs + 7) / 8;
-    p.ksplit_nq = p.q_tiles >= 2 && (few_pairs || per_xcd * p.q_tiles > 32) ? 2 : 1;
-    p.q_groups = ceil_div(p.q_tiles, p.ksplit_nq);
-    const long items = per_xcd * p.q_groups;
-    // 8 wavefronts per workgroup (one workgroup per compute unit) while that still gives every compute
-    // unit at most one; beyond, 4 wavefronts so that two workgroups share a unit
-    p.ksplit_waves = items <= 32 ? 8 : 4;
-    // Keys are sliced over workgroups where the items of an XCD are few and their keys many, never into more workgroups than it has
-    // units (20 items of two query tiles, 1024 keys: one slice 22.0 us, two 30.5; 12 items of one, 1056 keys: two 12.4, three 16.4).
-    // A slice more pays for the merge launch, 3 us, from 24 key tiles of 128 dims on when every item has a pair to itself
-    // (64 pairs, 768 keys 12.9 -> 12.3 us, 1200 keys 17.8 -> 14.6), from 36 when items share a pair, whose K/V the L2 then
-    // holds, or when only two slices fit (32 items on 8 pairs: 29 tiles 10.6 -> 11.0, 38 tiles 12.1 -> 11.5). Four slices
-    // take most of it; three where four would take every unit (8 items, 1700 keys: three 15.8, four 16.6).
+    const int n_tiles = ceil_div(seq_len, KT);
+    constexpr float kFixed = 4.1f, kTwoTiles = 1.48f, kFourWaves = 0.79f, kMerge = 0.81f, kMergeSlice = 0.39f, kFull = 1.035f;
+    const float keys = (head_dim == 64 ? 0.5f : 1.0f) * (float)n_tiles;
+    const int most_slices = n_tiles * head_dim < 24 * 128 ? 1 : n_tiles / 16 > 4 ? n_tiles / 16 : 4;
+    const bool few_pairs = pairs < 8 && seq_len > 1024;
+    float best = 0.f;
     int s = 1;
     if (few_pairs) {
+        p.ksplit_nq = p.q_tiles >= 2 ? 2 : 1;
+        p.q_groups = ceil_div(p.q_tiles, p.ksplit_nq);
+        p.ksplit_waves = per_xcd * p.q_groups <= 32 ? 8 : 4;
         const long all = pairs * p.q_groups;
         s = all < 192 ? (int)((384 + all - 1) / all) : 1;
         if (s > n_tiles / 16) s = n_tiles / 16;             // two tiles per wavefront
-    } else if (items <= 16 && (long)n_tiles * head_dim >= 128L * (p.q_tiles > 1 || items > 12 ? 36 : 24)) {
-        s = n_tiles / 16 > 4 ? n_tiles / 16 : 4;
-        if (s > 32 / items) s = (int)(32 / items);
-        if (s > 2 && s * items == 32) --s;
+    }
+    for (int nq = 1; !few_pairs && nq <= 2 && nq <= p.q_tiles; ++nq) {
+        const int groups = ceil_div(p.q_tiles, nq);
+        const long items = per_xcd * groups;
+        if (nq == 1 && items > 64 && p.q_tiles > 1) continue;
+        const int waves = items <= 32 ? 8 : 4;
+        const float chain = (nq == 2 ? kTwoTiles : 1.0f) * (waves == 8 ? 1.0f : kFourWaves) * keys / (float)waves;
+        for (int slices = 1; slices == 1 || (slices <= most_slices && slices * items <= 32); ++slices) {
+            float t = kFixed + chain / (float)slices;
+            if (slices > 1) t += kMerge + kMergeSlice * (float)slices;
+            if (slices > 1 && slices * items == 32) t *= kFull;
+            if (best == 0.f || t < best) {
+                best = t;
+                s = slices;
+                p.ksplit_nq = nq;
+                p.q_groups = groups;
+                p.ksplit_waves = waves;
+            }
+        }
     }
     p.tiles_per_split = ceil_div(n_tiles, s);
     p.splits = ceil_div(n_tiles, p.tiles_per_split);
@@ -445,6 +460,15 @@ size_t dkv_attn_partial_bytes(const AttnPlan &p, int batch, int n_q_heads, int n
     // rows per sequence are at most q_tiles*16/G (rounded up); records are indexed by (row, head, split)
     size_t rows = (size_t)batch * (size_t)ceil_div(p.q_tiles * 16, G);
     return rows * n_q_heads * p.splits * (size_t)(head_dim + 4) * sizeof(float);
+}
+
+void dkv_attn_fit_partials(AttnPlan &p, size_t bytes, int batch, int n_q_heads, int n_kv_heads, int seq_len, int head_dim) {
+    if (!p.use_mfma || p.splits == 1) return;
+    const size_t fit = bytes / (dkv_attn_partial_bytes(p, batch, n_q_heads, n_kv_heads, head_dim) / p.splits);
+    if (fit >= (size_t)p.splits) return;
+    const int n_tiles = ceil_div(seq_len, KT);
+    p.tiles_per_split = fit ? ceil_div(n_tiles, (int)fit) : n_tiles;
+    p.splits = ceil_div(n_tiles, p.tiles_per_split);
 }
 
 int dkv_attn_can_fuse_update(const AttnPlan &plan, int max_rows_per_seq) {

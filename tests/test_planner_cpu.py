@@ -80,11 +80,13 @@ def test_every_attention_kernel_is_planned_where_its_measurements_say():
     (3, 28, 4, 512, 36, "ksplit1x8", 1), (3, 28, 4, 512, 37, "ksplit2x8", 1),                                             # 12
     (5, 28, 4, 512, 22, "ksplit1x8", 1), (5, 28, 4, 512, 23, "ksplit2x8", 1),                                             # 20
     (1, 28, 4, 512, 146, "ksplit2x8", 1), (1, 28, 4, 512, 147, "ksplit2x4", 1),                                           # 33 of two tiles
-    (2, 32, 32, 736, 5, "ksplit1x8", 1), (2, 32, 32, 737, 5, "ksplit1x8", 3), (1, 32, 32, 737, 5, "ksplit1x8", 4),        # 24 key tiles
-    (2, 32, 32, 1120, 20, "ksplit1x8", 1), (2, 32, 32, 1121, 16, "ksplit1x8", 3), (1, 32, 32, 1121, 20, "ksplit1x8", 3),  # 36 key tiles
-    (3, 28, 4, 1536, 16, "ksplit1x8", 2), (3, 28, 4, 1536, 18, "ksplit1x8", 2), (3, 28, 4, 1536, 19, "ksplit1x8", 1),     # slices on 12 pairs
-    (5, 32, 32, 1024, 20, "ksplit2x8", 1), (4, 32, 32, 1121, 9, "ksplit1x8", 2), (1, 16, 16, 8192, 9, "ksplit1x8", 15),   # 16 items; long
-    (1, 28, 4, 1024, 9, "ksplit1x8", 1), (1, 28, 4, 1025, 9, "ksplit2x8", 2)])                                            # fewer than 8 pairs
+    (2, 32, 32, 736, 5, "ksplit1x8", 1), (2, 32, 32, 737, 5, "ksplit1x8", 3), (1, 32, 32, 737, 5, "ksplit1x8", 3),        # 24 key tiles
+    (2, 32, 32, 1120, 20, "ksplit1x8", 2), (2, 32, 32, 1121, 16, "ksplit1x8", 3), (1, 32, 32, 1121, 20, "ksplit1x8", 3),
+    (3, 28, 4, 1536, 16, "ksplit1x8", 2), (3, 28, 4, 1536, 19, "ksplit2x8", 3),                                           # slices on 12 pairs
+    (5, 32, 32, 1024, 20, "ksplit2x8", 1), (4, 32, 32, 1121, 9, "ksplit1x8", 2), (1, 16, 16, 8192, 9, "ksplit1x8", 9),    # 16 items; long
+    (3, 12, 12, 8192, 64, "ksplit2x8", 3), (2, 28, 4, 8192, 48, "ksplit2x8", 2), (8, 28, 4, 16384, 16, "ksplit2x8", 2),   # two tiles, slices
+    (20, 16, 16, 150, 40, "ksplit2x4", 1), (21, 8, 8, 200, 40, "ksplit1x4", 1), (22, 8, 8, 200, 40, "ksplit2x4", 1),        # 64 of 4 wavefronts
+    (1, 28, 4, 1024, 9, "ksplit1x8", 3), (1, 28, 4, 1025, 9, "ksplit2x8", 2)])                                            # fewer than 8 pairs
 def test_key_split_items_hold_one_query_tile_while_each_has_a_compute_unit(batch, q_heads, kv_heads, seq_len, rows, kernel, splits):
     """Both sides of each line, which are counted on the fullest XCD; slices of one-tile items never make more workgroups than it has
     compute units, and the records of these calls fit the library's static scratch of 4 MiB."""
