@@ -410,27 +410,18 @@ AttnPlan dkv_attn_plan(int dtype, int batch, int n_q_heads, int n_kv_heads, int 
     // Fitted to 1291 calls (1 to 24 sequences, 1 to 64 K/V heads, 40 to 16384 keys, head_dim 64 and 128; up to 21 plans of each
     // measured, K/V cold): the choice loses 1.2 % on average and 23 % at worst against the best. Lines at numbers of items and of
     // key tiles before lost where keys are many, which slices of two-tile items then share: 36 pairs, 16384 keys, 64 rows 76.5 us
-    // with two tiles in three slices, 135 with one in one; 8192 keys 45 and 70; 8 pairs of 7 query heads, 8192 keys, 48 rows 41 and 57.
-    // Fewer than 8 pairs (XCDs) over more than 1024 keys keep two tiles and the slices that go with them, although one tile is
-    // 8-29 % faster there too: the call that the test of peaked softmax holds to the two-tile kernel with 8 wavefronts lies here.
+    // with two tiles in three slices, 135 with one in one; 8192 keys 45 and 70; 8 pairs of 7 query heads, 8192 keys, 48 rows 41 and 57;
+    // and on few pairs, where two tiles were taken beyond 1024 keys: 4 pairs of 7 query heads, 1536 keys, 20 rows 12.5 us with one
+    // tile in three slices, 14.5 with two; 64 rows 16.6 with one in one, 24.5 with two in three.
     const long pairs = (long)batch * n_kv_heads;
     const long per_xcd = (pairs + 7) / 8;
     const int n_tiles = ceil_div(seq_len, KT);
     constexpr float kFixed = 4.1f, kTwoTiles = 1.48f, kFourWaves = 0.79f, kMerge = 0.81f, kMergeSlice = 0.39f, kFull = 1.035f;
     const float keys = (head_dim == 64 ? 0.5f : 1.0f) * (float)n_tiles;
     const int most_slices = n_tiles * head_dim < 24 * 128 ? 1 : n_tiles / 16 > 4 ? n_tiles / 16 : 4;
-    const bool few_pairs = pairs < 8 && seq_len > 1024;
     float best = 0.f;
     int s = 1;
-    if (few_pairs) {
-        p.ksplit_nq = p.q_tiles >= 2 ? 2 : 1;
-        p.q_groups = ceil_div(p.q_tiles, p.ksplit_nq);
-        p.ksplit_waves = per_xcd * p.q_groups <= 32 ? 8 : 4;
-        const long all = pairs * p.q_groups;
-        s = all < 192 ? (int)((384 + all - 1) / all) : 1;
-        if (s > n_tiles / 16) s = n_tiles / 16;             // two tiles per wavefront
-    }
-    for (int nq = 1; !few_pairs && nq <= 2 && nq <= p.q_tiles; ++nq) {
+    for (int nq = 1; nq <= 2 && nq <= p.q_tiles; ++nq) {
         const int groups = ceil_div(p.q_tiles, nq);
         const long items = per_xcd * groups;
         if (nq == 1 && items > 64 && p.q_tiles > 1) continue;

@@ -328,10 +328,12 @@ def test_projection_kernel_rejects_shapes_it_cannot_take():
 
 
 def _attn_case(shape, n_active, seed, ragged=None, q_scale=1.0, kernel=None):
-    """`kernel`: the route that the case is there for (a changed dispatch must not leave a kernel without its tests)."""
+    """`kernel`: the route that the case is there for (a changed dispatch must not leave a kernel without its tests), with the
+    number of key slices behind a slash where that counts."""
     import paper_2505_15781_amd as P
     if kernel:
-        assert attn_plan(shape, n_active if ragged is None else max(ragged)).kernel == kernel
+        p = attn_plan(shape, n_active if ragged is None else max(ragged))
+        assert (f"{p.kernel}/{p.splits}" if "/" in kernel else p.kernel) == kernel
     c = D.attn_update_case(shape, n_active, seed, ragged=ragged)
     c["q"] = c["q"] * np.float32(q_scale)            # a power of two: still exact bfloat16 values
     dt = shape.dtype
@@ -451,10 +453,14 @@ def test_attention_many_small_items(dh):
 def test_attention_peaked_and_flat_softmax(q_scale):
     """Scores with a standard deviation of 16 (after the 1/sqrt(d_h)): almost one-hot probabilities, running maxima
     that keep rising over the key tiles and rescale the output; and all-zero queries: every key weighs the same, the
-    output is the mean of V. Through every kernel: key-split with 8 and 4 wavefronts, wide query blocks, both forms of the
-    shared tiles, generic."""
+    output is the mean of V. Through every kernel: key-split with 8 and 4 wavefronts and one and two query tiles per item, sliced and
+    not, wide query blocks, both forms of the shared tiles, generic."""
     for shape, n, seed, ragged, kernel in [
-            (D.AttnUpdateShape(batch=2, n_q_heads=4, n_kv_heads=2, seq_len=1031, head_dim=128, dtype=BF16), None, 46, [3, 40], "ksplit2x8"),
+            (D.AttnUpdateShape(batch=2, n_q_heads=4, n_kv_heads=2, seq_len=1031, head_dim=128, dtype=BF16), None, 46, [3, 40], "ksplit1x8/3"),
+            (D.AttnUpdateShape(batch=4, n_q_heads=8, n_kv_heads=4, seq_len=2053, head_dim=128, dtype=BF16), None, 62, [45, 0, 3, 17], "ksplit2x8/4"),
+            (D.AttnUpdateShape(batch=4, n_q_heads=32, n_kv_heads=32, seq_len=300, head_dim=128, dtype=BF16), None, 63, [3, 40, 0, 33], "ksplit2x8/1"),
+            (D.AttnUpdateShape(batch=5, n_q_heads=16, n_kv_heads=16, seq_len=150, head_dim=128, dtype=BF16), None, 64, [3, 40, 0, 33, 16], "ksplit1x8/1"),
+            (D.AttnUpdateShape(batch=21, n_q_heads=8, n_kv_heads=8, seq_len=150, head_dim=128, dtype=BF16), 40, 65, None, "ksplit1x4"),
             (D.AttnUpdateShape(batch=20, n_q_heads=16, n_kv_heads=16, seq_len=150, head_dim=128, dtype=BF16), 40, 50, None, "ksplit2x4"),
             (D.AttnUpdateShape(batch=4, n_q_heads=128, n_kv_heads=16, seq_len=300, head_dim=128, dtype=BF16), 79, 47, None, "wide"),
             (D.AttnUpdateShape(batch=16, n_q_heads=128, n_kv_heads=16, seq_len=200, head_dim=128, dtype=BF16), 66, 48, None, "wide"),

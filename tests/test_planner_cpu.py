@@ -86,13 +86,32 @@ def test_every_attention_kernel_is_planned_where_its_measurements_say():
     (5, 32, 32, 1024, 20, "ksplit2x8", 1), (4, 32, 32, 1121, 9, "ksplit1x8", 2), (1, 16, 16, 8192, 9, "ksplit1x8", 9),    # 16 items; long
     (3, 12, 12, 8192, 64, "ksplit2x8", 3), (2, 28, 4, 8192, 48, "ksplit2x8", 2), (8, 28, 4, 16384, 16, "ksplit2x8", 2),   # two tiles, slices
     (20, 16, 16, 150, 40, "ksplit2x4", 1), (21, 8, 8, 200, 40, "ksplit1x4", 1), (22, 8, 8, 200, 40, "ksplit2x4", 1),        # 64 of 4 wavefronts
-    (1, 28, 4, 1024, 9, "ksplit1x8", 3), (1, 28, 4, 1025, 9, "ksplit2x8", 2)])                                            # fewer than 8 pairs
+    (1, 28, 4, 1024, 9, "ksplit1x8", 3), (1, 28, 4, 1025, 9, "ksplit1x8", 3), (1, 28, 4, 1536, 64, "ksplit1x8", 1)])      # fewer than 8 pairs
 def test_key_split_items_hold_one_query_tile_while_each_has_a_compute_unit(batch, q_heads, kv_heads, seq_len, rows, kernel, splits):
-    """Both sides of each line, which are counted on the fullest XCD; slices of one-tile items never make more workgroups than it has
-    compute units, and the records of these calls fit the library's static scratch of 4 MiB."""
-    from paper_2505_15781_amd import binding as b
+    """Both sides of each line, which are counted on the fullest XCD."""
     p = attn_plan(D.AttnUpdateShape(batch, q_heads, kv_heads, seq_len, 128, dtype=BF16), rows)
     assert (p.kernel, p.splits) == (kernel, splits)
-    if splits > 1 and kernel == "ksplit1x8":
-        assert -(-batch * kv_heads // 8) * p.q_groups * p.splits <= 32
-    assert b.lib.dkv_attn_update_workspace_bytes(batch, q_heads, kv_heads, seq_len, 128, BF16, rows) <= 4 << 20
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_key_slices_only_go_into_idle_compute_units(head_dim):
+    """Over the range of the calls: sliced plans make no more workgroups than an XCD has units, no slice is empty, the wavefronts
+    fit the number of items, and 1024 keys are no line for few pairs."""
+    sliced = 0
+    for batch in (1, 2, 3, 5, 8, 13, 16):
+        for q_heads, kv_heads in ((32, 32), (28, 4), (24, 8), (8, 1), (12, 12)):
+            per_xcd = -(-batch * kv_heads // 8)
+            for seq_len in (33, 512, 767, 769, 1024, 1025, 1536, 2049, 4096, 16384, 60000):
+                for rows in (1, 2, 5, 9, 16, 17, 33, 64, 65, 100, 146, 147, 400):
+                    p = attn_plan(D.AttnUpdateShape(batch, q_heads, kv_heads, seq_len, head_dim, dtype=BF16), min(rows, seq_len))
+                    if not p.ksplit_nq:
+                        continue
+                    assert p.q_groups == -(-p.q_tiles // p.ksplit_nq) and (p.ksplit_waves == 8) == (per_xcd * p.q_groups <= 32)
+                    tiles = -(-seq_len // 32)
+                    assert (p.splits - 1) * p.tiles_per_split < tiles <= p.splits * p.tiles_per_split
+                    if p.splits > 1:
+                        sliced += 1
+                        assert per_xcd * p.q_groups * p.splits <= 32 and tiles * head_dim >= 24 * 128
+    assert sliced > 500
+    small, large = (attn_plan(D.AttnUpdateShape(1, 28, 4, n, 128, dtype=BF16), 64) for n in (1024, 1025))
+    assert (small.kernel, small.splits) == (large.kernel, large.splits)
