@@ -72,10 +72,10 @@ Layout make_layout(const dkv_model_desc &m, const dkv_run_desc &r) {
     // partial-sum buffer: worst case over every row count a step can have
     size_t pf = 0;
     for (int rows = 1; rows <= y.rows_cap; ++rows) {
-        GemmPlan p1 = dkv_gemm_plan(m.dtype, rows, nqkv, m.d_model);
-        GemmPlan p2 = dkv_gemm_plan(m.dtype, rows, m.d_model, qn);
+        GemmPlan p1 = dkv_gemm_plan(m.dtype, rows, nqkv, m.d_model, SLICES_PRODUCT);
+        GemmPlan p2 = dkv_gemm_plan(m.dtype, rows, m.d_model, qn, SLICES_PRODUCT);
         GemmPlan p3 = dkv_gemm_plan(m.dtype, rows, 2 * m.d_ffn, m.d_model);
-        GemmPlan p4 = dkv_gemm_plan(m.dtype, rows, m.d_model, m.d_ffn);
+        GemmPlan p4 = dkv_gemm_plan(m.dtype, rows, m.d_model, m.d_ffn, SLICES_PRODUCT);
         size_t a = (size_t)p1.split_k * rows * nqkv, b = (size_t)p2.split_k * rows * m.d_model,
                c = (size_t)p3.split_k * rows * 2 * m.d_ffn, d = (size_t)p4.split_k * rows * m.d_model;
         if (dkv_gemm_can_fuse_swiglu(m.dtype, 2 * m.d_ffn, m.d_model, p3)) c = 0;   // SwiGLU in the epilogue: no fp32 product
@@ -397,7 +397,7 @@ extern "C" int dkv_denoise_step(dkv_ctx *c, int32_t step, const int32_t *forced_
         if ((rc = capture(l))) return rc;
         char *Kl = static_cast<char *>(c->buf.k_cache) + layer_elems * c->es * l;
         char *Vl = static_cast<char *>(c->buf.v_cache) + layer_elems * c->es * l;
-        GemmPlan p = dkv_gemm_plan(dt, rows, nqkv, d);
+        GemmPlan p = dkv_gemm_plan(dt, rows, nqkv, d, SLICES_PRODUCT);
         if ((rc = timed_gemm(c, c->a, c->wqkv[l], c->part, rows, n_rows, nqkv, d, p))) return rc;
         if ((rc = dkv_launch_rope_scatter(dt, s, rows, c->part, p.split_k, (size_t)rows * nqkv, c->row_pos, c->row_seq,
                                           c->counts, reinterpret_cast<const float *>(c->rope), c->q, Kl, Vl,
@@ -410,7 +410,7 @@ extern "C" int dkv_denoise_step(dkv_ctx *c, int32_t step, const int32_t *forced_
                                                    AttnFusedUpdate{nullptr, nullptr, nullptr}, s);
                    });
         if (rc) return rc;
-        p = dkv_gemm_plan(dt, rows, d, qn);
+        p = dkv_gemm_plan(dt, rows, d, qn, SLICES_PRODUCT);
         if ((rc = timed_gemm(c, c->attn_out, c->wo[l], c->part, rows, n_rows, d, qn, p))) return rc;
         if ((rc = dkv_launch_residual_norm(dt, s, rows, d, c->part, p.split_k, (size_t)rows * d, c->counts, c->n2[l],
                                            c->h, c->a, m.rms_eps))) return rc;
@@ -429,7 +429,7 @@ extern "C" int dkv_denoise_step(dkv_ctx *c, int32_t step, const int32_t *forced_
             if ((rc = timed_gemm(c, c->a, c->wgu[l], c->part, rows, n_rows, 2 * m.d_ffn, d, p))) return rc;
             if ((rc = dkv_launch_swiglu(dt, s, rows, c->part, p.split_k, (size_t)rows * 2 * m.d_ffn, c->counts, c->f, m.d_ffn))) return rc;
         }
-        p = dkv_gemm_plan(dt, rows, d, m.d_ffn);
+        p = dkv_gemm_plan(dt, rows, d, m.d_ffn, SLICES_PRODUCT);
         if ((rc = timed_gemm(c, c->f, c->wdown[l], c->part, rows, n_rows, d, m.d_ffn, p))) return rc;
         const float *next_gain = (l + 1 < m.n_layers) ? c->n1[l + 1] : c->final_norm;
         if ((rc = dkv_launch_residual_norm(dt, s, rows, d, c->part, p.split_k, (size_t)rows * d, c->counts, next_gain,

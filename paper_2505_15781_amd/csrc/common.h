@@ -113,9 +113,10 @@ struct GemmPlan {
     int frac_units; // 0, or K tiles per workgroup when workgroups take 3/4 of a tile's K range each
     int flags;     // GEMM_FLAG_* launch options of the gemm_dma kinds
 };
-// Who adds up the K slices of a product: the row kernel that reads it anyway; nobody, K is not split (products whose epilogue
-// needs whole sums: the vocabulary statistics); a launch that is made only for it (the projection on its own).
-enum { SLICES_CONSUMER = 0, SLICES_NONE, SLICES_LAUNCH };
+// Who adds up the K slices of a product: the row kernel that reads it anyway, or with one slice the SwiGLU epilogue; nobody, K is not
+// split (products whose epilogue needs whole sums: the vocabulary statistics); a launch that is made only for it (the projection
+// on its own); the row kernel that reads the fp32 product of any number of slices.
+enum { SLICES_CONSUMER = 0, SLICES_NONE, SLICES_LAUNCH, SLICES_PRODUCT };
 GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to = SLICES_CONSUMER);
 int dkv_gemm_plan_valid(int dtype, int k, GemmPlan p);
 

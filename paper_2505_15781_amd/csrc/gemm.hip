@@ -202,19 +202,22 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
     //   unit, 14.5 TB/s over all workgroups in flight) and its MFMAs (5.7 TFLOP/s per compute unit);
     //   a workgroup of the 8-wavefront tiles needs the times of kPingPong, alone and with the whole chip at work;
     //   128x256 tiles have no second workgroup on the compute unit that would work in a round's first fills and epilogue, and
-    //   lose that time with every further round;
+    //   lose that time with every further round where the epilogue computes (SwiGLU, vocabulary statistics); one that only stores
+    //   the fp32 product is shorter with them than with the 8-wavefront tiles (24576 x 4096 at 640 rows, 128x256 / 192x256 tiles: SwiGLU 150 /
+    //   144 us, product 139 / 160; 37888 x 3584 at 384 rows 148 / 136 and 145 / 152);
     //   workgroups run in rounds of 256 (one per compute unit), a partly filled round costs a full one;
     //   no launch beats streaming its operands and results once;
     //   every further K slice adds the write and re-read of its partial sums by the consumer; a reduction of its own also
     //   reads the first slice and is a launch more (fitted with dkv_gemm over 12 shapes at 8 to 5000 rows: mean loss 1.3 %;
     //   charged like the consumer's, 400 x 4608 x 3584 took 36.6 us in 4 slices against 29.2 in one).
     // The times of 256x256 tiles and of a further round of 128x256 tiles are those of a chip that has been busy for 12 ms and
-    // more, as it is inside a step (261 shapes and row counts of 65 to 8192, launches with their consumers: mean loss 1.4 %
-    // with the constants of single launches, 1.0 % with these; what is planned differently: 37888 x 3584 at 257 to 384 rows,
-    // 192x256 for 128x256 tiles, 148 -> 133-140 us; 24576 x 4096 at 513 to 640 rows, the same, 151 -> 148; 4096 x 12288 at 410
-    // to 512 rows, 256x256 in 6 slices for 128x256 in 4, 72 -> 66; 3584 x 18944 at 480 to 512 rows, 256x256 in 8 slices for
-    // 256x192 in 6, 88 -> 84; 152064 x 3584 at 65 to 128 candidates, 192x256 for 128x256, level; no other plan
-    // of fewer than 257 rows).
+    // more, as it is inside a step. Against the constants of single launches, over 1440 launches (27 layer shapes, 65 to 6144 rows; stored
+    // products with and without a reduction of their own, SwiGLU): 0.999 of the time on average. Planned differently are 37888 x
+    // 3584 at 257 to 384 rows with SwiGLU, 192x256 for 128x256 tiles, 148 -> 133-140 us; 24576 x 4096 at 513 to 640 rows, the same,
+    // 150 -> 144; 4096 x 12288 at 410 to 512 rows, 256x256 in 6 slices for 128x256 in 4, 70 -> 67; 24576 x 4096 at 3072 rows, 256x256 for
+    // 192x256, 506 -> 489; 152064 x 3584 at 65 to 128 candidates, 192x256 for 128x256, level; and, the one that loses more than
+    // 3 %, 8192 x 8192 at 413 to 512 rows, 256x256 in 3 slices for 4, 76 -> 84 (rows 16 KB apart; a time that repairs it takes the gain
+    // of 4096 x 12288 away).
     // Tiles of 96 and 192 columns or rows exist because 12288 / 96 = 128 and 24576 / 192 = 128 column tiles make
     // exactly one or two full rounds where 128- and 256-column tiles leave a quarter of the chip idle, and 129..192 or
     // 257..384 rows fill one or two 192-row tiles (320 rows of the 8B vocabulary: 821 -> 393 us).
@@ -229,6 +232,7 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
     constexpr PingPong kPingPong[] = {{}, {}, {}, {}, {1.130, 1.290}, {}, {}, {1.041, 1.092}, {0.980, 1.078}};
     static_assert(GEMM_DMA_256x256 == 4 && GEMM_DMA_256x192 == 7 && GEMM_DMA_192x256 == 8 && GEMM_DMA_LAST == 8, "order of kPingPong");
     const int kt_total = k / BK;
+    const bool stored = slices_go_to == SLICES_LAUNCH || slices_go_to == SLICES_PRODUCT;        // in one slice too
     struct { int s, nk; } slices[6];       // K slices worth trying, K tiles of each
     int n_slices = 0;
     for (int s : {1, 2, 3, 4, 6, 8}) {
@@ -260,7 +264,7 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
                 t_rounds = rounds * (all > t_cu ? all : t_cu);
             }
             double t = slices[i].nk * t_rounds + rounds * (eight ? kPipeFill8 : kPipeFill);
-            if (kind == GEMM_DMA_128x256) t += (rounds - 1) * kNextRound128x256;
+            if (kind == GEMM_DMA_128x256 && !stored) t += (rounds - 1) * kNextRound128x256;
             const double stream = (operands + s * product) * kPerStream;
             if (stream > t) t = stream;
             t += kLaunch;
@@ -278,7 +282,7 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
     // over the plan without them: 7-20 % where the tiles make whole rounds of a long K (24576 x 4096, 22016 x 4096,
     // 3584 x 18944, 4096 x 12288), nothing where K is short (4096 x 4096: 1.06-1.11 of the time) or the rounds do not fit
     // (37888 x 3584: 1.13-1.21). With up to 128 rows the 128-row tiles are level (24576 x 4096 at 128 rows 43.3 against 51.6 us).
-    if (slices_go_to == SLICES_CONSUMER && m_upper > 128 && m_upper <= 256) {
+    if ((slices_go_to == SLICES_CONSUMER || slices_go_to == SLICES_PRODUCT) && m_upper > 128 && m_upper <= 256) {
         struct Stream { int kind, bn; double alone, full; };                                    // us per K tile
         constexpr Stream kStream[] = {{GEMM_STREAM_256x96, 96, 0.52, 0.56}, {GEMM_STREAM_256x64, 64, 0.44, 0.44}};
         constexpr double kPipeFillStream = 6.5;

@@ -21,11 +21,11 @@ class GemmPlan(C.Structure):
         return rows, rows * -(-n // bn) * self.split_k
 
 
-CONSUMER, ONE_SLICE, OWN_LAUNCH = 0, 1, 2          # who adds the K slices up
+CONSUMER, ONE_SLICE, OWN_LAUNCH, PRODUCT = 0, 1, 2, 3          # who adds the K slices up
 
 
 def gemm_plan(m, n, k, slices_go_to=CONSUMER, dtype=0):
-    """The plan of a projection inside a step; OWN_LAUNCH: of dkv_gemm."""
+    """The plan of the gate / up projection inside a step; PRODUCT: of one whose fp32 product is stored; OWN_LAUNCH: of dkv_gemm."""
     from paper_2505_15781_amd import binding
     f = binding.lib._Z13dkv_gemm_planiiiii
     f.restype, f.argtypes = GemmPlan, [C.c_int] * 5

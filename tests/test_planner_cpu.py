@@ -4,7 +4,7 @@ import pytest
 import dkv_inputs as D
 from dkv_inputs.configs import BF16
 
-from plans import CONSUMER, EIGHT_WAVEFRONTS, ONE_SLICE, OWN_LAUNCH, STREAM_TILES, STREAM_W, attn_plan, gemm_plan
+from plans import CONSUMER, EIGHT_WAVEFRONTS, ONE_SLICE, OWN_LAUNCH, PRODUCT, STREAM_TILES, STREAM_W, attn_plan, gemm_plan
 
 
 @pytest.mark.parametrize("m,n,k", [(2049, 512, 4096), (4096, 512, 4096), (2304, 3584, 18944), (3072, 1024, 8192), (5000, 1024, 4096)])
@@ -25,6 +25,14 @@ def test_k_is_not_sliced_where_the_tiles_fill_the_chip(m, n, k):
 def test_128x256_tiles_are_planned_for_one_round(m, n, k, tile):
     """A second round of them (444 and 480 workgroups) costs more than its K tiles; one round (240) is theirs."""
     assert gemm_plan(m, n, k).tile == tile
+
+
+@pytest.mark.parametrize("m,n,k,tile", [(384, 37888, 3584, "dma_128x256"), (640, 24576, 4096, "dma_128x256"), (600, 22016, 4096, "dma_128x256"),
+                                        (640, 24576, 8192, "dma_128x256"), (800, 18432, 6144, "dma_128x256"), (400, 37888, 3584, "dma_192x256")])
+def test_a_further_round_of_128x256_tiles_is_cheap_where_the_product_is_stored(m, n, k, tile):
+    """The charge of the test above is for epilogues that compute: dkv_gemm and the projections whose fp32 product a row kernel
+    reads keep these tiles in their second round, up to the line where a third begins."""
+    assert gemm_plan(m, n, k, OWN_LAUNCH).tile == tile and gemm_plan(m, n, k, PRODUCT).tile == tile
 
 
 @pytest.mark.parametrize("m,n,k", [(400, 4608, 3584), (700, 4608, 3584), (1024, 4608, 3584), (400, 12288, 4096)])
@@ -57,6 +65,7 @@ def test_one_row_of_wide_tiles_is_planned_up_to_256_rows_inside_a_step():
     for n, k in [(24576, 4096), (3584, 18944), (4096, 12288)]:
         assert gemm_plan(128, n, k).kind not in stream and gemm_plan(257, n, k).kind not in stream
         assert gemm_plan(160, n, k).kind in stream and gemm_plan(256, n, k).kind in stream
+        assert gemm_plan(256, n, k, PRODUCT).kind in stream and gemm_plan(257, n, k, PRODUCT).kind not in stream
         assert gemm_plan(256, n, k, OWN_LAUNCH).kind not in stream and gemm_plan(256, n, k, ONE_SLICE).kind not in stream
     for n, k in [(37888, 3584), (4096, 4096), (3584, 3584), (1024, 8192)]:
         assert all(gemm_plan(m, n, k).kind not in stream for m in range(129, 257)), (n, k)
