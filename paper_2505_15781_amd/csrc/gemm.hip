@@ -240,7 +240,7 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
         if (s == 1 || (slices_go_to != SLICES_NONE && nk >= 8 && ceil_div(kt_total, nk) == s)) slices[n_slices++] = {s, nk};
     }
     const double product = 4.0 * m_upper * (double)n, operands = 2.0 * n * k + 2.0 * m_upper * (double)k;
-    double best = 0.0;
+    double best = 0.0, best_work = 0.0;
     p.kind = -1;
     for (int kind = 0; kind <= GEMM_DMA_LAST; ++kind) {
         const KindInfo &ki = kKinds[kind];
@@ -265,12 +265,13 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
             }
             double t = slices[i].nk * t_rounds + rounds * (eight ? kPipeFill8 : kPipeFill);
             if (kind == GEMM_DMA_128x256 && !stored) t += (rounds - 1) * kNextRound128x256;
-            const double stream = (operands + s * product) * kPerStream;
+            const double stream = (operands + s * product) * kPerStream, work = t;
             if (stream > t) t = stream;
             t += kLaunch;
             if (s > 1) t += (s - (slices_go_to == SLICES_LAUNCH ? 0 : 1)) * product * kPerReduce + kReduceFixed;
-            if (p.kind < 0 || t < best) {
+            if (p.kind < 0 || t < best || (t == best && work < best_work)) {      // level where only the stream counts: less work
                 best = t;
+                best_work = work;
                 p.kind = kind;
                 p.split_k = s;
             }

@@ -35,6 +35,13 @@ def test_a_further_round_of_128x256_tiles_is_cheap_where_the_product_is_stored(m
     assert gemm_plan(m, n, k, OWN_LAUNCH).tile == tile and gemm_plan(m, n, k, PRODUCT).tile == tile
 
 
+@pytest.mark.parametrize("m,n,k", [(191, 32000, 3584), (191, 28672, 3584), (137, 28672, 2048)])
+def test_of_two_plans_that_only_stream_the_one_with_less_work_is_taken(m, n, k):
+    """Two slices of 192x256 and of 256x256 tiles, both as fast as the operands come: no padding to 256 rows."""
+    p = gemm_plan(m, n, k)
+    assert p.tile == "dma_192x256" and p.split_k == 2
+
+
 @pytest.mark.parametrize("m,n,k", [(400, 4608, 3584), (700, 4608, 3584), (1024, 4608, 3584), (400, 12288, 4096)])
 def test_a_projection_on_its_own_pays_for_the_reduction_of_its_slices(m, n, k):
     """dkv_gemm adds the slices up in a launch of its own, a step's row kernel while it reads the product: where the slices
