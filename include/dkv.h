@@ -209,11 +209,12 @@ int dkv_destroy(dkv_ctx *ctx);
 #define DKV_GEMM_DMA_128x192  6
 #define DKV_GEMM_DMA_256x192  7
 #define DKV_GEMM_DMA_192x256  8
-#define DKV_GEMM_REG_64x128   9   /* bf16 with K not a multiple of 64; in a profile also the 256-row tiles that
-                                     the library plans by itself for 129 to 256 rows, K a multiple of 64 */
+#define DKV_GEMM_REG_64x128   9   /* bf16 with K not a multiple of 64 */
 #define DKV_GEMM_SIMT         10  /* fp32 mode / generic */
 #define DKV_PROF_ATTN         11  /* attention (including the key-slice merge when it runs) */
-#define DKV_PROF_KINDS        12
+#define DKV_PROF_STREAM       12  /* projection kernels without a number of their own: the 256-row tiles that the library
+                                     plans by itself for 129 to 256 rows inside a step */
+#define DKV_PROF_KINDS        13
 typedef struct {
     int64_t launches;
     double ms, bytes, flops;

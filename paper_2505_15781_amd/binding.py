@@ -64,12 +64,13 @@ class ProfEntry(C.Structure):
 
 
 # kernel kinds of the profile report; the tile kernels are named as in a rocprofv3 trace, `*` standing for the epilogue
-# (0 fp32 product, 1 fused SwiGLU, 2 vocabulary statistics), which the report does not tell apart
-PROF_KINDS = ("gemm_dma<*,1,1,1,4,4>", "gemm_dma<*,2,1,1,4,4>", "gemm_dma<*,2,2,2,2,3>", "gemm_dma<*,2,4,2,2,3>",
+# (0 fp32 product, 1 fused SwiGLU, 2 vocabulary statistics), which the report does not tell apart; 64x128 tiles have other
+# wavefronts and stages with the vocabulary statistics
+PROF_KINDS = ("gemm_dma<*,1,1,1,4,4>", "gemm_dma<*,2,1,1,4,4>, gemm_dma<2,1,2,2,2,3>", "gemm_dma<*,2,2,2,2,3>", "gemm_dma<*,2,4,2,2,3>",
               "gemm_dma<*,4,2,2,4,2>", "gemm_dma<*,1,3,4,1,4>", "gemm_dma<*,2,3,2,2,3>", "gemm_dma<*,2,3,4,2,2>",
-              "gemm_dma<*,3,2,2,4,2>", "gemm_stream, gemm_reg",
+              "gemm_dma<*,3,2,2,4,2>", "gemm_reg",
               "gemm_simt",
-              "attention")
+              "attention", "gemm_stream")
 GEMM_KINDS = {"dma_32x128": 0, "dma_64x128": 1, "dma_128x128": 2, "dma_128x256": 3, "dma_256x256": 4,
               "dma_128x96": 5, "dma_128x192": 6, "dma_256x192": 7, "dma_192x256": 8, "reg_64x128": 9, "simt": 10}
 lib.dkv_profile_begin.argtypes = [c_vp]

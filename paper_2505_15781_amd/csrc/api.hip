@@ -197,7 +197,7 @@ int timed_gemm(dkv_ctx *c, const void *A, const void *W, float *out, int m, cons
     const double es = (double)c->es;
     // output bytes: fp32 [M, N], or the fused SwiGLU's [M, N/2] elements
     const double out_bytes = (p.flags & GEMM_FLAG_SWIGLU) ? es * m * (n / 2) : 4.0 * m * n;
-    const int slot = dkv_gemm_is_stream(p.kind) ? (int)GEMM_REG_64x128 : p.kind;
+    const int slot = dkv_gemm_is_stream(p.kind) ? DKV_PROF_STREAM : p.kind;
     return timed(c, slot, ((double)m * k + (double)n * k) * es + out_bytes,
                  2.0 * m * n * k,
                  [&] { return dkv_launch_gemm(c->m.dtype, A, W, out, m, m, m_dev, n, k, p, c->stream); });

@@ -104,7 +104,7 @@ enum { GEMM_DMA_32x128 = 0, GEMM_DMA_64x128, GEMM_DMA_128x128, GEMM_DMA_128x256,
        GEMM_DMA_128x96, GEMM_DMA_128x192, GEMM_DMA_256x192, GEMM_DMA_192x256, GEMM_REG_64x128, GEMM_SIMT, GEMM_KINDS };
 enum { GEMM_DMA_LAST = GEMM_DMA_192x256 };      // the gemm_dma tile kernels are the kinds 0 .. GEMM_DMA_LAST
 // Kinds that only dkv_gemm_plan hands out, for projections inside a step (dkv_gemm_with takes the numbers of dkv.h, which end
-// before): gemm_stream.h, one row of tiles. A profile counts them with GEMM_REG_64x128, whose K they never have.
+// before): gemm_stream.h, one row of tiles. A profile counts them together as DKV_PROF_STREAM.
 enum { GEMM_STREAM_256x96 = GEMM_KINDS, GEMM_STREAM_256x64, GEMM_STREAM_LAST = GEMM_STREAM_256x64 };
 enum { GEMM_FLAG_STAGGER = 1, GEMM_FLAG_XCD_GROUP = 2, GEMM_FLAG_SWIGLU = 4, GEMM_FLAG_STREAM_W = 8 };
 struct GemmPlan {

@@ -8,7 +8,7 @@ from dkv_inputs.configs import BF16, FP32
 from oracle.attn_update import attn_update as oracle_attn_update
 from helpers import rel_err
 from gpu_parity import check_close, tolerances
-from plans import OWN_LAUNCH, STAGGER, STREAM_TILES, XCD_GROUP, attn_plan, embed_norm, gather_rows, gemm_plan, launch_head, launch_stream
+from plans import OWN_LAUNCH, PRODUCT, STAGGER, STREAM_TILES, XCD_GROUP, attn_plan, embed_norm, gather_rows, gemm_plan, launch_head, launch_stream
 
 pytestmark = pytest.mark.gpu
 
@@ -674,3 +674,24 @@ def test_profile_report_counts_the_bytes_each_projection_really_moves():
     assert sum(v["bytes"] for v in got) == want_bytes and sum(v["flops"] for v in got) == want_flops
     assert prof["attention"]["launches"] == m.n_layers
     g.close()
+
+
+def test_profile_report_keeps_the_projection_kernels_apart():
+    """A step whose Q/K/V projection runs on the 256-row tiles and whose down projection has a K that is no multiple of 64: each
+    kernel in a place of its own."""
+    import paper_2505_15781_amd as P
+    from paper_2505_15781_amd import binding
+    from dkv_inputs.configs import ModelShape, RunShape
+    m = ModelShape(n_layers=1, d_model=4096, n_q_heads=36, n_kv_heads=9, head_dim=128, d_ffn=200, vocab=520, mask_id=519, dtype=BF16)
+    r = RunShape(batch=1, prompt_len=128, gen_len=32, steps=32, block_len=32, refresh_interval=4)
+    rows, d, qkv = 160, m.d_model, m.qkv_rows
+    assert gemm_plan(rows, qkv, d, PRODUCT).kind in STREAM_TILES.values() and gemm_plan(rows, d, m.d_ffn, PRODUCT).tile == "reg_64x128"
+    streams = [(n, k) for n, k in ((qkv, d), (d, 36 * 128)) if gemm_plan(rows, n, k, PRODUCT).kind in STREAM_TILES.values()]
+    g = P.DkvRun(m, r, binding.random_weights(m, 3), D.prompt_tokens(m, r, 4))
+    g.profile_begin()
+    g.denoise_step(0)
+    prof = g.profile_end()
+    g.close()
+    assert prof["gemm_stream"]["launches"] == len(streams)
+    assert prof["gemm_stream"]["bytes"] == sum((rows + n) * k * 2 + 4 * rows * n for n, k in streams)
+    assert prof["gemm_reg"]["launches"] == 1 and prof["gemm_reg"]["flops"] == 2.0 * rows * d * m.d_ffn
