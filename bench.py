@@ -20,11 +20,12 @@ HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 # HBM bytes moved per algorithmic byte, per kernel, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of
 # kernel_bench.py at the configs[2] layer shapes (FETCH x2.00, WRITE x1.00 after calibration against a 1 GiB copy
-# kernel); see profiles/projection_cfg2_hbm_traffic_pmc.txt. Hardware counters cannot be read inside this program,
+# kernel; gemm_stream inside the steps of a performance case); see profiles/projection_cfg2_hbm_traffic_pmc.txt. The ratios count
+# every K slice's output as algorithmic, the report only the first. Hardware counters cannot be read inside this program,
 # so `roofline.traffic` is null and `roofline.traffic_estimate` scales this run's algorithmic bytes by these ratios.
 MEASURED_TRAFFIC_RATIO = {"gemm_dma<*,1,1,1,4,4>": 1.05, "gemm_dma<*,2,1,1,4,4>": 1.09, "gemm_dma<*,1,3,4,1,4>": 1.06,
                           "gemm_dma<*,2,3,2,2,3>": 1.13, "gemm_dma<*,2,2,2,2,3>": 1.33, "gemm_dma<*,2,4,2,2,3>": 1.44,
-                          "gemm_dma<*,2,3,4,2,2>": 1.12, "gemm_dma<*,3,2,2,4,2>": 1.21}
+                          "gemm_dma<*,2,3,4,2,2>": 1.12, "gemm_dma<*,3,2,2,4,2>": 1.21, "gemm_stream": 1.06}
 WORKLOADS = {2: "configs[2]: LLaDA-8B shape, dKV-Cache-Decode, batch 1, 256 prompt + 256 generated tokens, 256 steps, "
                 "blocks of 32, refresh every 8 steps",
              3: "configs[3]: LLaDA-8B shape, dKV-Cache-Greedy (window 4), batch 4, 1024 prompt + 512 generated tokens, "
@@ -259,8 +260,8 @@ def main():
                 "traffic_estimate": (round(MEASURED_TRAFFIC_RATIO[dom] * p["bytes"] / p["launches"])
                                      if dom in MEASURED_TRAFFIC_RATIO and args.config == 2 else None),
                 "traffic_note": "hardware counters are not readable inside this run: traffic_estimate = algorithmic "
-                                "bytes x the FETCH_SIZE/WRITE_SIZE ratio measured for this kernel with rocprofv3 --pmc on "
-                                "kernel_bench.py (profiles/projection_cfg2_hbm_traffic_pmc.txt)",
+                                "bytes x the FETCH_SIZE/WRITE_SIZE ratio measured for this kernel with rocprofv3 --pmc "
+                                "(profiles/projection_cfg2_hbm_traffic_pmc.txt); outputs of K slices beyond the first come on top",
                 "timing": "HIP events around each launch on the launch stream (includes the gap to the previous kernel)",
                 "avg_launch_us": round(p["ms"] * 1e3 / p["launches"], 2), "launches": p["launches"],
                 "algorithmic_bytes_per_launch": round(p["bytes"] / p["launches"]),

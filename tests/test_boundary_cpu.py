@@ -117,6 +117,7 @@ def test_traffic_ratios_of_the_bench_are_those_of_the_profile():
     text = open(os.path.join(ROOT, "profiles", "projection_cfg2_hbm_traffic_pmc.txt")).read()
     table = {f"gemm_dma<*,{m.group(1).replace(' ', '')}>": float(m.group(2))
              for m in re.finditer(r"^#\s+gemm_dma<0, ([\d, ]+)>.* MB\s+([\d.]+)$", text, flags=re.M)}
+    table["gemm_stream"] = float(re.search(r"^#\s+gemm_stream  .* MB\s+([\d.]+)$", text, flags=re.M).group(1))
     src = open(os.path.join(ROOT, "bench.py")).read()
     ratios = eval(re.search(r"^MEASURED_TRAFFIC_RATIO = (\{.*?\})", src, flags=re.S | re.M).group(1))
-    assert len(table) == 8 and ratios == table
+    assert len(table) == 9 and ratios == table
