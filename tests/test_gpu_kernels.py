@@ -84,13 +84,25 @@ def test_projection_of_one_row_of_tiles(tile, m, n, k, split, rows):
     ref = x[:live].double() @ w.double().T
     err = got[:, :live].double().sum(0) - ref
     assert (err.norm() / ref.norm()).item() <= 1e-5 and (err.abs().max() / ref.abs().max()).item() <= 1e-5
-    if split == 1 and n % 2 == 0:
-        y = launch_stream(x, w, tile, 1, swiglu=True)
-        full = x.double() @ w.double().T
-        want = torch.nn.functional.silu(full[:, 0::2]) * full[:, 1::2]
-        # the result is rounded to bf16: half a unit of 8 significant bits, at most 2^-8 of the value; the sums as above
-        excess = ((y.double() - want).abs() - 2.0 ** -8 * want.abs()).max() / want.abs().max()
-        assert excess.item() <= 1e-5
+
+
+@pytest.mark.parametrize("tile", sorted(STREAM_TILES))
+@pytest.mark.parametrize("m,n,k,rows", [(m, n, k, rows) for m, n, k in ((256, 384, 1024), (129, 200, 64), (255, 98, 128), (1, 1000, 192))
+                                        for rows in (None, 1, 64, 65, 131) if rows is None or rows <= m])
+def test_swiglu_of_one_row_of_tiles(tile, m, n, k, rows):
+    """The same sums through the SwiGLU epilogue, with device-side row counts at and across the 64 rows of a multiplying wavefront:
+    rows past the count are not written. The result is rounded to bf16: half a unit of 8 significant bits, at most 2^-8 of the
+    value; the sums as above."""
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    x = torch.randn((m, k), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((n, k), generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+    y = launch_stream(x, w, tile, 1, None if rows is None else torch.tensor([rows], dtype=torch.int32, device="cuda"), swiglu=True)
+    live = m if rows is None else rows
+    assert torch.isnan(y[live:]).all() and not torch.isnan(y[:live]).any()
+    full = x[:live].double() @ w.double().T
+    want = torch.nn.functional.silu(full[:, 0::2]) * full[:, 1::2]
+    excess = ((y[:live].double() - want).abs() - 2.0 ** -8 * want.abs()).max() / want.abs().max()
+    assert excess.item() <= 1e-5
 
 
 @pytest.mark.parametrize("kind,split", [("dma_32x128", 1), ("dma_32x128", 3), ("dma_64x128", 2), ("dma_128x128", 1),
@@ -402,6 +414,21 @@ def test_attention_key_slices_across_workgroups(dh):
     _attn_case(shape, None, 34, ragged=[21])
     shape = D.AttnUpdateShape(batch=2, n_q_heads=2, n_kv_heads=2, seq_len=1031, head_dim=dh, dtype=BF16)
     _attn_case(shape, None, 35, ragged=[3, 40])
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,seq_len,dh,ragged,kernel", [
+    (2, 20, 4, 1301, 128, [20, 11], "ksplit1x8/4"), (8, 4, 4, 1301, 128, [20, 0, 1, 17, 16, 20, 0, 5], "ksplit1x8/3"),      # 7 and 2 groups
+    (1, 32, 32, 737, 128, [5], "ksplit1x8/3"), (2, 32, 32, 769, 128, [3, 0], "ksplit1x8/3"),                               # 4 and 8 pairs per XCD
+    (1, 28, 4, 1100, 128, [33], "ksplit1x8/2"), (1, 4, 4, 6000, 128, [20], "ksplit1x8/8"), (1, 2, 2, 16500, 128, [3], "ksplit1x8/13"),
+    (4, 28, 4, 2053, 128, [17, 0, 3, 9], "ksplit2x8/4"), (1, 2, 2, 4500, 128, [200], "ksplit2x8/4"),                        # two tiles per item
+    (3, 12, 12, 3073, 128, [64, 0, 33], "ksplit2x8/3"),
+    (1, 2, 2, 1543, 64, [9], "ksplit1x8/3"), (4, 28, 4, 2053, 64, [17, 0, 3, 9], "ksplit1x8/2"), (2, 4, 2, 6001, 64, [33, 5], "ksplit1x8/6"),
+    (1, 2, 2, 4500, 64, [200], "ksplit2x8/4"),
+    (21, 8, 8, 200, 128, [40, 33, 0] * 7, "ksplit1x4/1"), (21, 8, 8, 200, 64, [40, 33, 0] * 7, "ksplit1x4/1")])
+def test_attention_key_slices_of_every_number(batch, q_heads, kv_heads, seq_len, dh, ragged, kernel):
+    """Two to 13 slices of the keys, of one- and two-tile items, with several query groups and with one, the cache update fused (64
+    rows and fewer) and not, sequences without rows; ragged last tiles and slices of unequal length."""
+    _attn_case(D.AttnUpdateShape(batch, q_heads, kv_heads, seq_len, dh, dtype=BF16), None, 66, ragged=ragged, kernel=kernel)
 
 
 def test_attention_many_query_tiles_per_head():
