@@ -15,10 +15,13 @@
 // workgroups share a compute unit and cover each other's barrier (one per tile).
 // Per call, with the scatter launch, before and after (same card): 8 sequences x 32 heads x 1024 keys, 512 rows 127.4 ->
 // 119.0 us; 4 x 32 heads x 1536 keys, 1536 rows 231 -> 218 us; 16 x 4 kv heads of 7, 768 keys, up to 129 rows 41.5 -> 35.3
-// us. What bounds it: vector instructions, 278 per wavefront and tile next to 37 MFMAs, 105 of them the rescaling of the
-// output, which some query of the 32 needs at 26 of 32 half tiles (independent scores). A reference that lags the maximum
-// by up to 2^8 saves those (another 8-14 %), but then the largest probability is no longer exactly 1 and the error against
-// float64 grows by up to 10 %: not done.
+// us. What bounds it: the energy of its instructions. Over a launch of 1.1 ms (4 x 32 heads, 4096 keys and rows) the chip holds 1.92
+// GHz of its 2.4, with the matrix pipes busy 57 % and vector issue 56 % of those cycles and 18 % of the wavefronts' time
+// waiting; the 512-row launch takes 83 us alone and 89-94 behind others of its kind. So neither port is full, and schedules that
+// only move instructions gain nothing; fewer instructions do: of 278 vector ones per wavefront and tile, next to 37 MFMAs, 105
+// rescale the output, which some query of the 32 needs at 26 of 32 half tiles (independent scores). A reference that lags the
+// maximum by up to 2^8 saves those (8-14 % less time), but then the largest probability is no longer exactly 1 and the error
+// against float64 grows by up to 10 %: not done.
 #pragma once
 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
@@ -33,7 +36,8 @@ __device__ __forceinline__ int wide_swizzle(int row) { return ((row & 3) << 2) |
 // blocks that hold query rows come first. A workgroup without rows leaves at once, and where it stood between others the
 // hardware put two busy workgroups on one unit and left others empty (11 sequences x 8 kv heads of 3, 10 to 115 rows: 1024
 // keys 35.9 -> 27.3 us, 4096 keys 113 -> 82; with no such sequences level to 1 % slower). With at most 256 workgroups every one
-// has a unit, with 512 every unit has two. A lane per (sequence, kv head) pair of the XCD counts its blocks; a prefix sum
+// has a unit; from 512 on, where the first two of every unit may be empty as well, the plain order is kept (the other one is not
+// measured there). A lane per (sequence, kv head) pair of the XCD counts its blocks; a prefix sum
 // over the lanes finds the pair of this workgroup.
 __device__ __forceinline__ bool wide_item_compact(const int *row_off, int pairs, int Hkv, int G, int q_blocks, int &pair, int &qb) {
     const int lane = threadIdx.x & 63, slot = blockIdx.x >> 3, p = lane * 8 + (blockIdx.x & 7), b = min(p, pairs - 1) / Hkv;

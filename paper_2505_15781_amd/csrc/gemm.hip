@@ -282,7 +282,9 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
     // columns, cold weights): the choice loses 0.4 % on average and 6 % at worst against the best of either, and gains 3.6 %
     // over the plan without them: 7-20 % where the tiles make whole rounds of a long K (24576 x 4096, 22016 x 4096,
     // 3584 x 18944, 4096 x 12288), nothing where K is short (4096 x 4096: 1.06-1.11 of the time) or the rounds do not fit
-    // (37888 x 3584: 1.13-1.21). With up to 128 rows the 128-row tiles are level (24576 x 4096 at 128 rows 43.3 against 51.6 us).
+    // (37888 x 3584: 1.13-1.21). Over 93 launches of 30 layer shapes whose plan they change, against that plan: 0.88 of the time, 0.99
+    // at worst; with only half of the bound's rows live 0.93, 1.12 at worst (8192 x 8192). dkv_gemm on its own does not get them: it
+    // goes through dkv_gemm_with, which takes the public kernel numbers, and no launch of its own was measured. With up to 128 rows the 128-row tiles are level (24576 x 4096 at 128 rows 43.3 against 51.6 us).
     if ((slices_go_to == SLICES_CONSUMER || slices_go_to == SLICES_PRODUCT) && m_upper > 128 && m_upper <= 256) {
         struct Stream { int kind, bn; double alone, full; };                                    // us per K tile
         constexpr Stream kStream[] = {{GEMM_STREAM_256x96, 96, 0.52, 0.56}, {GEMM_STREAM_256x64, 64, 0.44, 0.44}};
