@@ -204,7 +204,8 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
     //   128x256 tiles have no second workgroup on the compute unit that would work in a round's first fills and epilogue, and
     //   lose that time with every further round where the epilogue computes (SwiGLU, vocabulary statistics); one that only stores
     //   the fp32 product is shorter with them than with the 8-wavefront tiles (24576 x 4096 at 640 rows, 128x256 / 192x256 tiles: SwiGLU 150 /
-    //   144 us, product 139 / 160; 37888 x 3584 at 384 rows 148 / 136 and 145 / 152);
+    //   144 us, product 139 / 160; 37888 x 3584 at 384 rows 148 / 136 and 145 / 152; up to K = 6144: beyond, 8-wavefront tiles in K slices
+    //   are ahead for products too, 22016 x 11008 at 608 rows 439 / 361, 37888 x 8192 at 288 rows 317 / 305);
     //   workgroups run in rounds of 256 (one per compute unit), a partly filled round costs a full one;
     //   no launch beats streaming its operands and results once;
     //   every further K slice adds the write and re-read of its partial sums by the consumer; a reduction of its own also
@@ -232,7 +233,7 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
     constexpr PingPong kPingPong[] = {{}, {}, {}, {}, {1.130, 1.290}, {}, {}, {1.041, 1.092}, {0.980, 1.078}};
     static_assert(GEMM_DMA_256x256 == 4 && GEMM_DMA_256x192 == 7 && GEMM_DMA_192x256 == 8 && GEMM_DMA_LAST == 8, "order of kPingPong");
     const int kt_total = k / BK;
-    const bool stored = slices_go_to == SLICES_LAUNCH || slices_go_to == SLICES_PRODUCT;        // in one slice too
+    const bool store_only = (slices_go_to == SLICES_LAUNCH || slices_go_to == SLICES_PRODUCT) && kt_total <= 96;
     struct { int s, nk; } slices[6];       // K slices worth trying, K tiles of each
     int n_slices = 0;
     for (int s : {1, 2, 3, 4, 6, 8}) {
@@ -264,12 +265,13 @@ GemmPlan dkv_gemm_plan(int dtype, int m_upper, int n, int k, int slices_go_to) {
                 t_rounds = rounds * (all > t_cu ? all : t_cu);
             }
             double t = slices[i].nk * t_rounds + rounds * (eight ? kPipeFill8 : kPipeFill);
-            if (kind == GEMM_DMA_128x256 && !stored) t += (rounds - 1) * kNextRound128x256;
+            if (kind == GEMM_DMA_128x256 && !store_only) t += (rounds - 1) * kNextRound128x256;
             const double stream = (operands + s * product) * kPerStream, work = t;
             if (stream > t) t = stream;
             t += kLaunch;
             if (s > 1) t += (s - (slices_go_to == SLICES_LAUNCH ? 0 : 1)) * product * kPerReduce + kReduceFixed;
-            if (p.kind < 0 || t < best || (t == best && work < best_work)) {      // level where only the stream counts: less work
+            // level where only the stream counts: of two 8-wavefront tiles the one with less work (padding)
+            if (p.kind < 0 || t < best || (t == best && eight && kPingPong[p.kind].full > 0.0 && work < best_work)) {
                 best = t;
                 best_work = work;
                 p.kind = kind;

@@ -15,9 +15,9 @@ __device__ __forceinline__ float lane_swap1(float x) {
 // apart, by data-parallel primitives and gfx950's row swap. Behind the first two steps the lanes of a quad agree, so that a
 // mirrored half row and row hand over the value of the lane four and eight apart. The epilogue of the vocabulary projection is
 // bound by these chains (three per row, 16 MT rows per wavefront): LDS permutes for the five steps against these, the whole launch
-// on the same tiles: 126464 x 4096 at 33 rows 211 and 180 us (162 since those tiles have three stages of LDS), 32000 x 2048 at 48 rows
-// 38 and 31; the launch's floor, the weights once at 6 TB/s, is 173 and 22 us. (128x256 tiles at 93 rows: 126464 x 4096 204 and 189,
-// 152064 x 3584 263 and 240; planned there are 192x256 tiles of 8 wavefronts, level with them, whose epilogue in
+// on the same tiles: 126464 x 4096 at 33 rows 211 and 180 us (162 since those tiles have three stages of LDS), at 93 rows 204 and
+// 189, 32000 x 2048 at 48 rows 38 and 31; the launch's floor, the weights once at 6 TB/s, is 173 and 22 us. (152064 x 3584 at 93
+// rows, 128x256 tiles, 263 and 240; planned there are 192x256 tiles of 8 wavefronts, level with them, whose epilogue in
 // gemm_epilogue8.h still permutes through LDS.)
 template <int CTRL> __device__ __forceinline__ int dpp_move(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true); }
 template <typename F> __device__ __forceinline__ int half_reduce(int x, F combine) {

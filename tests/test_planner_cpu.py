@@ -28,10 +28,11 @@ def test_128x256_tiles_are_planned_for_one_round(m, n, k, tile):
 
 
 @pytest.mark.parametrize("m,n,k,tile", [(384, 37888, 3584, "dma_128x256"), (640, 24576, 4096, "dma_128x256"), (600, 22016, 4096, "dma_128x256"),
-                                        (640, 24576, 8192, "dma_128x256"), (800, 18432, 6144, "dma_128x256"), (400, 37888, 3584, "dma_192x256")])
+                                        (640, 24576, 5120, "dma_128x256"), (800, 18432, 6144, "dma_128x256"), (400, 37888, 3584, "dma_192x256"),
+                                        (288, 37888, 8192, "dma_192x256"), (608, 22016, 11008, "dma_192x256")])
 def test_a_further_round_of_128x256_tiles_is_cheap_where_the_product_is_stored(m, n, k, tile):
     """The charge of the test above is for epilogues that compute: dkv_gemm and the projections whose fp32 product a row kernel
-    reads keep these tiles in their second round, up to the line where a third begins."""
+    reads keep these tiles in their second round, up to the line where a third begins and to K = 6144."""
     assert gemm_plan(m, n, k, OWN_LAUNCH).tile == tile and gemm_plan(m, n, k, PRODUCT).tile == tile
 
 
@@ -40,6 +41,13 @@ def test_of_two_plans_that_only_stream_the_one_with_less_work_is_taken(m, n, k):
     """Two slices of 192x256 and of 256x256 tiles, both as fast as the operands come: no padding to 256 rows."""
     p = gemm_plan(m, n, k)
     assert p.tile == "dma_192x256" and p.split_k == 2
+
+
+@pytest.mark.parametrize("m,n,k,tile", [(33, 65536, 2048, "dma_64x128"), (64, 65536, 512, "dma_64x128"), (82, 126464, 512, "dma_192x256"),
+                                        (100, 126464, 4096, "dma_128x256"), (163, 65536, 1024, "dma_192x256"), (378, 65536, 512, "dma_192x256")])
+def test_vocabularies_that_only_stream(m, n, k, tile):
+    """A 128x256 tile for 33 to 64 candidates has as little work on paper as two 64x128, but three quarters of it is padding."""
+    assert gemm_plan(m, n, k, ONE_SLICE).tile == tile
 
 
 @pytest.mark.parametrize("m,n,k", [(400, 4608, 3584), (700, 4608, 3584), (1024, 4608, 3584), (400, 12288, 4096)])
