@@ -106,12 +106,9 @@ __global__ __launch_bounds__(1024) void select_active_kernel(SelectArgs a) {
 
 // ------------------------------------------------------------------------------------------------
 // h[r] = embed[token at (seq, pos)], a[r] = RMSNorm(h[r]) * gain; stamps the row's position.
-// One workgroup of NT threads per row, V pieces of W elements per lane: d must be a multiple of W and at most W * NT * V.
+// One workgroup of NT threads per row, V4 pieces of four elements per lane: d must be a multiple of 4 and at most 4 * NT * V4.
 // At few rows a chain of latencies (count, row, token, row of the table), at thousands bound by memory: in loads and stores of
 // one element 6144 rows of 4096 bf16 took 94 us behind a flushed cache, in fours 64 (201 MB: 34 at 6 TB/s); 512 rows 11.2 and 9.9, 32 rows 8.4 and 6.6.
-// fp32 keeps pieces of one element: the order in which a row's squares are added decides the last bits of everything behind
-// it, and a generation of the toy model gives the same bits from one version to the next (in fours 59 of 60 generations
-// differed, one of another twelve in its tokens; the time of a generation is level, 2684 and 2688 us).
 // ------------------------------------------------------------------------------------------------
 // four consecutive outputs as one store
 __device__ __forceinline__ void store4(float *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
@@ -133,13 +130,7 @@ __device__ __forceinline__ float4 load4(const bf16_t *p) {
     return make_float4(bf2f((bf16_t)(w[0] & 0xffff)), bf2f((bf16_t)(w[0] >> 16)), bf2f((bf16_t)(w[1] & 0xffff)), bf2f((bf16_t)(w[1] >> 16)));
 }
 
-template <int W> __device__ __forceinline__ float4 load_piece(const float *p) {
-    if constexpr (W == 4) return load4(p);
-    return make_float4(*p, 0.f, 0.f, 0.f);
-}
-template <int W> __device__ __forceinline__ float4 load_piece(const bf16_t *p) { return load4(p); }
-
-template <typename T, int V, int NT, int W>
+template <typename T, int V4, int NT>
 __global__ __launch_bounds__(NT) void embed_norm_kernel(const T *__restrict__ embed,
                                                          const int *__restrict__ tokens,
                                                          const int *__restrict__ row_pos,
@@ -148,7 +139,6 @@ __global__ __launch_bounds__(NT) void embed_norm_kernel(const T *__restrict__ em
                                                          const float *__restrict__ gain, float *__restrict__ h,
                                                          T *__restrict__ a, int *__restrict__ stamp, int L,
                                                          int d, float eps, int step) {
-    static_assert(W == 4 || (W == 1 && sizeof(T) == 4), "pieces of four elements, or of one fp32 element");
     __shared__ float red[16];
     const int r = blockIdx.x;
     if (r >= counts[0]) return;
@@ -156,34 +146,27 @@ __global__ __launch_bounds__(NT) void embed_norm_kernel(const T *__restrict__ em
     const int tok = tokens[(size_t)b * L + p];
     if (threadIdx.x == 0) stamp[(size_t)b * L + p] = step;
     const T *e = embed + (size_t)tok * d;
-    float4 v[V], g[V];
+    float4 v[V4], g[V4];
     float ss = 0.f;
 #pragma unroll
-    for (int i = 0; i < V; ++i) {
-        const int c = (threadIdx.x + NT * i) * W;
+    for (int i = 0; i < V4; ++i) {
+        const int c = (threadIdx.x + NT * i) * 4;
         v[i] = g[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (c < d) {
-            v[i] = load_piece<W>(e + c);
-            g[i] = load_piece<W>(gain + c);
+            v[i] = load4(e + c);
+            g[i] = load4(gain + c);
         }
-        if constexpr (W == 1) ss += v[i].x * v[i].x;
-        else ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+        ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
     }
     ss = block_sum(ss, red);
     const float rs = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
-    for (int i = 0; i < V; ++i) {
-        const int c = (threadIdx.x + NT * i) * W;
+    for (int i = 0; i < V4; ++i) {
+        const int c = (threadIdx.x + NT * i) * 4;
         if (c < d) {
             const size_t at = (size_t)r * d + c;
-            const float4 y = make_float4(v[i].x * rs * g[i].x, v[i].y * rs * g[i].y, v[i].z * rs * g[i].z, v[i].w * rs * g[i].w);
-            if constexpr (W == 1) {
-                h[at] = v[i].x;
-                a[at] = y.x;
-            } else {
-                store4(h + at, v[i]);
-                store4(a + at, y);
-            }
+            store4(h + at, v[i]);
+            store4(a + at, make_float4(v[i].x * rs * g[i].x, v[i].y * rs * g[i].y, v[i].z * rs * g[i].z, v[i].w * rs * g[i].w));
         }
     }
 }
@@ -576,23 +559,16 @@ template <typename T> int vpt_dispatch_embed(hipStream_t s, int rows, int d, con
                                              const int *row_pos, const int *row_seq, const int *counts,
                                              const float *gain, float *h, T *a, int *stamp, int L, float eps,
                                              int step) {
-#define GO(V, NT, W)                                                                                          \
-    hipLaunchKernelGGL((embed_norm_kernel<T, V, NT, W>), dim3(rows), dim3(NT), 0, s, embed, tokens, row_pos,  \
+#define GO(V, NT)                                                                                          \
+    hipLaunchKernelGGL((embed_norm_kernel<T, V, NT>), dim3(rows), dim3(NT), 0, s, embed, tokens, row_pos,  \
                        row_seq, counts, gain, h, a, stamp, L, d, eps, step)
     if (d % 4) { dkv_set_error("d_model %d must be a multiple of 4", d); return DKV_E_UNSUPPORTED; }
-    if (d > 8192) { dkv_set_error("d_model %d above 8192 is not supported", d); return DKV_E_UNSUPPORTED; }
-    if constexpr (sizeof(T) == 4) {
-        if (d <= 256) GO(1, 256, 1);
-        else if (d <= 1024) GO(1, 1024, 1);
-        else if (d <= 4096) GO(4, 1024, 1);
-        else GO(8, 1024, 1);
-    } else {
-        if (d <= 256) GO(1, 64, 4);
-        else if (d <= 1024) GO(1, 256, 4);
-        else if (d <= 2048) GO(1, 512, 4);
-        else if (d <= 4096) GO(1, 1024, 4);
-        else GO(2, 1024, 4);
-    }
+    if (d <= 256) GO(1, 64);
+    else if (d <= 1024) GO(1, 256);
+    else if (d <= 2048) GO(1, 512);
+    else if (d <= 4096) GO(1, 1024);
+    else if (d <= 8192) GO(2, 1024);
+    else { dkv_set_error("d_model %d above 8192 is not supported", d); return DKV_E_UNSUPPORTED; }
 #undef GO
     DKV_LAUNCH_CHECK();
     return DKV_OK;

@@ -296,34 +296,6 @@ def test_embedded_rows_and_gathered_candidates_in_pieces_of_four(dtype, d):
     assert torch.equal(picked[:3], a[[5, 0, 5]]) and not picked[3].any()
 
 
-@pytest.mark.parametrize("d", [4, 60, 64, 68, 128, 252, 256, 260, 512, 1024])
-def test_embedded_rows_in_fp32_keep_the_order_of_their_sums(d):
-    """Bit for bit: the squares in groups of 64 by partners 32, 16 ... 1 apart, the first addition fused with the square as the compiler
-    contracts it (in float64 the product is exact), the groups in ascending order, and the reciprocal root, division and
-    products as IEEE rounds them."""
-    rows, V = 5, 9
-    g = torch.Generator(device="cuda").manual_seed(d)
-    table, gain = torch.randn((V, d), generator=g, device="cuda"), torch.rand(d, generator=g, device="cuda") + 0.5
-    tokens = torch.arange(rows, device="cuda", dtype=torch.int32)[None].contiguous()
-    zero = torch.zeros(rows, dtype=torch.int32, device="cuda")
-    h, a = torch.zeros((rows, d), device="cuda"), torch.zeros((rows, d), device="cuda")
-    embed_norm(table, tokens, tokens[0], zero, torch.tensor([rows, 0], dtype=torch.int32, device="cuda"), gain, h, a, torch.zeros_like(tokens), 1e-5, 1)
-    x = table[:rows].cpu().numpy()
-    part = np.zeros((rows, -(-d // 64) * 64), np.float32)
-    part[:, :d] = x
-    part = part.reshape(rows, -1, 64)
-    lane = np.arange(64)
-    part = (part.astype(np.float64) ** 2 + (part * part)[:, :, lane ^ 32]).astype(np.float32)
-    for apart in (16, 8, 4, 2, 1):
-        part = part + part[:, :, lane ^ apart]
-    total = np.zeros(rows, np.float32)
-    for group in range(part.shape[1]):
-        total = total + part[:, group, 0]
-    root = np.float32(1) / np.sqrt(total / np.float32(d) + np.float32(1e-5))
-    want = x * root[:, None] * gain.cpu().numpy()
-    assert (h.cpu().numpy() == x).all() and (a.cpu().numpy() == want).all()
-
-
 @pytest.mark.parametrize("m,n,k", [(1, 2, 4), (16, 16, 64), (17, 30, 60), (64, 130, 68), (65, 16, 1028), (128, 4096, 64),
                                    (129, 4096, 64), (16, 16, 128), (20, 20, 132)])
 def test_fp32_projection_of_few_rows_at_tile_edges(m, n, k):
