@@ -296,6 +296,35 @@ def test_embedded_rows_and_gathered_candidates_in_pieces_of_four(dtype, d):
     assert torch.equal(picked[:3], a[[5, 0, 5]]) and not picked[3].any()
 
 
+@pytest.mark.parametrize("d", [4, 60, 128, 252, 256, 260, 512, 1024, 1028, 2048, 4096])
+def test_embedded_rows_in_fp32_keep_the_order_of_their_sums(d):
+    """Two candidates of a step can be equal but for a rounding, so another order of the sums would commit the other one: bit for
+    bit, a lane's four squares (fused as the compiler contracts them; in float64 a product is exact), the 64 lanes by partners 32,
+    16 ... 1 apart, the wavefronts in ascending order, and the reciprocal root, division and products as IEEE rounds them."""
+    rows, V = 5, 9
+    g = torch.Generator(device="cuda").manual_seed(d)
+    table, gain = torch.randn((V, d), generator=g, device="cuda"), torch.rand(d, generator=g, device="cuda") + 0.5
+    tokens = torch.arange(rows, device="cuda", dtype=torch.int32)[None].contiguous()
+    zero = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    h, a = torch.zeros((rows, d), device="cuda"), torch.zeros((rows, d), device="cuda")
+    embed_norm(table, tokens, tokens[0], zero, torch.tensor([rows, 0], dtype=torch.int32, device="cuda"), gain, h, a, torch.zeros_like(tokens), 1e-5, 1)
+    x = table[:rows].cpu().numpy()
+    v = np.zeros((rows, -(-d // 256) * 256), np.float32)
+    v[:, :d] = x
+    v = v.reshape(rows, -1, 64, 4)
+    part = v[..., 0] * v[..., 0]
+    for e in (1, 2, 3):
+        part = (v[..., e].astype(np.float64) ** 2 + part).astype(np.float32)
+    for apart in (32, 16, 8, 4, 2, 1):
+        part = part + part[:, :, np.arange(64) ^ apart]
+    total = np.zeros(rows, np.float32)
+    for wavefront in range(part.shape[1]):
+        total = total + part[:, wavefront, 0]
+    root = np.float32(1) / np.sqrt(total / np.float32(d) + np.float32(1e-5))
+    want = x * root[:, None] * gain.cpu().numpy()
+    assert (h.cpu().numpy() == x).all() and (a.cpu().numpy() == want).all()
+
+
 @pytest.mark.parametrize("m,n,k", [(1, 2, 4), (16, 16, 64), (17, 30, 60), (64, 130, 68), (65, 16, 1028), (128, 4096, 64),
                                    (129, 4096, 64), (16, 16, 128), (20, 20, 132)])
 def test_fp32_projection_of_few_rows_at_tile_edges(m, n, k):
