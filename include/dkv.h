@@ -248,8 +248,8 @@ int dkv_attn_update(void *k_cache, void *v_cache, const void *q, const void *k_n
  * capture, tight serving loops, harnesses that forbid hipMalloc. Same arguments, same kernels and the same
  * result as dkv_attn_update, but the scratch of key-sliced attention (partial softmax records) is a
  * DKV_STATIC_SCRATCH_BYTES array inside the library's device image; the call allocates nothing. Shapes whose
- * scratch (dkv_attn_update_workspace_bytes) exceeds that size get fewer key slices, as many as fit (the same result
- * up to the order of its sums). Each GPU holds one such array for the life of the process and all calls on that GPU share it:
+ * scratch (dkv_attn_update_workspace_bytes) exceeds that size are run with key slices that fit (the same result up
+ * to the order of its sums). Each GPU holds one such array for the life of the process and all calls on that GPU share it:
  * calls that overlap on one GPU (different streams or threads) race on it; calls on one stream are ordered.
  * Nothing in the array needs clearing between calls. The first call on a device looks the array up and must
  * not happen inside a graph capture. */

@@ -616,8 +616,8 @@ int attn_update_impl(void *k_cache, void *v_cache, const void *q, const void *k_
     if (dtype != DKV_BF16 && dtype != DKV_FP32) { dkv_set_error("unknown dtype"); return DKV_E_INVALID_ARG; }
     if (rows == 0) return DKV_OK;
     if (!q || !k_new || !v_new || !active_idx || !out) { dkv_set_error("null argument"); return DKV_E_INVALID_ARG; }
-    AttnPlan p = dkv_attn_plan(dtype, batch, n_q_heads, n_kv_heads, seq_len, head_dim, max_rows_per_seq);
-    if (fit_workspace) dkv_attn_fit_partials(p, workspace_bytes, batch, n_q_heads, n_kv_heads, seq_len, head_dim);
+    const AttnPlan p = dkv_attn_plan_within(fit_workspace ? workspace_bytes : SIZE_MAX, dtype, batch, n_q_heads, n_kv_heads, seq_len,
+                                            head_dim, max_rows_per_seq);
     size_t need = dkv_attn_partial_bytes(p, batch, n_q_heads, n_kv_heads, head_dim);
     if (need > workspace_bytes || (need && !workspace)) {
         dkv_set_error("workspace has %zu bytes, %zu needed", workspace_bytes, need);

@@ -365,6 +365,11 @@ int launch_generic(const void *q, const void *k, const void *v, const int *row_o
 
 AttnPlan dkv_attn_plan(int dtype, int batch, int n_q_heads, int n_kv_heads, int seq_len, int head_dim,
                        int max_rows_per_seq) {
+    return dkv_attn_plan_within(SIZE_MAX, dtype, batch, n_q_heads, n_kv_heads, seq_len, head_dim, max_rows_per_seq);
+}
+
+AttnPlan dkv_attn_plan_within(size_t partial_bytes, int dtype, int batch, int n_q_heads, int n_kv_heads, int seq_len, int head_dim,
+                              int max_rows_per_seq) {
     AttnPlan p;
     p.use_mfma = (dtype == DKV_BF16 && (head_dim == 64 || head_dim == 128)) ? 1 : 0;
     p.shared = 0;
@@ -403,34 +408,41 @@ AttnPlan dkv_attn_plan(int dtype, int batch, int n_q_heads, int n_kv_heads, int 
     // XCDs do. In steps of one key tile and one query tile of a wavefront (about 2 us with 128 dims, half of it with 64):
     //   a workgroup costs kFixed and the key tiles of a wavefront; a second query tile makes a step half as long again, but the
     //   items half as many;
-    //   workgroups have 8 wavefronts, one on a compute unit, where all items of an XCD fit at once, otherwise 4 (0.88 of the time of
-    //   8 there, median of 347 plans); items of one tile go up to 64 of those (beyond, two tiles take 0.63-1.1 of the time);
-    //   slices go only into units that would stay idle (where the last one is taken as well: 3 % more), from 24 key tiles of
-    //   128 dims on, with two tiles for each wavefront beyond four slices, and cost a merge launch that reads them all.
-    // Fitted to 1291 calls (1 to 24 sequences, 1 to 64 K/V heads, 40 to 16384 keys, head_dim 64 and 128; up to 21 plans of each
-    // measured, K/V cold): the choice loses 1.2 % on average and 23 % at worst against the best. Lines at numbers of items and of
-    // key tiles before lost where keys are many, which slices of two-tile items then share: 36 pairs, 16384 keys, 64 rows 76.5 us
+    //   workgroups have 8 wavefronts, one on a compute unit, where all items of an XCD fit at once or keys are sliced, otherwise 4
+    //   (0.88 of the time of 8 there, median of 347 plans); items of one tile go up to 64 of those (beyond, two tiles take 0.63-1.1 of the time);
+    //   slices begin at 24 key tiles of 128 dims, leave two tiles to each wavefront beyond four slices, may run in up to four rounds of
+    //   32 workgroups (kRound for each further one: where the keys are many, rounds of short chains beat one of long chains
+    //   that leaves units idle; 3 % where a round takes every unit), and cost a merge launch that reads them all.
+    // Fitted to 1991 calls (1 to 24 sequences, 1 to 64 K/V heads, 40 to 20000 keys, head_dim 64 and 128; up to 30 plans of each
+    // measured, K/V cold): the choice loses 1.2 % on average and 23 % at worst against the best, and takes 0.87 of the time of two tiles
+    // always with slices up to 384 workgroups (1.17 at worst), 0.94 of that of lines at numbers of items and key tiles (1.10 at worst);
+    // over 700 other calls 0.86 (1.11) and 0.95 (1.16).
+    // Those lost where keys are many, which slices of two-tile items then share: 36 pairs, 16384 keys, 64 rows 76.5 us
     // with two tiles in three slices, 135 with one in one; 8192 keys 45 and 70; 8 pairs of 7 query heads, 8192 keys, 48 rows 41 and 57;
     // and on few pairs, where two tiles were taken beyond 1024 keys: 4 pairs of 7 query heads, 1536 keys, 20 rows 12.5 us with one
     // tile in three slices, 14.5 with two; 64 rows 16.6 with one in one, 24.5 with two in three.
     const long pairs = (long)batch * n_kv_heads;
     const long per_xcd = (pairs + 7) / 8;
     const int n_tiles = ceil_div(seq_len, KT);
-    constexpr float kFixed = 4.1f, kTwoTiles = 1.48f, kFourWaves = 0.79f, kMerge = 0.81f, kMergeSlice = 0.39f, kFull = 1.035f;
+    constexpr float kFixed = 4.0f, kTwoTiles = 1.56f, kFourWaves = 0.89f, kRound = 5.5f, kMerge = 0.9f, kMergeSlice = 0.36f,
+                    kFull = 1.035f;
     const float keys = (head_dim == 64 ? 0.5f : 1.0f) * (float)n_tiles;
     const int most_slices = n_tiles * head_dim < 24 * 128 ? 1 : n_tiles / 16 > 4 ? n_tiles / 16 : 4;
+    const size_t slice_bytes = (size_t)batch * ceil_div(p.q_tiles * 16, G) * n_q_heads * (head_dim + 4) * sizeof(float);
+    const size_t fit = partial_bytes / slice_bytes;
     float best = 0.f;
     int s = 1;
     for (int nq = 1; nq <= 2 && nq <= p.q_tiles; ++nq) {
         const int groups = ceil_div(p.q_tiles, nq);
         const long items = per_xcd * groups;
         if (nq == 1 && items > 64 && p.q_tiles > 1) continue;
-        const int waves = items <= 32 ? 8 : 4;
-        const float chain = (nq == 2 ? kTwoTiles : 1.0f) * (waves == 8 ? 1.0f : kFourWaves) * keys / (float)waves;
-        for (int slices = 1; slices == 1 || (slices <= most_slices && slices * items <= 32); ++slices) {
-            float t = kFixed + chain / (float)slices;
+        const float chain = (nq == 2 ? kTwoTiles : 1.0f) * keys;
+        for (int slices = 1; slices == 1 || (slices <= most_slices && slices * items <= 128 && (size_t)slices <= fit); ++slices) {
+            const int waves = items > 32 && slices == 1 ? 4 : 8;
+            const float rounds = waves == 8 ? (float)((slices * items + 31) / 32) : kFourWaves;
+            float t = kFixed + rounds * chain / (float)(slices * waves) + (rounds > 1.0f ? (rounds - 1.0f) * kRound : 0.0f);
             if (slices > 1) t += kMerge + kMergeSlice * (float)slices;
-            if (slices > 1 && slices * items == 32) t *= kFull;
+            if (slices > 1 && slices * items % 32 == 0) t *= kFull;
             if (best == 0.f || t < best) {
                 best = t;
                 s = slices;
@@ -451,15 +463,6 @@ size_t dkv_attn_partial_bytes(const AttnPlan &p, int batch, int n_q_heads, int n
     // rows per sequence are at most q_tiles*16/G (rounded up); records are indexed by (row, head, split)
     size_t rows = (size_t)batch * (size_t)ceil_div(p.q_tiles * 16, G);
     return rows * n_q_heads * p.splits * (size_t)(head_dim + 4) * sizeof(float);
-}
-
-void dkv_attn_fit_partials(AttnPlan &p, size_t bytes, int batch, int n_q_heads, int n_kv_heads, int seq_len, int head_dim) {
-    if (!p.use_mfma || p.splits == 1) return;
-    const size_t fit = bytes / (dkv_attn_partial_bytes(p, batch, n_q_heads, n_kv_heads, head_dim) / p.splits);
-    if (fit >= (size_t)p.splits) return;
-    const int n_tiles = ceil_div(seq_len, KT);
-    p.tiles_per_split = fit ? ceil_div(n_tiles, (int)fit) : n_tiles;
-    p.splits = ceil_div(n_tiles, p.tiles_per_split);
 }
 
 int dkv_attn_can_fuse_update(const AttnPlan &plan, int max_rows_per_seq) {

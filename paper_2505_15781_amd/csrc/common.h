@@ -188,8 +188,9 @@ struct AttnPlan {
 AttnPlan dkv_attn_plan(int dtype, int batch, int n_q_heads, int n_kv_heads, int seq_len, int head_dim,
                        int max_rows_per_seq);
 size_t dkv_attn_partial_bytes(const AttnPlan &p, int batch, int n_q_heads, int n_kv_heads, int head_dim);
-// fewer key slices where the plan's records would take more than `bytes`
-void dkv_attn_fit_partials(AttnPlan &p, size_t bytes, int batch, int n_q_heads, int n_kv_heads, int seq_len, int head_dim);
+// the plan whose records take at most `partial_bytes`
+AttnPlan dkv_attn_plan_within(size_t partial_bytes, int dtype, int batch, int n_q_heads, int n_kv_heads, int seq_len, int head_dim,
+                              int max_rows_per_seq);
 
 // New K/V rows that the attention kernel itself writes into the cache before using them (all null: the cache
 // is already up to date). Row r holds [n_kv_heads][head_dim] for position active_idx[r] of its sequence.

@@ -51,6 +51,14 @@ def attn_plan(shape, max_rows_per_seq):
     return f(shape.dtype, shape.batch, shape.n_q_heads, shape.n_kv_heads, shape.seq_len, shape.head_dim, max_rows_per_seq)
 
 
+def attn_plan_within(partial_bytes, shape, max_rows_per_seq):
+    """The plan whose records of key slices take at most `partial_bytes`."""
+    from paper_2505_15781_amd import binding
+    f = binding.lib._Z20dkv_attn_plan_withinmiiiiiii
+    f.restype, f.argtypes = AttnPlan, [C.c_size_t] + [C.c_int] * 7
+    return f(partial_bytes, shape.dtype, shape.batch, shape.n_q_heads, shape.n_kv_heads, shape.seq_len, shape.head_dim, max_rows_per_seq)
+
+
 class HeadEpilogue(C.Structure):
     _fields_ = [("kind", C.c_int), ("out", C.c_void_p), ("head_part", C.c_void_p), ("head_tiles", C.c_int), ("mask_id", C.c_int),
                 ("status", C.c_void_p)]

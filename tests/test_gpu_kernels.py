@@ -423,12 +423,13 @@ def test_attention_key_slices_across_workgroups(dh):
     (1, 28, 4, 1100, 128, [33], "ksplit1x8/2"), (1, 4, 4, 6000, 128, [20], "ksplit1x8/8"), (1, 2, 2, 16500, 128, [3], "ksplit1x8/13"),
     (4, 28, 4, 2053, 128, [17, 0, 3, 9], "ksplit2x8/4"), (1, 2, 2, 4500, 128, [200], "ksplit2x8/4"),                        # two tiles per item
     (3, 12, 12, 3073, 128, [64, 0, 33], "ksplit2x8/3"),
+    (1, 4, 1, 4008, 128, [131], "ksplit2x8/3"), (1, 7, 1, 7026, 128, [153], "ksplit2x8/3"), (1, 8, 1, 7514, 64, [65], "ksplit2x8/3"),   # 2, 4, 2 rounds
     (1, 2, 2, 1543, 64, [9], "ksplit1x8/3"), (4, 28, 4, 2053, 64, [17, 0, 3, 9], "ksplit1x8/2"), (2, 4, 2, 6001, 64, [33, 5], "ksplit1x8/6"),
     (1, 2, 2, 4500, 64, [200], "ksplit2x8/4"),
     (21, 8, 8, 200, 128, [40, 33, 0] * 7, "ksplit1x4/1"), (21, 8, 8, 200, 64, [40, 33, 0] * 7, "ksplit1x4/1")])
 def test_attention_key_slices_of_every_number(batch, q_heads, kv_heads, seq_len, dh, ragged, kernel):
     """Two to 13 slices of the keys, of one- and two-tile items, with several query groups and with one, the cache update fused (64
-    rows and fewer) and not, sequences without rows; ragged last tiles and slices of unequal length."""
+    rows and fewer) and not, sequences without rows; ragged last tiles and slices of unequal length; workgroups in several rounds."""
     _attn_case(D.AttnUpdateShape(batch, q_heads, kv_heads, seq_len, dh, dtype=BF16), None, 66, ragged=ragged, kernel=kernel)
 
 

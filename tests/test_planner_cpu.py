@@ -4,7 +4,7 @@ import pytest
 import dkv_inputs as D
 from dkv_inputs.configs import BF16
 
-from plans import CONSUMER, EIGHT_WAVEFRONTS, ONE_SLICE, OWN_LAUNCH, PRODUCT, STREAM_TILES, STREAM_W, attn_plan, gemm_plan
+from plans import CONSUMER, EIGHT_WAVEFRONTS, ONE_SLICE, OWN_LAUNCH, PRODUCT, STREAM_TILES, STREAM_W, attn_plan, attn_plan_within, gemm_plan
 
 
 @pytest.mark.parametrize("m,n,k", [(2049, 512, 4096), (4096, 512, 4096), (2304, 3584, 18944), (3072, 1024, 8192), (5000, 1024, 4096)])
@@ -109,6 +109,7 @@ def test_every_attention_kernel_is_planned_where_its_measurements_say():
     (3, 28, 4, 1536, 16, "ksplit1x8", 2), (3, 28, 4, 1536, 19, "ksplit2x8", 3),                                           # slices on 12 pairs
     (5, 32, 32, 1024, 20, "ksplit2x8", 1), (4, 32, 32, 1121, 9, "ksplit1x8", 2), (1, 16, 16, 8192, 9, "ksplit1x8", 9),    # 16 items; long
     (3, 12, 12, 8192, 64, "ksplit2x8", 3), (2, 28, 4, 8192, 48, "ksplit2x8", 2), (8, 28, 4, 16384, 16, "ksplit2x8", 2),   # two tiles, slices
+    (1, 4, 1, 4008, 131, "ksplit2x8", 3), (1, 4, 1, 3000, 131, "ksplit2x8", 1), (1, 7, 1, 7026, 153, "ksplit2x8", 3),     # rounds of slices
     (20, 16, 16, 150, 40, "ksplit2x4", 1), (21, 8, 8, 200, 40, "ksplit1x4", 1), (22, 8, 8, 200, 40, "ksplit2x4", 1),        # 64 of 4 wavefronts
     (1, 28, 4, 1024, 9, "ksplit1x8", 3), (1, 28, 4, 1025, 9, "ksplit1x8", 3), (1, 28, 4, 1536, 64, "ksplit1x8", 1)])      # fewer than 8 pairs
 def test_key_split_items_hold_one_query_tile_while_each_has_a_compute_unit(batch, q_heads, kv_heads, seq_len, rows, kernel, splits):
@@ -119,8 +120,8 @@ def test_key_split_items_hold_one_query_tile_while_each_has_a_compute_unit(batch
 
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_key_slices_only_go_into_idle_compute_units(head_dim):
-    """Over the range of the calls: sliced plans make no more workgroups than an XCD has units, no slice is empty, the wavefronts
-    fit the number of items, and 1024 keys are no line for few pairs."""
+    """Over the range of the calls: up to 2000 keys sliced plans make no more workgroups than an XCD has units, never more than four
+    rounds; no slice is empty, the wavefronts fit the number of items, and 1024 keys are no line for few pairs."""
     sliced = 0
     for batch in (1, 2, 3, 5, 8, 13, 16):
         for q_heads, kv_heads in ((32, 32), (28, 4), (24, 8), (8, 1), (12, 12)):
@@ -130,12 +131,30 @@ def test_key_slices_only_go_into_idle_compute_units(head_dim):
                     p = attn_plan(D.AttnUpdateShape(batch, q_heads, kv_heads, seq_len, head_dim, dtype=BF16), min(rows, seq_len))
                     if not p.ksplit_nq:
                         continue
-                    assert p.q_groups == -(-p.q_tiles // p.ksplit_nq) and (p.ksplit_waves == 8) == (per_xcd * p.q_groups <= 32)
+                    assert p.q_groups == -(-p.q_tiles // p.ksplit_nq) and (p.ksplit_waves == 8) == (per_xcd * p.q_groups <= 32 or p.splits > 1)
                     tiles = -(-seq_len // 32)
                     assert (p.splits - 1) * p.tiles_per_split < tiles <= p.splits * p.tiles_per_split
                     if p.splits > 1:
                         sliced += 1
-                        assert per_xcd * p.q_groups * p.splits <= 32 and tiles * head_dim >= 24 * 128
+                        assert per_xcd * p.q_groups * p.splits <= (32 if seq_len <= 2048 else 128) and tiles * head_dim >= 24 * 128
     assert sliced > 500
     small, large = (attn_plan(D.AttnUpdateShape(1, 28, 4, n, 128, dtype=BF16), 64) for n in (1024, 1025))
     assert (small.kernel, small.splits) == (large.kernel, large.splits)
+
+
+def test_every_call_has_a_plan_within_the_static_scratch():
+    """dkv_attn_update_static refuses no call for its size: where the records of the plan exceed its array, the plan within it."""
+    from paper_2505_15781_amd import binding as b
+    limit, shrunk = b.STATIC_SCRATCH_BYTES, 0
+    for batch in (1, 2, 4, 7, 16, 31):
+        for q_heads, kv_heads in ((32, 32), (28, 4), (56, 8), (8, 1), (3, 1), (190, 38)):
+            for seq_len in (768, 1543, 2211, 5749, 15590, 40156):
+                for rows in (1, 4, 7, 16, 26, 49, 115, 300):
+                    s = D.AttnUpdateShape(batch, q_heads, kv_heads, seq_len, 128, dtype=BF16)
+                    p, free = attn_plan_within(limit, s, rows), attn_plan(s, rows)
+                    record = batch * -(-p.q_tiles * 16 // (q_heads // kv_heads)) * q_heads * (128 + 4) * 4
+                    assert p.splits == 1 or record * p.splits <= limit
+                    fits = free.splits == 1 or record * free.splits <= limit
+                    assert not fits or (p.kernel, p.splits) == (free.kernel, free.splits)
+                    shrunk += not fits
+    assert shrunk > 50

@@ -57,6 +57,6 @@ def test_static_scratch_entry_matches_the_workspace_entry_on_two_calls_in_a_row(
 
 
 def test_static_scratch_entry_takes_fewer_key_slices_where_their_records_do_not_fit():
-    """The plan's records (four slices) exceed the static array by 5 %: three slices, on both sides of the same result."""
-    shape = D.AttnUpdateShape(batch=2, n_q_heads=20, n_kv_heads=4, seq_len=1543, head_dim=128, dtype=BF16)
-    _both_entries(shape, [49, 33], 63, fits=False)
+    """The plan's records (four slices) exceed the static array by 13 %: one with fewer is taken, on both sides of the same result."""
+    shape = D.AttnUpdateShape(batch=4, n_q_heads=56, n_kv_heads=8, seq_len=2211, head_dim=128, dtype=BF16)
+    _both_entries(shape, [7, 0, 3, 5], 63, fits=False)
